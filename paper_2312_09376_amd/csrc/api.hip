@@ -958,12 +958,13 @@ int gepp_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_t lda, dou
   RBT_HIP_CHECK(launch_copy_cols(n, n, A, lda, LU, ldlu, s));
   {
     StageScope t(kStagePivoted, s, 2.0 / 3.0 * double(n) * n * n);
-    RBT_HIP_CHECK(launch_gepp(n, LU, ldlu, ipiv, info, at<char>(work, L.o_gscr), s));
+    // (scratch: the diagonal inverses' area, which is formed afterwards)
+    RBT_HIP_CHECK(clear_sweep_err(sync, s));
+    RBT_HIP_CHECK(launch_gepp(n, LU, ldlu, ipiv, info, winv, L.winv, sync + kSweepErrWord, s));
   }
   RBT_HIP_CHECK(launch_ipiv_to_perm(n, ipiv, perm, s));
   int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(clear_sweep_err(sync, s));
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   rc = gepp_apply(n, nrhs, LU, ldlu, perm, X, ldx, ygat, winv, sync, s);
   if (rc) return rc;
@@ -1461,7 +1462,7 @@ extern "C" int rbt_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv_dev, in
   if (info_dev) RBT_HIP_CHECK(launch_fill_i32(info_dev, 0, s));
   if (n == 0) return 0;
   StageScope t(kStagePivoted, s, 2.0 / 3.0 * double(n) * n * n);
-  RBT_HIP_CHECK(launch_gepp(n, A, lda, ipiv_dev, info_dev, work, s));
+  RBT_HIP_CHECK(launch_gepp(n, A, lda, ipiv_dev, info_dev, work, work_bytes, nullptr, s));
   return 0;
 }
 

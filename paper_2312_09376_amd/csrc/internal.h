@@ -316,12 +316,16 @@ inline int64_t batched_sys_doubles(int64_t n, int64_t nrhs, int d) {
 // k_gepp.hip : elimination with partial pivoting (the robust re-solve of the
 // Sec. 5 fallback). launch_gepp factors A in place (P A = L U, ipiv 1-based
 // as LAPACK's getrf; *info = first zero pivot column, 1-based) using
-// gepp_scratch_bytes() of scratch; launch_ipiv_to_perm turns ipiv into
+// scratch_bytes >= gepp_scratch_bytes() of scratch, and the faster slab
+// kernel from gepp_slab_bytes(n) on; *err (nullable) is set when an exchange of
+// the slab kernel waited longer than sweep_spin_limit() (its rows are then NaN).
+// launch_ipiv_to_perm turns ipiv into
 // perm[i] = original row of row i; launch_gather_rows: Y[i, :] = B[perm[i], :].
 constexpr int64_t kPermLdsMax = 16384;  // ipiv_to_perm works in LDS up to this n
 size_t gepp_scratch_bytes();
+size_t gepp_slab_bytes(int64_t n);
 hipError_t launch_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv, int32_t *info,
-                       void *scratch, hipStream_t s);
+                       void *scratch, size_t scratch_bytes, int32_t *err, hipStream_t s);
 hipError_t launch_ipiv_to_perm(int64_t n, const int64_t *ipiv, int64_t *perm, hipStream_t s);
 hipError_t launch_gather_rows(int64_t n, int64_t nrhs, const int64_t *perm, const double *B,
                               int64_t ldb, double *Y, int64_t ldy, hipStream_t s);
