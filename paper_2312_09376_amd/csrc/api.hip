@@ -511,18 +511,33 @@ int genp_fp64(int64_t n, double *A, int64_t lda, int32_t *info, hipStream_t s) {
   return genp_impl(n, A, lda, info, RBT_FP64, s);
 }
 
-// B <- (LU)^-1 B (trans = 0) or (LU)^-T B (trans = 1): block solves with the
-// diagonal blocks (k_trsm.hip) and updates of the remaining rows, by the
-// FMA kernel for few right-hand sides and the matrix-core GEMM otherwise.
+// Right-hand sides of FP64 factors that are solved by sweeps: up to kSkinnyMax
+// always, up to kSweepWide where the caller has a publication buffer of
+// n * nrhs doubles for them (pub). A sweep costs its chain of blocks, whatever
+// the number of groups of 16, until the groups' reads of the factors outweigh
+// it; the block solves cost two launches per block and grow little with nrhs.
+// Sweeps / block solves, both directions of one solve, in ms: n = 5003 1.07 / 2.13
+// (64) and 1.35 / 2.38 (384); n = 20000 5.07 / 9.56 (64), 9.8 / 12.4 (256), 13.8 / 14.4
+// (384) and 18.4 / 16.3 (512 right-hand sides).
+constexpr int64_t kSweepWide = 384;
+bool by_sweeps(int64_t nrhs, const double *pub) {
+  return nrhs <= kSkinnyMax || (nrhs <= kSweepWide && pub != nullptr);
+}
+
+// B <- (LU)^-1 B (trans = 0) or (LU)^-T B (trans = 1): persistent sweeps with
+// the inverses of the diagonal blocks (by_sweeps), else block solves with the
+// diagonal blocks (k_trsm.hip) and updates of the remaining rows by the
+// matrix-core GEMM.
 int getrs_fp64(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-               int trans, const double *winv, int32_t *sync, hipStream_t s) {
+               int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s) {
   if (n == 0 || nrhs == 0) return 0;
-  if (nrhs <= kSkinnyMax) {
+  if (by_sweeps(nrhs, pub)) {
     // one persistent launch per sweep: inverse + one refinement step per block
+    double *P = nrhs <= kSkinnyMax ? nullptr : pub;
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::UT : TriMode::LN, n, nrhs, LU, ld, winv, B, ldb,
-                               sync, s));
+                               sync, s, P));
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::LT : TriMode::UN, n, nrhs, LU, ld, winv, B, ldb,
-                               sync, s));
+                               sync, s, P));
     return 0;
   }
   const int64_t nb = nblocks(n);
@@ -593,14 +608,14 @@ hipError_t transform_v_t(const Geometry &g, int64_t nrhs, double *B, int64_t ldb
   return transform_vec_t(g, nrhs, B, ldb, V, op, s);
 }
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, hipStream_t s) {
+            int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s) {
   StageScope t(kStageSolve, s, 2.0 * double(n) * n * nrhs);
-  return getrs_fp64(n, nrhs, LU, ld, B, ldb, trans, winv, sync, s);
+  return getrs_fp64(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s);
 }
-// Inverses of the diagonal blocks, needed by the few-right-hand-side solves.
+// Inverses of the diagonal blocks, needed by the solves by sweeps.
 int diag_inverses_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *winv,
-                    hipStream_t s) {
-  if (nrhs > kSkinnyMax || n == 0) return 0;
+                    const double *pub, hipStream_t s) {
+  if (!by_sweeps(nrhs, pub) || n == 0) return 0;
   StageScope t(kStageSolve, s, 2.0 / 3.0 * double(n) * kNB * kNB);
   RBT_HIP_CHECK(launch_diag_inverses(n, LU, ld, winv, s));
   return 0;
@@ -621,25 +636,29 @@ int diag_inverses_t(int64_t n, const float *LU, int64_t ld, double *winv, bool f
   return 0;
 }
 // B <- (LU)^-1 B or (LU)^-T B with FP32 factors and FP64 right-hand sides:
-// sweeps over groups of at most kSkinnyMax columns, in FP32 arithmetic (the
+// sweeps, groups of kSkinnyMax columns side by side in one launch where the
+// caller has a publication buffer of n * nrhs doubles (pub), else one after
+// another, in FP32 arithmetic (the
 // right-hand side rounded to FP32 on load, the result widened on store), or
 // in FP64 arithmetic (f64: the FP64-inner option, and the preconditioner of
 // GMRES-IR, which that method applies in the working precision). The
 // inverses must have been formed by diag_inverses_t with the same f64.
 int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, bool f64, hipStream_t s) {
+            int trans, const double *winv, int32_t *sync, double *pub, bool f64, hipStream_t s) {
   StageScope t(kStageSolve, s, 2.0 * double(n) * n * nrhs);
   const float *winv32 = reinterpret_cast<const float *>(winv);
-  for (int64_t c0 = 0; c0 < nrhs; c0 += kSkinnyMax) {
-    const int64_t nc = nrhs - c0 < kSkinnyMax ? nrhs - c0 : kSkinnyMax;
+  const int64_t step = pub != nullptr && nrhs > kSkinnyMax ? nrhs : kSkinnyMax;
+  double *P = nrhs > kSkinnyMax ? pub : nullptr;
+  for (int64_t c0 = 0; c0 < nrhs; c0 += step) {
+    const int64_t nc = nrhs - c0 < step ? nrhs - c0 : step;
     double *Bc = B + c0 * ldb;
     for (int pass = 0; pass < 2; ++pass) {
       const TriMode m = pass == 0 ? (trans ? TriMode::UT : TriMode::LN)
                                   : (trans ? TriMode::LT : TriMode::UN);
       if (f64)
-        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv, Bc, ldb, sync, s));
+        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv, Bc, ldb, sync, s, P));
       else
-        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv32, Bc, ldb, sync, s));
+        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv32, Bc, ldb, sync, s, P));
     }
   }
   return 0;
@@ -648,15 +667,16 @@ int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int
 // R <- V (L U)^-1 U^T R: the solve of Eq. 1 with the factors of A~ (f64:
 // arithmetic of the triangular solves with FP32 factors, see getrs_t).
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, bool /*f64*/, hipStream_t s) {
-  return getrs_t(n, nrhs, LU, ld, B, ldb, trans, winv, sync, s);
+            int trans, const double *winv, int32_t *sync, double *pub, bool /*f64*/,
+            hipStream_t s) {
+  return getrs_t(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s);
 }
 template <typename TF>
 int apply_solve(const Geometry &g, int64_t nrhs, const TF *LU, int64_t ld, double *R, int64_t ldr,
-                const double *U, const double *V, const double *winv, int32_t *sync, bool f64,
-                hipStream_t s) {
+                const double *U, const double *V, const double *winv, int32_t *sync, double *pub,
+                bool f64, hipStream_t s) {
   RBT_HIP_CHECK(transform_vec_t(g, nrhs, R, ldr, U, RBT_OP_T, s));
-  const int rc = getrs_t(g.n, nrhs, LU, ld, R, ldr, 0, winv, sync, f64, s);
+  const int rc = getrs_t(g.n, nrhs, LU, ld, R, ldr, 0, winv, sync, pub, f64, s);
   if (rc) return rc;
   RBT_HIP_CHECK(transform_v_t(g, nrhs, R, ldr, V, RBT_OP_N, s));
   return 0;
@@ -671,8 +691,9 @@ template <typename TF>
 int refine_classic(int64_t n, int64_t nrhs, const double *A, int64_t lda, const TF *LU,
                    int64_t ldlu, const double *B, int64_t ldb, double *X, int64_t ldx,
                    const Geometry &g, const double *U, const double *V, const double *winv,
-                   int32_t *sync, double *R, double *scratch, double *anorm, double *berr, double tol,
-                   int max_iter, int *it_out, bool f64, hipStream_t s, bool *stalled = nullptr) {
+                   int32_t *sync, double *pub, double *R, double *scratch, double *anorm,
+                   double *berr, double tol, int max_iter, int *it_out, bool f64, hipStream_t s,
+                   bool *stalled = nullptr) {
   int it = 0;
   double be_prev = 0.0;
   for (;;) {
@@ -693,7 +714,7 @@ int refine_classic(int64_t n, int64_t nrhs, const double *A, int64_t lda, const 
       break;
     }
     be_prev = be_host;
-    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, f64, s);
+    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, pub, f64, s);
     if (rc) return rc;
     RBT_HIP_CHECK(launch_axpy_cols(n, nrhs, R, n, X, ldx, s));
     ++it;
@@ -726,7 +747,7 @@ int refine_classic_device(int64_t n, int64_t nrhs, const double *A, int64_t lda,
   RefineGate on(gate);
   for (int it = 0; it < max_iter; ++it) {
     RBT_HIP_CHECK(launch_refine_step(berr, tol, gate, iters, s));
-    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, f64, s);
+    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, nullptr, f64, s);
     if (rc) return rc;
     RBT_HIP_CHECK(launch_axpy_cols(n, nrhs, R, n, X, ldx, s));
     StageScope t(kStageResidual, s, 8.0 * double(n) * n);
@@ -793,7 +814,7 @@ int refine_gmres(int64_t n, int64_t nrhs, const double *A, int64_t lda, const TF
       }
       bool stop = false;
       // z = M^-1 r, v_0 = z / ||z||
-      rc = apply_solve(g, nc, LU, ldlu, R, n, U, V, winv, sync, true, s);
+      rc = apply_solve(g, nc, LU, ldlu, R, n, U, V, winv, sync, nullptr, true, s);
       if (rc) return rc;
       RBT_HIP_CHECK(launch_coldots(n, nc, 1, R, 0, R, n, nrm, s));
       RBT_HIP_CHECK(launch_colscale(n, nc, R, n, nrm, Vb, s));
@@ -818,7 +839,7 @@ int refine_gmres(int64_t n, int64_t nrhs, const double *A, int64_t lda, const TF
           StageScope t(kStageResidual, s, 8.0 * double(n) * n);
           RBT_HIP_CHECK(launch_matvec(n, nc, A, lda, Vj, n, W, n, scratch, s));
         }
-        rc = apply_solve(g, nc, LU, ldlu, W, n, U, V, winv, sync, true, s);
+        rc = apply_solve(g, nc, LU, ldlu, W, n, U, V, winv, sync, nullptr, true, s);
         if (rc) return rc;
         RBT_HIP_CHECK(launch_coldots(n, nc, j + 1, Vb, vs, W, n, dots, s));
         RBT_HIP_CHECK(launch_colcombo(n, nc, j + 1, Vb, vs, dots, -1.0, W, n, s));
@@ -935,7 +956,7 @@ int gepp_apply(int64_t n, int64_t nrhs, const double *LU, int64_t ld, const int6
                hipStream_t s) {
   RBT_HIP_CHECK(launch_gather_rows(n, nrhs, perm, R, ldr, ygat, n, s));
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, ygat, n, R, ldr, s));
-  return getrs_t(n, nrhs, LU, ld, R, ldr, 0, winv, sync, s);
+  return getrs_t(n, nrhs, LU, ld, R, ldr, 0, winv, sync, ygat, s);
 }
 
 // GEPP of A (copied into LU) and the solve X = A^-1 B, then classical FP64
@@ -963,7 +984,7 @@ int gepp_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_t lda, dou
     RBT_HIP_CHECK(launch_gepp(n, LU, ldlu, ipiv, info, winv, L.winv, sync + kSweepErrWord, s));
   }
   RBT_HIP_CHECK(launch_ipiv_to_perm(n, ipiv, perm, s));
-  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, ygat, s);
   if (rc) return rc;
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   rc = gepp_apply(n, nrhs, LU, ldlu, perm, X, ldx, ygat, winv, sync, s);
@@ -1064,10 +1085,13 @@ extern "C" int rbt_getrs(int64_t n, int64_t nrhs, const double *LU, int64_t ldlu
   hipStream_t s = S(stream);
   double *winv = at<double>(work, L.o_winv);
   int32_t *sync = at<int32_t>(work, L.o_sync);
+  // (a workspace that ends after the sweeps' area has no publication buffer
+  // for more than kSkinnyMax right-hand sides)
+  double *pub = work_bytes >= L.total ? at<double>(work, L.o_ygat) : nullptr;
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
-  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
   if (rc) return rc;
-  return getrs_fp64(n, nrhs, LU, ldlu, B, ldb, trans, winv, sync, s);
+  return getrs_fp64(n, nrhs, LU, ldlu, B, ldb, trans, winv, sync, pub, s);
 }
 
 extern "C" int rbt_solve_ex(int64_t n, int64_t nrhs, double *A, int64_t lda, double *B, int64_t ldb,
@@ -1094,10 +1118,11 @@ extern "C" int rbt_solve_ex(int64_t n, int64_t nrhs, double *A, int64_t lda, dou
   double *winv = at<double>(work, L.o_winv);
   int rc = genp_fp64(n, A, lda, info_dev, s);
   if (rc) return rc;
-  rc = diag_inverses_t(n, nrhs, A, lda, winv, s);
+  double *pub = at<double>(work, L.o_ygat);
+  rc = diag_inverses_t(n, nrhs, A, lda, winv, pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(clear_sweep_err(at<int32_t>(work, L.o_sync), s));
-  rc = getrs_t(n, nrhs, A, lda, B, ldb, 0, winv, at<int32_t>(work, L.o_sync), s);
+  rc = getrs_t(n, nrhs, A, lda, B, ldb, 0, winv, at<int32_t>(work, L.o_sync), pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(transform_v_t(g, nrhs, B, ldb, V, RBT_OP_N, s));
   return 0;
@@ -1221,12 +1246,13 @@ extern "C" int rbt_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_
   double *winv = at<double>(work, L.o_winv);
   int rc = genp_fp64(n, LU, ldlu, info_dev, s);
   if (rc) return rc;
-  rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+  double *pub = at<double>(work, L.o_ygat);
+  rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   int32_t *sync = at<int32_t>(work, L.o_sync);
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
-  rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, true, s);
+  rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, pub, true, s);
   if (rc) return rc;
   if (options().capturable) {
     // no host test: an expired sweep wait shows as a NaN backward error
@@ -1236,8 +1262,8 @@ extern "C" int rbt_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_
                                  words, iters_dev ? iters_dev : words + 1, true, s);
   }
   int it = 0;
-  rc = refine_classic(n, nrhs, A, lda, (const double *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv, sync, R,
-                      scratch, anorm, berr, tol, max_iter, &it, true, s);
+  rc = refine_classic(n, nrhs, A, lda, (const double *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv, sync,
+                      pub, R, scratch, anorm, berr, tol, max_iter, &it, true, s);
   if (rc) return rc;
   if (iters_dev)
     RBT_HIP_CHECK(hipMemcpyAsync(iters_dev, &it, sizeof(int32_t), hipMemcpyHostToDevice, s));
@@ -1298,7 +1324,8 @@ int mixed_impl(int64_t n, int64_t nrhs, const double *A, int64_t lda, float *LU,
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   int32_t *sync = at<int32_t>(work, L.o_sync);
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
-  rc = apply_solve(g, nrhs, (const float *)LU, ldlu, X, ldx, U, V, winv, sync, f64, s);
+  double *pub = at<double>(work, L.o_ygat);
+  rc = apply_solve(g, nrhs, (const float *)LU, ldlu, X, ldx, U, V, winv, sync, pub, f64, s);
   if (rc) return rc;
   if (iters_cap != nullptr) {
     int32_t *words = reinterpret_cast<int32_t *>(small + 32);
@@ -1312,7 +1339,7 @@ int mixed_impl(int64_t n, int64_t nrhs, const double *A, int64_t lda, float *LU,
                       it_out, s, stalled);
   else
     rc = refine_classic(n, nrhs, A, lda, (const float *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv,
-                        sync, R, scratch, anorm, berr, tol, max_iter, it_out, f64, s, stalled);
+                        sync, pub, R, scratch, anorm, berr, tol, max_iter, it_out, f64, s, stalled);
   if (rc) return rc;
   return read_sweep_err(sync, s);  // synchronizes
 }
@@ -1416,15 +1443,16 @@ extern "C" int rbt_solve_mixed_guarded(int64_t n, int64_t nrhs, const double *A,
     RBT_HIP_CHECK(transform2_t(g, A, lda, LU64, ldlu64, RBT_FP64, U, V, s));
     rc = genp_fp64(n, LU64, ldlu64, info_dev ? info_dev + 1 : nullptr, s);
     if (rc) return rc;
-    rc = diag_inverses_t(n, nrhs, LU64, ldlu64, winv, s);
+    double *pub = at<double>(work, L.o_ygat);
+    rc = diag_inverses_t(n, nrhs, LU64, ldlu64, winv, pub, s);
     if (rc) return rc;
     RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
-    rc = apply_solve(g, nrhs, (const double *)LU64, ldlu64, X, ldx, U, V, winv, sync, true, s);
+    rc = apply_solve(g, nrhs, (const double *)LU64, ldlu64, X, ldx, U, V, winv, sync, pub, true, s);
     if (rc) return rc;
     int it64 = 0;
     bool stalled64 = false;
     rc = refine_classic(n, nrhs, A, lda, (const double *)LU64, ldlu64, B, ldb, X, ldx, g, U, V,
-                        winv, sync, at<double>(work, L.o_resid), at<double>(work, L.o_partial),
+                        winv, sync, pub, at<double>(work, L.o_resid), at<double>(work, L.o_partial),
                         small, berr, tol, max_iter64, &it64, true, s, &stalled64);
     if (rc) return rc;
     its[1] = it64;
@@ -1486,7 +1514,7 @@ extern "C" int rbt_gepp_solve(int64_t n, int64_t nrhs, const double *LU, int64_t
   int32_t *sync = at<int32_t>(work, L.o_sync);
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
   RBT_HIP_CHECK(launch_ipiv_to_perm(n, ipiv_dev, perm, s));
-  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, at<double>(work, L.o_ygat), s);
   if (rc) return rc;
   return gepp_apply(n, nrhs, LU, ldlu, perm, B, ldb, at<double>(work, L.o_ygat), winv, sync, s);
 }
@@ -1531,16 +1559,17 @@ extern "C" int rbt_solve_guarded(int64_t n, int64_t nrhs, const double *A, int64
     RBT_HIP_CHECK(transform2_t(g, A, lda, LU, ldlu, RBT_FP64, U, V, s));
     int rc = genp_fp64(n, LU, ldlu, info_dev, s);
     if (rc) return rc;
-    rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+    double *pub = at<double>(work, L.o_ygat);
+    rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
     if (rc) return rc;
     RBT_HIP_CHECK(clear_sweep_err(sync, s));
     RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
-    rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, true, s);
+    rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, pub, true, s);
     if (rc) return rc;
     int it = 0;
     bool stalled = false;
     rc = refine_classic(n, nrhs, A, lda, (const double *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv,
-                        sync, at<double>(work, L.o_resid), at<double>(work, L.o_partial), small,
+                        sync, pub, at<double>(work, L.o_resid), at<double>(work, L.o_partial), small,
                         berr, tol, max_iter, &it, true, s, &stalled);
     if (rc) return rc;
     its[0] = it;
@@ -1712,7 +1741,8 @@ extern "C" int rbt_solve_backward_mixed(int64_t n, int64_t nrhs, const float *LU
   if (rc) return rc;
   auto adjoint_solve = [&](double *Y, int64_t ldy) -> int {
     RBT_HIP_CHECK(transform_v_t(g, nrhs, Y, ldy, V, RBT_OP_T, s));
-    const int r = getrs_t(n, nrhs, LU, ldlu, Y, ldy, 1, winv, sync, f64, s);
+    const int r = getrs_t(n, nrhs, LU, ldlu, Y, ldy, 1, winv, sync, at<double>(work, L.o_ygat), f64,
+                          s);
     if (r) return r;
     RBT_HIP_CHECK(transform_vec_t(g, nrhs, Y, ldy, U, RBT_OP_N, s));
     return 0;
@@ -1858,10 +1888,11 @@ extern "C" int rbt_solve_backward(int64_t n, int64_t nrhs, const double *LU, int
   RBT_HIP_CHECK(generate_t(n, depth, seed, U, V, s));
   RBT_HIP_CHECK(launch_copy_cols(n, nrhs, G, ldg, dB, lddb, s));
   RBT_HIP_CHECK(transform_v_t(g, nrhs, dB, lddb, V, RBT_OP_T, s));
-  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, s);
+  double *pub = at<double>(work, L.o_ygat);
+  int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(clear_sweep_err(at<int32_t>(work, L.o_sync), s));
-  rc = getrs_t(n, nrhs, LU, ldlu, dB, lddb, 1, winv, at<int32_t>(work, L.o_sync), s);
+  rc = getrs_t(n, nrhs, LU, ldlu, dB, lddb, 1, winv, at<int32_t>(work, L.o_sync), pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(transform_vec_t(g, nrhs, dB, lddb, U, RBT_OP_N, s));
   if (dA != nullptr) {

@@ -214,13 +214,19 @@ constexpr int kSweepErrWord = 3;
 // Sleeps a sweep's wait may take before it expires (rbt_set_option
 // RBT_OPT_SWEEP_SPIN_LIMIT; negative: every wait expires at once).
 int64_t sweep_spin_limit();
+// pub: publication buffer of n * nrhs doubles elsewhere, for any number of
+// right-hand sides (groups of kSkinnyMax side by side); null: the one in the
+// sync area, nrhs <= kSkinnyMax.
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const double *LU, int64_t ld,
-                        const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s);
+                        const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
+                        double *pub = nullptr);
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
-                        const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s);
+                        const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
+                        double *pub = nullptr);
 // FP32 arithmetic with FP32 inverses (B stays FP64 storage)
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
-                        const float *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s);
+                        const float *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
+                        double *pub = nullptr);
 // doubles of scratch needed by launch_residual_berr
 size_t resid_scratch_doubles(int64_t n, int64_t nrhs);
 // R = B - A X; berr = Eq. 7 (max over columns); with_anorm: also ||A||_inf -> *anorm

@@ -1,4 +1,4 @@
-// Triangular sweeps for few right-hand sides (nrhs <= 16) as ONE persistent
+// Triangular sweeps for few right-hand sides (groups of 16) as ONE persistent
 // launch per sweep, for the solves after the elimination (Sec. 1, step 3:
 // L y = b~, U x~ = y) and the adjoint solves.
 //
@@ -31,8 +31,31 @@
 // block's solution, so the result can never be a silently wrong finite
 // vector, and goes on, so the grid always drains.
 //
-// Layout: 512 threads = 128 rows x 4 column segments of 32; products of a
-// 128 x 128 block with the x block are reduced over the segments in LDS.
+// Layout: 512 threads = 8 wavefronts of 16 rows each. A wavefront forms whole
+// rows of a product of a 128 x 128 block with the x block, so nothing is
+// reduced across wavefronts and each of the up to four products on the
+// critical path (the last block's, and three with the diagonal block) costs
+// one barrier. One right-hand side: a row belongs to a quad of lanes, 32
+// columns each, summed over the quad by DPP. More: the matrix cores, a lane
+// holding row l % 16 and every fourth group of columns of the block
+// (16x16x4 products for 9 to 16 right-hand sides and in FP32; in FP64 up to
+// 8 the 4x4x4 product on four row groups, whose cost goes with the
+// right-hand sides: 16 cycles per four of them against 64 for sixteen). With
+// lanes on 128 rows x 4 segments, FMA loops over x in LDS and a sum over the
+// segments through LDS after each product, the step from block to block was
+// LDS-bound for several right-hand sides. Microseconds per block then and now
+// (FP64, n = 4096, not transposed / transposed): 16 right-hand sides 43 / 48 and
+// 12.6, 8 of them 14.9 / 19.6 and 7.4, 4 of them 9.0 / 13.7 and 4.2 / 4.9, one 5.2 / 7.9
+// and 3.2 / 3.4 (n = 20000: 5.8 / 10.0 and 4.0).
+//
+// Columns of a block are dealt to the lanes of a row in pairs (FP64; groups
+// of four in FP32): step q = qq V + h takes column qq 4 V + sl V + h in lane
+// group sl, so that the transposed modes, where a row is contiguous, read
+// 64-byte runs with 16-byte loads.
+//
+// More than 16 right-hand sides are groups of 16 in the same launch, their
+// tickets interleaved: the groups run side by side, each on its own chain,
+// and share the blocks through the caches.
 //
 // Arithmetic type C: FP64 for FP64 factors. For the FP32 factors of the
 // mixed-precision solve it is FP32: the right-hand side (FP64 storage, the
@@ -43,22 +66,14 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "mma16.h"
 
 namespace rbt {
 
 namespace {
 
 constexpr int TPB = 512;
-constexpr int SEG = 4;
-constexpr int SEGW = kNB / SEG;  // 32 columns per segment
-
-template <TriMode MODE, typename TF>
-__device__ __forceinline__ TF op_e(const TF *A, int64_t ld, int64_t m, int64_t k) {
-  if constexpr (MODE == TriMode::LN || MODE == TriMode::UN)
-    return A[m + k * ld];
-  else
-    return A[k + m * ld];
-}
+constexpr int STEPS = 32;  // columns per lane of a 128-wide block
 
 __device__ __forceinline__ double coherent_load(const double *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -73,362 +88,463 @@ constexpr uint64_t kUnpublished = 0x7FF4B1A5C0DE0001ull;
 __device__ __forceinline__ bool unpublished(double v) {
   return __builtin_bit_cast(uint64_t, v) == kUnpublished;
 }
-// P: 256 bytes after the start of the sync area, column c at P + c n.
+// P of the single group: 256 bytes after the start of the sync area.
 constexpr int kSyncPubOffsetInts = 64;
 
-template <int NMAX, TriMode MODE, typename TF, bool REFINE, typename C>
+// Sums over the four lanes that share a row (the same in all four): a quad,
+// or the lanes l, l + 16, l + 32, l + 48.
+template <typename C>
+__device__ __forceinline__ C quad_sum(C v) {
+  const C a = quad_bcast_k<0>(v) + quad_bcast_k<1>(v);
+  const C b = quad_bcast_k<2>(v) + quad_bcast_k<3>(v);
+  return a + b;
+}
+// v[l] + v[l ^ 32], v[l] + v[l ^ 16]: swapping halves (rows) of two copies of v
+// leaves one half (the even rows) in the first, the other in the second.
+template <bool HALVES>
+__device__ __forceinline__ uint2 swap_copies(unsigned v) {
+  if constexpr (HALVES) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return uint2{r[0], r[1]};
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return uint2{r[0], r[1]};
+  }
+}
+template <bool HALVES>
+__device__ __forceinline__ float add_swapped(float v) {
+  const uint2 r = swap_copies<HALVES>(unsigned(__float_as_int(v)));
+  return __int_as_float(int(r.x)) + __int_as_float(int(r.y));
+}
+template <bool HALVES>
+__device__ __forceinline__ double add_swapped(double v) {
+  const uint2 lo = swap_copies<HALVES>(unsigned(__double2loint(v)));
+  const uint2 hi = swap_copies<HALVES>(unsigned(__double2hiint(v)));
+  return __hiloint2double(int(hi.x), int(lo.x)) + __hiloint2double(int(hi.y), int(lo.y));
+}
+
+// Product of the wavefront's 16 rows of a 128 x 128 block (STEPS entries per
+// lane: row rl, columns of lane group sl) with the x block in LDS. NT
+// right-hand sides; the result has NV values per lane, value v at row
+// row(v), right-hand side col(v). XN: values of x per LDS row.
+template <int NT, bool TRANS, typename C>
+struct Prod;
+
+// One right-hand side: four lanes per row, such that consecutive lanes read
+// consecutive memory: a quad where rows are contiguous (TRANS), else the lanes
+// l, l + 16, l + 32, l + 48.
+template <bool TRANS, typename C>
+struct Prod<1, TRANS, C> {
+  static constexpr int NV = 1, XN = 1;
+  static __device__ __forceinline__ int rl(int lane) { return TRANS ? lane >> 2 : lane & 15; }
+  static __device__ __forceinline__ int sl(int lane) { return TRANS ? lane & 3 : lane >> 4; }
+  static __device__ __forceinline__ int row(int lane, int) { return rl(lane); }
+  static __device__ __forceinline__ int col(int, int) { return 0; }
+  static __device__ __forceinline__ bool owns(int lane) { return sl(lane) == 0; }
+  template <int V>
+  static __device__ __forceinline__ int slot(int k) { return k; }
+  template <int V>
+  static __device__ __forceinline__ void mul(const C (&e)[STEPS], const C *xs, int lane,
+                                             C (&out)[NV]) {
+    const C *x = xs + sl(lane) * V;
+    C a[4] = {C(0), C(0), C(0), C(0)};
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q)
+      a[q & 3] = fma_c(e[q], x[(q / V) * 4 * V + q % V], a[q & 3]);
+    const C v = (a[0] + a[1]) + (a[2] + a[3]);
+    if constexpr (TRANS)
+      out[0] = quad_sum(v);
+    else
+      out[0] = add_swapped<false>(add_swapped<true>(v));
+  }
+};
+
+// Matrix cores, 16 x 16 x 4. LDS row of column k: the rows of one step's four
+// lane groups are neighbours (conflict-free reads); 17 apart.
+template <bool TRANS, typename C>
+struct Prod<16, TRANS, C> {
+  typedef Mma16<C> M;
+  static constexpr int NV = 4, XN = 17;
+  static __device__ __forceinline__ int rl(int lane) { return lane & 15; }
+  static __device__ __forceinline__ int sl(int lane) { return lane >> 4; }
+  static __device__ __forceinline__ int row(int lane, int v) { return M::row(lane >> 4, v); }
+  static __device__ __forceinline__ int col(int lane, int) { return lane & 15; }
+  static __device__ __forceinline__ bool owns(int) { return true; }
+  template <int V>
+  static __device__ __forceinline__ int slot(int k) {
+    return 4 * ((k / (4 * V)) * V + k % V) + (k / V) % 4;
+  }
+  template <int V>
+  static __device__ __forceinline__ void mul(const C (&e)[STEPS], const C *xs, int lane,
+                                             C (&out)[NV]) {
+    const C *x = xs + (lane >> 4) * XN + (lane & 15);
+    typename M::v4 a0 = {C(0), C(0), C(0), C(0)}, a1 = a0;
+#pragma unroll
+    for (int q = 0; q < STEPS; q += 2) {
+      a0 = M::mma(e[q], x[4 * q * XN], a0);
+      a1 = M::mma(e[q + 1], x[4 * (q + 1) * XN], a1);
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = a0[v] + a1[v];
+  }
+};
+
+// FP64 matrix cores, 4 x 4 x 4 on four blocks of rows: lane l supplies
+// A[row l % 16][l / 16] (as for 16 x 16 x 4) and B[l / 16][l % 4], and holds
+// row 4 ((l / 4) % 4) + l / 16, column l % 4 of the result.
+template <int NT>
+struct Prod4 {
+  static constexpr int NV = NT / 4, XN = NT + 1;
+  static __device__ __forceinline__ int rl(int lane) { return lane & 15; }
+  static __device__ __forceinline__ int sl(int lane) { return lane >> 4; }
+  static __device__ __forceinline__ int row(int lane, int) {
+    return 4 * ((lane >> 2) & 3) + (lane >> 4);
+  }
+  static __device__ __forceinline__ int col(int lane, int v) { return 4 * v + (lane & 3); }
+  static __device__ __forceinline__ bool owns(int) { return true; }
+  template <int V>
+  static __device__ __forceinline__ int slot(int k) {
+    return 4 * ((k / (4 * V)) * V + k % V) + (k / V) % 4;
+  }
+  template <int V>
+  static __device__ __forceinline__ void mul(const double (&e)[STEPS], const double *xs, int lane,
+                                             double (&out)[NV]) {
+    constexpr int CH = 4 / NV;  // accumulation chains per column group
+    const double *x = xs + (lane >> 4) * XN + (lane & 3);
+    double a[NV][CH];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int h = 0; h < CH; ++h) a[v][h] = 0.0;
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        a[v][q % CH] = __builtin_amdgcn_mfma_f64_4x4x4f64(e[q], x[4 * q * XN + 4 * v], a[v][q % CH],
+                                                          0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      out[v] = a[v][0];
+#pragma unroll
+      for (int h = 1; h < CH; ++h) out[v] += a[v][h];
+    }
+  }
+};
+template <bool TRANS>
+struct Prod<4, TRANS, double> : Prod4<4> {};
+template <bool TRANS>
+struct Prod<8, TRANS, double> : Prod4<8> {};
+
+// The lane's STEPS entries of row m of op(A), columns c0 .. c0 + cb - 1 of the
+// block (cb <= 128, FULL: cb = 128; entries beyond are zero).
+template <bool FULL, TriMode MODE, int V, typename TF, typename C>
+__device__ __forceinline__ void load_block(const TF *A, int64_t ld, int64_t m, int64_t c0, int cb,
+                                           int sl, C (&e)[STEPS]) {
+  constexpr bool TRANS = MODE == TriMode::UT || MODE == TriMode::LT;
+  typedef TF vec __attribute__((ext_vector_type(V), aligned(sizeof(TF))));
+  if constexpr (FULL) {
+    if constexpr (TRANS) {
+      const TF *p = A + c0 + m * ld + sl * V;
+      vec w[STEPS / V];
+#pragma unroll
+      for (int qq = 0; qq < STEPS / V; ++qq) w[qq] = *reinterpret_cast<const vec *>(p + qq * 4 * V);
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q) e[q] = C(w[q / V][q % V]);
+    } else {
+      const TF *p = A + m + (c0 + sl * V) * ld;
+      TF w[STEPS];
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q) w[q] = p[int64_t((q / V) * 4 * V + q % V) * ld];
+#pragma unroll
+      for (int q = 0; q < STEPS; ++q) e[q] = C(w[q]);
+    }
+    return;
+  }
+  TF w[STEPS];  // clamped, unconditional loads, masked afterwards
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q) {
+    const int k = (q / V) * 4 * V + sl * V + q % V;
+    const int64_t kc = c0 + (k < cb ? k : cb - 1);
+    w[q] = TRANS ? A[kc + m * ld] : A[m + kc * ld];
+  }
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q) {
+    const int k = (q / V) * 4 * V + sl * V + q % V;
+    e[q] = k < cb ? C(w[q]) : C(0);
+  }
+}
+
+template <int NT, TriMode MODE, typename TF, bool REFINE, typename C>
 __global__ void __launch_bounds__(TPB)
-    k_sweep(int64_t n, int N, const TF *__restrict__ A, int64_t ld,
-            const C *__restrict__ Winv, double *B, int64_t ldb, int32_t *sync, int64_t nb,
-            int64_t spin_limit, const int32_t *gate) {
+    k_sweep(int64_t n, int64_t nrhs, const TF *__restrict__ A, int64_t ld,
+            const C *__restrict__ Winv, double *B, int64_t ldb, int32_t *sync, double *P,
+            int64_t nb, int groups, int64_t spin_limit, const int32_t *gate) {
   // (the gate is read before any ticket is taken: every workgroup of a gated
   // launch returns here)
   if (gated(gate)) return;
   constexpr bool FWD = (MODE == TriMode::LN || MODE == TriMode::UT);
   constexpr bool UNIT = (MODE == TriMode::LN || MODE == TriMode::LT);
-  __shared__ C xs[kNB][NMAX];
-  __shared__ C part[SEG][kNB][NMAX];
-  __shared__ int64_t tk;
+  constexpr bool TRANS = (MODE == TriMode::UT || MODE == TriMode::LT);
+  typedef Prod<NT, TRANS, C> Pr;
+  constexpr int V = 16 / int(sizeof(TF));
+  constexpr int NV = Pr::NV, XN = Pr::XN;
+  __shared__ __attribute__((aligned(16))) C xs[2][kNB * XN];
+  __shared__ int32_t tk;
+  __shared__ int expired_sh;
 
   const int tid = threadIdx.x;
-  const int i = tid & (kNB - 1), sg = tid >> 7;
-  if (tid == 0) tk = atomicAdd(&sync[0], 1);
-  __shared__ int expired_sh;
-  if (tid == 0) expired_sh = 0;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sl = Pr::sl(lane);
+  const int i = 16 * wave + Pr::rl(lane);  // the lane's row as an operand
+  if (tid == 0) {
+    tk = atomicAdd(&sync[0], 1);
+    expired_sh = 0;
+  }
+  for (int e = tid; e < 2 * kNB * XN; e += TPB) xs[0][e] = C(0);  // unused columns stay zero
   __syncthreads();
-  const int64_t t = tk;
-  if (t >= nb) return;
-  int32_t *err = sync + 3;  // sticky: cleared by the entry points, not per sweep
-  double *pub = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
+  const int64_t ticket = __builtin_amdgcn_readfirstlane(tk);  // (block indices in scalar registers)
+  if (ticket >= nb * groups) return;
+  const int64_t t = ticket / groups;
+  const int64_t c16 = (ticket - t * groups) * kSkinnyMax;  // the group's first right-hand side
+  const int N = int(nrhs - c16 < kSkinnyMax ? nrhs - c16 : kSkinnyMax);
+  B += c16 * ldb;
+  double *pub = P + c16 * n;  // entry (row, c) of the group at pub[row N + c]
+  int32_t *err = sync + kSweepErrWord;  // sticky: cleared by the entry points, not per sweep
   const int64_t b = FWD ? t : nb - 1 - t;
   const int64_t r0 = b * kNB;
   const int kb = int(n - r0 < kNB ? n - r0 : kNB);
-  const int ir = i < kb ? i : kb - 1;  // clamped row for loads
+  const int64_t ri = r0 + (i < kb ? i : kb - 1);  // clamped row for loads
 
-  // sum over segments of part -> out (threads of segment 0)
-  auto reduce = [&](const C (&a)[NMAX], C (&out)[NMAX]) {
+  // The diagonal block's inverse, the block itself (masked to its triangle)
+  // and the block's right-hand side do not depend on other blocks: they are
+  // loaded before any wait and leave the critical path of the sweep.
+  C di[STEPS];
+  {
+    const C *Di = Winv + b * 2 * kNB * kNB + (UNIT ? 0 : kNB * kNB);
+    load_block<true, MODE, V, C, C>(Di, int64_t(kNB), int64_t(i), int64_t(0), kNB, sl, di);
 #pragma unroll
-    for (int c = 0; c < NMAX; ++c) part[sg][i][c] = a[c];
-    __syncthreads();
-    if (sg == 0) {
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c)
-        out[c] = (part[0][i][c] + part[1][i][c]) + (part[2][i][c] + part[3][i][c]);
-    }
-    __syncthreads();
-  };
-
-  // The diagonal block's inverse and the block's right-hand side do not
-  // depend on other blocks: up to 8 right-hand sides they are loaded into
-  // registers before any wait and leave the critical path of the sweep;
-  // with 16 and FP32 factors the inverse is loaded right after the last
-  // accumulation; with 16 and FP64 factors at each use.
-  constexpr bool PRE = (NMAX <= 8);
-  const C *Di = Winv + b * 2 * kNB * kNB +
-                ((MODE == TriMode::LN || MODE == TriMode::LT) ? 0 : kNB * kNB);
-  auto load_dinv = [&](C (&ev)[SEGW]) {
-#pragma unroll
-    for (int q = 0; q < SEGW; ++q) {
-      const int jj = sg * SEGW + q;
+    for (int q = 0; q < STEPS; ++q) {
       // Di is a full kNB x kNB allocation; entries beyond kb are masked
-      const C v = (MODE == TriMode::LN || MODE == TriMode::UN) ? Di[i + jj * kNB]
-                                                               : Di[jj + i * kNB];
-      ev[q] = (i < kb && jj < kb) ? v : C(0);
+      const int k = (q / V) * 4 * V + sl * V + q % V;
+      di[q] = (i < kb && k < kb) ? di[q] : C(0);
     }
-  };
-  auto load_tdiag = [&](TF (&e)[SEGW]) {
+  }
+  C td[REFINE ? STEPS : 1];
+  if constexpr (REFINE) {
+    if (kb == kNB)
+      load_block<true, MODE, V, TF, C>(A, ld, ri, r0, kb, sl, td);
+    else
+      load_block<false, MODE, V, TF, C>(A, ld, ri, r0, kb, sl, td);
 #pragma unroll
-    for (int q = 0; q < SEGW; ++q) {
-      const int jj = sg * SEGW + q;
-      e[q] = op_e<MODE>(A, ld, r0 + ir, r0 + (jj < kb ? jj : kb - 1));
+    for (int q = 0; q < STEPS; ++q) {
+      const int k = (q / V) * 4 * V + sl * V + q % V;
+      if (k >= kb || i >= kb) td[q] = C(0);
+      else if (k == i) td[q] = UNIT ? C(1) : td[q];
+      else if (FWD ? (k > i) : (k < i)) td[q] = C(0);
     }
-  };
-  C dpre[PRE ? SEGW : 1];
-  C bpre[PRE ? NMAX : 1];
-  if constexpr (PRE) {
-    load_dinv(dpre);
+  }
+  // the lane's results: rows rv[v] of the block, right-hand sides cv[v]
+  int rv[NV], cv[NV];
+  bool in[NV];
+  C bv[NV];
 #pragma unroll
-    for (int c = 0; c < NMAX; ++c)
-      bpre[c] = (sg == 0 && i < kb && c < N) ? C(B[(r0 + i) + int64_t(c) * ldb]) : C(0);
+  for (int v = 0; v < NV; ++v) {
+    rv[v] = 16 * wave + Pr::row(lane, v);
+    cv[v] = Pr::col(lane, v);
+    in[v] = rv[v] < kb && cv[v] < N;
+    bv[v] = in[v] ? C(B[(r0 + rv[v]) + int64_t(cv[v]) * ldb]) : C(0);
+  }
+  // writes the lane's values into an x block in LDS (zero outside)
+  auto to_lds = [&](C *x, const C (&val)[NV]) {
+    if (!Pr::owns(lane)) return;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      if (NT == 1 || cv[v] < NT)
+        x[Pr::template slot<V>(rv[v]) * XN + cv[v]] = in[v] ? val[v] : C(0);
+  };
+
+  // entries of P this thread polls: entry idx of block j sits at
+  // P[c0 N + idx], row idx / N, right-hand side idx % N
+  constexpr int PER = (kNB * NT + TPB - 1) / TPB;
+  int prow[PER], pslot[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int idx = tid + q * TPB;
+    prow[q] = NT == 1 ? idx : idx / N;
+    pslot[q] = prow[q] < kNB
+                   ? Pr::template slot<V>(prow[q]) * XN + (NT == 1 ? 0 : idx - prow[q] * N)
+                   : 0;
   }
 
-  // The diagonal block of the refinement step is loaded here too where
-  // registers allow (one right-hand side; FP32 factors up to eight): after
-  // the last wait its memory latency would sit on the sweep's critical path.
-  constexpr bool PRE_T = REFINE && (NMAX == 1 || (sizeof(TF) == 4 && NMAX <= 8));
-  TF etp[PRE_T ? SEGW : 1];
-  if constexpr (PRE_T) load_tdiag(etp);
-
   // ---- accumulate op(A)[b, j] x_j over the blocks solved before b ----
-  C acc[NMAX];
+  C acc[NV];
 #pragma unroll
-  for (int c = 0; c < NMAX; ++c) acc[c] = C(0);
-  for (int64_t s = 0; s < t; ++s) {
+  for (int v = 0; v < NV; ++v) acc[v] = C(0);
+  auto block = [&](int64_t s, auto full) {
     const int64_t j = FWD ? s : nb - 1 - s;
     const int64_t c0 = j * kNB;
-    const int cb = int(n - c0 < kNB ? n - c0 : kNB);
-    TF e[SEGW];
+    const int cb = full.value ? kNB : int(n - c0);
+    C e[STEPS];
+    load_block<full.value, MODE, V, TF, C>(A, ld, ri, c0, cb, sl, e);
+    // x_j from P, each entry polled until published (bounded); a thread's
+    // entries are all loaded before any is waited on, so a published block
+    // costs one round trip. The two buffers of x alternate: a wavefront still
+    // reading the last block's is at most one barrier behind.
+    C *x = xs[s & 1];
+    const double *pj = pub + c0 * N + tid;
+    double xv[PER];
 #pragma unroll
-    for (int q = 0; q < SEGW; ++q) {
-      const int col = sg * SEGW + q;
-      e[q] = op_e<MODE>(A, ld, r0 + ir, c0 + (col < cb ? col : cb - 1));
-    }
-    // x_j from P, each entry polled until published (bounded). A thread's
-    // entries (two or four with 8 or 16 right-hand sides) are all loaded
-    // before any is waited on, so a published block costs one round trip.
+    for (int q = 0; q < PER; ++q) xv[q] = prow[q] < cb ? coherent_load(pj + q * TPB) : 0.0;
     bool expired = false;
-    constexpr int PER = (kNB * NMAX + TPB - 1) / TPB;
-    // entry (k, c) sits at P[(c0 + k) + c n]: consecutive lanes take
-    // consecutive k, so a wavefront's polls read contiguous memory
-    if constexpr (PER == 1) {
-      const int k = tid % kNB, c = tid / kNB;
-      if (tid < kNB * NMAX) {
-        C v = C(0);
-        if (k < cb && c < N) {
-          const double *p = pub + (c0 + k) + int64_t(c) * n;
-          double xv = coherent_load(p);
-          int64_t spins = 0;
-          while (unpublished(xv)) {
-            if (spins >= spin_limit) {  // expired: NaN for this entry, poison this block
-              expired = true;
-              xv = __builtin_nan("");
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            ++spins;
-            xv = coherent_load(p);
-          }
-          v = C(xv);
-        }
-        xs[k][c] = v;
-      }
-    } else {
-      double xv[PER];
 #pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int idx = tid + q * TPB;
-        const int k = idx % kNB, c = idx / kNB;
-        xv[q] = 0.0;
-        if (idx < kNB * NMAX && k < cb && c < N) xv[q] = coherent_load(pub + (c0 + k) + int64_t(c) * n);
-      }
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int idx = tid + q * TPB;
-        const int k = idx % kNB, c = idx / kNB;
-        if (idx >= kNB * NMAX) continue;
-        C v = C(0);
-        if (k < cb && c < N) {
-          const double *p = pub + (c0 + k) + int64_t(c) * n;
-          int64_t spins = 0;
-          while (unpublished(xv[q])) {
-            if (spins >= spin_limit) {  // expired: NaN for this entry, poison this block
-              expired = true;
-              xv[q] = __builtin_nan("");
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            ++spins;
-            xv[q] = coherent_load(p);
-          }
-          v = C(xv[q]);
+    for (int q = 0; q < PER; ++q) {
+      if (prow[q] >= kNB) continue;
+      int64_t spins = 0;
+      while (unpublished(xv[q])) {
+        if (spins >= spin_limit) {  // expired: NaN for this entry, poison this block
+          expired = true;
+          xv[q] = __builtin_nan("");
+          break;
         }
-        xs[k][c] = v;
+        __builtin_amdgcn_s_sleep(1);
+        ++spins;
+        xv[q] = coherent_load(pj + q * TPB);
       }
+      x[pslot[q]] = C(xv[q]);
     }
     if (expired) {
       __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       expired_sh = 1;
     }
     __syncthreads();
+    C o[NV];
+    Pr::template mul<V>(e, x, lane, o);
 #pragma unroll
-    for (int q = 0; q < SEGW; ++q) {
-      const int col = sg * SEGW + q;
-      const C a = col < cb ? C(e[q]) : C(0);
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) acc[c] += a * xs[col][c];
-    }
-    __syncthreads();
-  }
-
-  // loads of the diagonal work, issued before the reductions (the FP64
-  // diagonal block of the refinement step only while registers allow;
-  // with one right-hand side it was loaded before the waits)
-  constexpr bool EARLY_T = REFINE && NMAX <= 8;
-  TF et[REFINE ? SEGW : 1];
-  if constexpr (PRE_T) {
-#pragma unroll
-    for (int q = 0; q < SEGW; ++q) et[q] = etp[q];
-  } else if constexpr (EARLY_T) {
-    load_tdiag(et);
-  }
-  // 16 right-hand sides: FP32 factors take the inverse here; FP64 factors
-  // (more registers live) load it at each use
-  constexpr bool EARLY_D = !PRE && !REFINE;
-  C dlate[EARLY_D ? SEGW : 1];
-  if constexpr (EARLY_D) load_dinv(dlate);
-
-  // ---- r = b_b - acc ----
-  C r[NMAX];
-  reduce(acc, r);
-  if (sg == 0) {
-#pragma unroll
-    for (int c = 0; c < NMAX; ++c) {
-      // rows beyond kb summed clamped loads: zero them
-      C bv;
-      if constexpr (PRE)
-        bv = bpre[c];
-      else
-        bv = (i < kb && c < N) ? C(B[(r0 + i) + int64_t(c) * ldb]) : C(0);
-      r[c] = (i < kb && c < N) ? bv - r[c] : C(0);
-      xs[i][c] = r[c];
-    }
-  }
-  __syncthreads();
-
-  // product of the diagonal block's inverse with xs
-  auto prod_dinv = [&](C (&out)[NMAX]) {
-    C ev[SEGW];
-    if constexpr (PRE) {
-#pragma unroll
-      for (int q = 0; q < SEGW; ++q) ev[q] = dpre[q];
-    } else if constexpr (EARLY_D) {
-#pragma unroll
-      for (int q = 0; q < SEGW; ++q) ev[q] = dlate[q];
-    } else {
-      load_dinv(ev);
-    }
-    C a[NMAX];
-#pragma unroll
-    for (int c = 0; c < NMAX; ++c) a[c] = C(0);
-#pragma unroll
-    for (int q = 0; q < SEGW; ++q)
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) a[c] += ev[q] * xs[sg * SEGW + q][c];
-    reduce(a, out);
+    for (int v = 0; v < NV; ++v) acc[v] += o[v];
   };
+  // only the last block can be partial: the first one that a backward sweep
+  // solves (its own step, so that the loop carries no column masks)
+  int64_t s0 = 0;
+  if (!FWD && t > 0 && n % kNB != 0) {
+    block(0, std::false_type{});
+    s0 = 1;
+  }
+  for (int64_t s = s0; s < t; ++s) block(s, std::true_type{});
 
-  // ---- x = Di r ----
-  C x[NMAX];
-  prod_dinv(x);
+  // ---- r = b_b - acc, x = Di r (and x += Di (r - T x)) ----
+  C r[NV], x[NV];
+  C *xa = xs[t & 1], *xb = xs[(t & 1) ^ 1];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) r[v] = in[v] ? bv[v] - acc[v] : C(0);
+  to_lds(xa, r);
+  __syncthreads();
+  Pr::template mul<V>(di, xa, lane, x);
   if constexpr (REFINE) {
-    // res = r - T x ; x += Di res
-    if (sg == 0) {
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) xs[i][c] = x[c];
-    }
+    to_lds(xb, x);
     __syncthreads();
-    if constexpr (!EARLY_T) load_tdiag(et);
-    C a[NMAX];
+    C tx[NV], dx[NV];
+    Pr::template mul<V>(td, xb, lane, tx);
 #pragma unroll
-    for (int c = 0; c < NMAX; ++c) a[c] = C(0);
-#pragma unroll
-    for (int q = 0; q < SEGW; ++q) {
-      const int jj = sg * SEGW + q;
-      C v = C(et[q]);
-      if (jj >= kb || i >= kb) v = C(0);
-      else if (jj == i) v = UNIT ? C(1) : v;
-      else if (FWD ? (jj > i) : (jj < i)) v = C(0);
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) a[c] += v * xs[jj][c];
-    }
-    C tx[NMAX];
-    reduce(a, tx);
-    if (sg == 0) {
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) xs[i][c] = r[c] - tx[c];
-    }
+    for (int v = 0; v < NV; ++v) tx[v] = r[v] - tx[v];
+    to_lds(xa, tx);
     __syncthreads();
-    C dx[NMAX];
-    prod_dinv(dx);
-    if (sg == 0) {
+    Pr::template mul<V>(di, xa, lane, dx);
 #pragma unroll
-      for (int c = 0; c < NMAX; ++c) x[c] += dx[c];
-    }
+    for (int v = 0; v < NV; ++v) x[v] += dx[v];
   }
 
-  // ---- publish x_b (NaN if a wait of this block expired): the output B
-  // and the consumers' copy in P ----
+  // ---- publish x_b (NaN if a wait of this block expired): the consumers'
+  // copy in P and the output B ----
   const bool poisoned = expired_sh != 0;
-  if (sg == 0 && i < kb) {
+  if (Pr::owns(lane)) {
 #pragma unroll
-    for (int c = 0; c < NMAX; ++c)
-      if (c < N) {
-        const double v = poisoned ? __builtin_nan("") : double(x[c]);
-        B[(r0 + i) + int64_t(c) * ldb] = v;
-        coherent_store(&pub[(r0 + i) + int64_t(c) * n], unpublished(v) ? __builtin_nan("") : v);
+    for (int v = 0; v < NV; ++v)
+      if (in[v]) {
+        const double val = poisoned ? __builtin_nan("") : double(x[v]);
+        coherent_store(&pub[(r0 + rv[v]) * N + cv[v]], unpublished(val) ? __builtin_nan("") : val);
       }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      if (in[v])
+        B[(r0 + rv[v]) + int64_t(cv[v]) * ldb] = poisoned ? __builtin_nan("") : double(x[v]);
   }
 }
 
 // Before a sweep: ticket and legacy words cleared, P (count entries) set to
 // the unpublished pattern.
-__global__ void k_sweep_reset(int32_t *sync, int64_t count) {
+__global__ void k_sweep_reset(int32_t *sync, double *P, int64_t count) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g < 3) sync[g] = 0;
-  double *pub = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
   const double u = __builtin_bit_cast(double, kUnpublished);
-  for (int64_t k = g; k < count; k += int64_t(gridDim.x) * blockDim.x) pub[k] = u;
+  for (int64_t k = g; k < count; k += int64_t(gridDim.x) * blockDim.x) P[k] = u;
 }
 
-template <int NMAX, TriMode MODE, typename TF, typename C>
-hipError_t sweep_t(int64_t n, int N, const TF *LU, int64_t ld, const C *Winv, double *B,
-                   int64_t ldb, int32_t *sync, hipStream_t s) {
+template <int NT, TriMode MODE, typename TF, typename C>
+hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *Winv, double *B,
+                   int64_t ldb, int32_t *sync, double *P, hipStream_t s) {
   // one refinement step per diagonal block for FP64 factors and for FP32
   // arithmetic (a product with an explicit FP32 inverse alone is accurate to
   // kappa(block) u32 only); FP64 arithmetic on FP32 factors needs none
   constexpr bool REFINE = std::is_same<TF, double>::value || std::is_same<C, float>::value;
   const int64_t nb = (n + kNB - 1) / kNB;
-  if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  // ticket and legacy words, and P for the N columns; the sticky error word
-  // sync[3] is left alone
-  const int64_t count = n * int64_t(N);
+  const int64_t groups = (nrhs + kSkinnyMax - 1) / kSkinnyMax;
+  if (nb * groups > 0x7fffffff) return hipErrorInvalidValue;
+  // ticket and legacy words, and P; the sticky error word sync[3] is left alone
+  const int64_t count = n * nrhs;
   const int64_t blocks = (count + 255) / 256 < 1024 ? (count + 255) / 256 : 1024;
   hipLaunchKernelGGL(k_sweep_reset, dim3(unsigned(blocks < 1 ? 1 : blocks)), dim3(256), 0, s, sync,
-                     count);
-  hipLaunchKernelGGL((k_sweep<NMAX, MODE, TF, REFINE, C>), dim3(unsigned(nb)), dim3(TPB), 0, s, n,
-                     N, LU, ld, Winv, B, ldb, sync, nb, sweep_spin_limit(), refine_gate());
+                     P, count);
+  hipLaunchKernelGGL((k_sweep<NT, MODE, TF, REFINE, C>), dim3(unsigned(nb * groups)), dim3(TPB), 0,
+                     s, n, nrhs, LU, ld, Winv, B, ldb, sync, P, nb, int(groups),
+                     sweep_spin_limit(), refine_gate());
   return hipGetLastError();
 }
 
-template <int NMAX, typename TF, typename C>
-hipError_t sweep_n(TriMode mode, int64_t n, int N, const TF *LU, int64_t ld, const C *Winv,
-                   double *B, int64_t ldb, int32_t *sync, hipStream_t s) {
+template <int NT, typename TF, typename C>
+hipError_t sweep_n(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *Winv,
+                   double *B, int64_t ldb, int32_t *sync, double *P, hipStream_t s) {
   switch (mode) {
-    case TriMode::LN: return sweep_t<NMAX, TriMode::LN>(n, N, LU, ld, Winv, B, ldb, sync, s);
-    case TriMode::UN: return sweep_t<NMAX, TriMode::UN>(n, N, LU, ld, Winv, B, ldb, sync, s);
-    case TriMode::UT: return sweep_t<NMAX, TriMode::UT>(n, N, LU, ld, Winv, B, ldb, sync, s);
-    default: return sweep_t<NMAX, TriMode::LT>(n, N, LU, ld, Winv, B, ldb, sync, s);
+    case TriMode::LN: return sweep_t<NT, TriMode::LN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    case TriMode::UN: return sweep_t<NT, TriMode::UN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    case TriMode::UT: return sweep_t<NT, TriMode::UT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    default: return sweep_t<NT, TriMode::LT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
   }
 }
 
 template <typename TF, typename C>
 hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t ld,
-                     const C *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s) {
+                     const C *Winv, double *B, int64_t ldb, int32_t *sync, double *P,
+                     hipStream_t s) {
   if (n <= 0 || nrhs <= 0) return hipSuccess;
-  if (nrhs > kSkinnyMax || sync == nullptr) return hipErrorInvalidValue;
-  const int N = int(nrhs);
-  if (N <= 1) return sweep_n<1>(mode, n, N, LU, ld, Winv, B, ldb, sync, s);
-  if (N <= 4) return sweep_n<4>(mode, n, N, LU, ld, Winv, B, ldb, sync, s);
-  if (N <= 8) return sweep_n<8>(mode, n, N, LU, ld, Winv, B, ldb, sync, s);
-  return sweep_n<16>(mode, n, N, LU, ld, Winv, B, ldb, sync, s);
+  if (sync == nullptr) return hipErrorInvalidValue;
+  if (P == nullptr) {
+    if (nrhs > kSkinnyMax) return hipErrorInvalidValue;
+    P = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
+  }
+  if (nrhs == 1) return sweep_n<1>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+  if constexpr (std::is_same<C, double>::value) {
+    if (nrhs <= 4) return sweep_n<4>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    if (nrhs <= 8) return sweep_n<8>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+  }
+  return sweep_n<16>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
 }
 
 }  // namespace
 
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const double *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, s);
+                        hipStream_t s, double *pub) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
 }
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, s);
+                        hipStream_t s, double *pub) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
 }
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const float *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, s);
+                        hipStream_t s, double *pub) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
 }
 
 }  // namespace rbt
