@@ -99,6 +99,7 @@ __device__ __forceinline__ double rotation_coefficient(uint64_t seed, int64_t i,
 
 // First index of group g.
 __device__ __forceinline__ int64_t group_base(const Pass &ps, int64_t g) {
+  if (ps.lo == 1 && ps.hi == ps.d) return g;  // one pass over all layers: q groups
   const int64_t r = g % ps.q;
   const int64_t rest = g / ps.q;
   const int lowbits = ps.d - ps.hi;
@@ -136,16 +137,25 @@ __device__ __forceinline__ void transform2_block(PA __restrict__ A, int64_t lda,
     ci[p] = cb + p * ps.stride;
     cv[p] = ci[p] < ps.n;
   }
+  // Loads at clamped addresses inside the block's own rows and columns, masked
+  // afterwards: a load under a condition waits for the one before it, which
+  // cost the batched kernel, with few wavefronts to hide it, one memory
+  // latency per element.
   double x[G][G];
 #pragma unroll
   for (int c = 0; c < G; ++c)
 #pragma unroll
     for (int r = 0; r < G; ++r) {
+      const int64_t at = (rv[r] ? ri[r] : rb) + (cv[c] ? ci[c] : cb) * lda;
       if constexpr (STREAM)
-        x[r][c] = (rv[r] && cv[c]) ? __builtin_nontemporal_load(&A[ri[r] + ci[c] * lda]) : 0.0;
+        x[r][c] = __builtin_nontemporal_load(&A[at]);
       else
-        x[r][c] = (rv[r] && cv[c]) ? A[ri[r] + ci[c] * lda] : 0.0;
+        x[r][c] = A[at];
     }
+#pragma unroll
+  for (int c = 0; c < G; ++c)
+#pragma unroll
+    for (int r = 0; r < G; ++r) x[r][c] = (rv[r] && cv[c]) ? x[r][c] : 0.0;
   const bool two = ps.sides != 1;
 #pragma unroll
   for (int bit = 0; bit < P; ++bit) {
@@ -189,8 +199,9 @@ __device__ __forceinline__ void transform2_block(PA __restrict__ A, int64_t lda,
       const int p2 = p ^ (1 << bit);
       const double sr = (rv[p] && rv[p2]) ? kInvSqrt2 : 1.0;
       const double sc = (cv[p] && cv[p2]) ? kInvSqrt2 : 1.0;
-      fr[p] = rv[p] ? U[off + ri[p]] * sr : 0.0;
-      fc[p] = two ? (cv[p] ? V[off + ci[p]] * sc : 0.0) : 1.0;
+      const double u = U[off + (rv[p] ? ri[p] : rb)], v = V[off + (cv[p] ? ci[p] : cb)];
+      fr[p] = rv[p] ? u * sr : 0.0;
+      fc[p] = two ? (cv[p] ? v * sc : 0.0) : 1.0;
     }
 #pragma unroll
     for (int p = 0; p < G; ++p) {  // rows
@@ -249,7 +260,9 @@ __device__ __forceinline__ void transform_vec_block(PB __restrict__ B, int64_t l
   }
   double x[G];
 #pragma unroll
-  for (int p = 0; p < G; ++p) x[p] = rv[p] ? B[ri[p] + j * ldb] : 0.0;
+  for (int p = 0; p < G; ++p) x[p] = B[(rv[p] ? ri[p] : rb) + j * ldb];  // (as above)
+#pragma unroll
+  for (int p = 0; p < G; ++p) x[p] = rv[p] ? x[p] : 0.0;
 #pragma unroll
   for (int s = 0; s < P; ++s) {
     const int bit = (OP == RBT_OP_T) ? s : P - 1 - s;
@@ -272,7 +285,8 @@ __device__ __forceinline__ void transform_vec_block(PB __restrict__ B, int64_t l
 #pragma unroll
     for (int p = 0; p < G; ++p) {
       const int p2 = p ^ (1 << bit);
-      f[p] = rv[p] ? C[off + ri[p]] * ((rv[p2]) ? kInvSqrt2 : 1.0) : 0.0;
+      const double cf = C[off + (rv[p] ? ri[p] : rb)];
+      f[p] = rv[p] ? cf * ((rv[p2]) ? kInvSqrt2 : 1.0) : 0.0;
     }
     if (OP == RBT_OP_N) {
       // scale by the coefficient of the input index (R_l before O_l); the

@@ -532,7 +532,9 @@ __device__ __noinline__ void diag_block(const Sys &s, int64_t k, int kb, double 
   TF RBT_AS_GLOBAL *F = (TF RBT_AS_GLOBAL *)fmat<TF>(s);
   TF RBT_AS_GLOBAL *Invg = (TF RBT_AS_GLOBAL *)wave_uniform(Invb);
   const int64_t n = wave_uniform(s.n);
+  typedef Mma16<TF> M;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lk = lane >> 4;
   {
     const int r = tid & 63, cg = tid >> 6;
     const int rr = r < kb ? r : kb - 1;
@@ -589,74 +591,96 @@ __device__ __noinline__ void diag_block(const Sys &s, int64_t k, int kb, double 
       for (int i = 0; i < 16; ++i) S[col * LDS_ + c0 + i] = y[i];
     }
     __syncthreads();
-    const int w = BB - c1;
-    for (int e = tid; e < w * w; e += BT) {
-      const int i = c1 + e % w, j = c1 + e / w;
-      TF a = S[j * LDS_ + i];
+    // rank-16 update on 16 x 16 tiles, one wavefront each
+    const int nt = (BB - c1) / 16;
+    for (int t = wave; t < nt * nt; t += BT / 64) {
+      const int i0 = c1 + 16 * (t % nt), j0 = c1 + 16 * (t / nt);
+      typename M::v4 acc;
 #pragma unroll
-      for (int t = 0; t < 16; ++t) a -= S[(c0 + t) * LDS_ + i] * S[j * LDS_ + c0 + t];
-      S[j * LDS_ + i] = a;
+      for (int v = 0; v < 4; ++v) acc[v] = S[(j0 + l16) * LDS_ + i0 + M::row(lk, v)];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const int kx = c0 + 4 * kk + lk;
+        acc = M::mma(-S[kx * LDS_ + i0 + l16], S[(j0 + l16) * LDS_ + kx], acc);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S[(j0 + l16) * LDS_ + i0 + M::row(lk, v)] = acc[v];
     }
     __syncthreads();
   }
-  // inverses, lane c of a wavefront owning column c (its own column of T,
-  // so no barriers): wave 0 L^-1 (strictly lower part of T), wave 1 U^-1
-  // (upper part with the diagonal). Rows are taken in a uniform order (L:
-  // top-down, U: bottom-up), so the factor entry of a step is one broadcast
-  // LDS read and the sum over the solved rows has a uniform range (masked
-  // per lane), unrolled into independent partial sums.
-  if (wave == 0) {
-    const int c = lane;
-    for (int i = 1; i < BB; ++i) {  // X[i][c] = -(L[i][c] + sum_{c<t<i} L[i][t] X[t][c]), i > c
-      TF p0 = TF(0), p1 = TF(0), p2 = TF(0), p3 = TF(0);
-      int t = 0;
-      for (; t + 4 <= i; t += 4) {
-        const TF t0 = T[c * LDS_ + t + 0], t1 = T[c * LDS_ + t + 1];
-        const TF t2 = T[c * LDS_ + t + 2], t3 = T[c * LDS_ + t + 3];
-        const TF x0 = t + 0 > c ? t0 : (t + 0 == c ? TF(1) : TF(0));
-        const TF x1 = t + 1 > c ? t1 : (t + 1 == c ? TF(1) : TF(0));
-        const TF x2 = t + 2 > c ? t2 : (t + 2 == c ? TF(1) : TF(0));
-        const TF x3 = t + 3 > c ? t3 : (t + 3 == c ? TF(1) : TF(0));
-        p0 += S[(t + 0) * LDS_ + i] * x0;
-        p1 += S[(t + 1) * LDS_ + i] * x1;
-        p2 += S[(t + 2) * LDS_ + i] * x2;
-        p3 += S[(t + 3) * LDS_ + i] * x3;
+  // Inverses L^-1 (strictly lower part of T) and U^-1 (upper part with the
+  // diagonal) by 16 x 16 blocks: the diagonal blocks by substitution, a lane
+  // per column (wavefront 0 those of L, wavefront 1 those of U), then block
+  // diagonal d by block diagonal, X_ij = -X_ii sum_t D_it X_tj with two
+  // matrix-core products. (Column by column over the whole block, on one
+  // wavefront each, the inverses were most of this function: it took 95 us
+  // for a 64 x 64 block with two workgroups on the compute unit, 20 us now.)
+  if (wave < 2) {
+    const int o = 16 * lk, c = l16;
+    TF x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = i == c ? TF(1) : TF(0);
+    if (wave == 0) {
+#pragma unroll
+      for (int t = 0; t < 16; ++t)
+#pragma unroll
+        for (int i = t + 1; i < 16; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
+#pragma unroll
+      for (int i = 1; i < 16; ++i)
+        if (i > c) T[(o + c) * LDS_ + o + i] = x[i];
+    } else {
+#pragma unroll
+      for (int t = 15; t >= 0; --t) {
+        x[t] *= TF(1) / S[(o + t) * LDS_ + o + t];
+#pragma unroll
+        for (int i = 0; i < t; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
       }
-      for (; t < i; ++t) {
-        const TF tv = T[c * LDS_ + t];
-        const TF x = t > c ? tv : (t == c ? TF(1) : TF(0));
-        p0 += S[t * LDS_ + i] * x;
-      }
-      if (i > c) T[c * LDS_ + i] = -((p0 + p1) + (p2 + p3));
-    }
-  } else if (wave == 1) {
-    const int c = lane;
-    T[c * LDS_ + c] = TF(1) / S[c * LDS_ + c];
-    for (int i = BB - 2; i >= 0; --i) {  // X[i][c] = -(sum_{i<t<=c} U[i][t] X[t][c]) / U[i][i], i < c
-      const TF rd = TF(1) / S[i * LDS_ + i];
-      TF p0 = TF(0), p1 = TF(0), p2 = TF(0), p3 = TF(0);
-      int t = i + 1;
-      for (; t + 4 <= BB; t += 4) {
-        const TF t0 = T[c * LDS_ + t + 0], t1 = T[c * LDS_ + t + 1];
-        const TF t2 = T[c * LDS_ + t + 2], t3 = T[c * LDS_ + t + 3];
-        const TF x0 = t + 0 <= c ? t0 : TF(0);
-        const TF x1 = t + 1 <= c ? t1 : TF(0);
-        const TF x2 = t + 2 <= c ? t2 : TF(0);
-        const TF x3 = t + 3 <= c ? t3 : TF(0);
-        p0 += S[(t + 0) * LDS_ + i] * x0;
-        p1 += S[(t + 1) * LDS_ + i] * x1;
-        p2 += S[(t + 2) * LDS_ + i] * x2;
-        p3 += S[(t + 3) * LDS_ + i] * x3;
-      }
-      for (; t < BB; ++t) {
-        const TF tv = T[c * LDS_ + t];
-        const TF x = t <= c ? tv : TF(0);
-        p0 += S[t * LDS_ + i] * x;
-      }
-      if (i < c) T[c * LDS_ + i] = -((p0 + p1) + (p2 + p3)) * rd;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (i <= c) T[(o + c) * LDS_ + o + i] = x[i];
     }
   }
   __syncthreads();
+  for (int d = 1; d < BB / 16; ++d) {
+    const int nl = BB / 16 - d;  // blocks of each inverse on this diagonal
+    // 16 x 16 block (i, j) of L^-1 (low) or U^-1, entry (r, c)
+    auto inv_at = [&](bool low, int i, int j, int r, int c) {
+      const TF v = T[(16 * j + c) * LDS_ + 16 * i + r];
+      if (i != j) return v;
+      return low ? (r > c ? v : (r == c ? TF(1) : TF(0))) : (r <= c ? v : TF(0));
+    };
+    // (the products' first factors are summed into the target blocks, read
+    // back as the second factor)
+    for (int t = wave; t < 2 * nl; t += BT / 64) {
+      const bool low = t < nl;
+      const int i = low ? t + d : t - nl, j = low ? t : t - nl + d;
+      typename M::v4 acc = {TF(0), TF(0), TF(0), TF(0)};
+      for (int q = 0; q < d; ++q) {
+        const int m = low ? j + q : i + 1 + q;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const int kx = 4 * kk + lk;
+          acc = M::mma(S[(16 * m + kx) * LDS_ + 16 * i + l16], inv_at(low, m, j, kx, l16), acc);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) T[(16 * j + l16) * LDS_ + 16 * i + M::row(lk, v)] = acc[v];
+    }
+    __syncthreads();
+    for (int t = wave; t < 2 * nl; t += BT / 64) {
+      const bool low = t < nl;
+      const int i = low ? t + d : t - nl, j = low ? t : t - nl + d;
+      typename M::v4 acc = {TF(0), TF(0), TF(0), TF(0)};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const int kx = 4 * kk + lk;
+        acc = M::mma(-inv_at(low, i, i, l16, kx), T[(16 * j + l16) * LDS_ + 16 * i + kx], acc);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) T[(16 * j + l16) * LDS_ + 16 * i + M::row(lk, v)] = acc[v];
+    }
+    __syncthreads();
+  }
   // FP32: a copy of L\U (identity beyond kb) in the second half of region 1
   // for the refinement step of the panel products
   lds_t *Sc = T + BB * LDS_;
@@ -1263,39 +1287,66 @@ __device__ void refine_system(const Sys &s, int d, double tol, int max_iter, dou
   *be_out = be;
 }
 
+// One pass of the two-sided transform from A (FIRST) or the factor storage
+// itself into the factor storage: a wavefront takes a column group at a time,
+// its lanes the row groups. A function for each number of layers P, so that
+// each has the registers of its own block size (in one function the largest
+// one's spills and the conditional loads took 9.7 us for 256 blocks; now 4.2).
+template <int P, bool FIRST, typename TF>
+__device__ __noinline__ void transform_pass(const Sys &s, const dev::Pass &pass) {
+  const int64_t n = wave_uniform(s.n), lda = wave_uniform(s.lda);
+  const double RBT_AS_GLOBAL *Ag = (const double RBT_AS_GLOBAL *)wave_uniform(s.A);
+  const double RBT_AS_GLOBAL *Ug = (const double RBT_AS_GLOBAL *)wave_uniform(s.U);
+  const double RBT_AS_GLOBAL *Vg = (const double RBT_AS_GLOBAL *)wave_uniform(s.V);
+  TF RBT_AS_GLOBAL *Fg = (TF RBT_AS_GLOBAL *)fmat<TF>(s);
+  dev::Pass ps;
+  ps.n = n;
+  ps.q = wave_uniform(pass.q);
+  ps.stride = wave_uniform(pass.stride);
+  ps.ngroups = wave_uniform(pass.ngroups);
+  ps.d = __builtin_amdgcn_readfirstlane(pass.d);
+  ps.lo = __builtin_amdgcn_readfirstlane(pass.lo);
+  ps.hi = __builtin_amdgcn_readfirstlane(pass.hi);
+  ps.rot = __builtin_amdgcn_readfirstlane(pass.rot);
+  ps.sides = __builtin_amdgcn_readfirstlane(pass.sides);
+  const int ng = int(ps.ngroups);
+  for (int gc = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)); gc < ng; gc += BT / 64) {
+    const int64_t cb = dev::group_base(ps, gc);
+    if (cb >= n) continue;
+    for (int gr = threadIdx.x & 63; gr < ng; gr += 64) {
+      const int64_t rb = dev::group_base(ps, gr);
+      if (rb >= n) continue;
+      if constexpr (FIRST)
+        dev::transform2_block<P, TF>(Ag, lda, Fg, n, Ug, Vg, ps, rb, cb);
+      else
+        dev::transform2_block<P, TF>(Fg, n, Fg, n, Ug, Vg, ps, rb, cb);
+    }
+  }
+}
+
 // A~ = U^T A V into the factor storage of type TF (FP32 for the
 // low-precision pass, FP64 for the fallback), in passes of at most three
 // layers from layer d down: the first reads A, the later ones the factor
 // storage in place (each block of a pass belongs to one thread).
 template <typename TF>
-__device__ __noinline__ void transform_into(const Sys &s, int d) {
-  const double RBT_AS_GLOBAL *Ag = (const double RBT_AS_GLOBAL *)wave_uniform(s.A);
-  const double RBT_AS_GLOBAL *Ug = (const double RBT_AS_GLOBAL *)wave_uniform(s.U);
-  const double RBT_AS_GLOBAL *Vg = (const double RBT_AS_GLOBAL *)wave_uniform(s.V);
-  TF RBT_AS_GLOBAL *Fg = (TF RBT_AS_GLOBAL *)fmat<TF>(s);
-  const int64_t n = wave_uniform(s.n), lda = wave_uniform(s.lda), q = wave_uniform(s.q);
+__device__ void transform_into(const Sys &s, int d) {
   for (int hi = d, first = 1; first || hi >= 1; first = 0) {
     const int lo = d == 0 ? 1 : (hi - 2 > 1 ? hi - 2 : 1);
     const dev::Pass ps =
-        d > 0 ? dev::make_pass(n, q, d, lo, hi, s.rot, s.sides) : dev::identity_pass(n);
+        d > 0 ? dev::make_pass(s.n, s.q, d, lo, hi, s.rot, s.sides) : dev::identity_pass(s.n);
     const int P = d > 0 ? hi - lo + 1 : 0;
-    for (int64_t e = threadIdx.x; e < ps.ngroups * ps.ngroups; e += BT) {
-      const int64_t gr = e % ps.ngroups, gc = e / ps.ngroups;
-      const int64_t rb = dev::group_base(ps, gr), cb = dev::group_base(ps, gc);
-      if (rb >= n || cb >= n) continue;
-      if (first) {
-        switch (P) {
-          case 0: dev::transform2_block<0, TF>(Ag, lda, Fg, n, Ug, Vg, ps, rb, cb); break;
-          case 1: dev::transform2_block<1, TF>(Ag, lda, Fg, n, Ug, Vg, ps, rb, cb); break;
-          case 2: dev::transform2_block<2, TF>(Ag, lda, Fg, n, Ug, Vg, ps, rb, cb); break;
-          default: dev::transform2_block<3, TF>(Ag, lda, Fg, n, Ug, Vg, ps, rb, cb); break;
-        }
-      } else {
-        switch (P) {
-          case 1: dev::transform2_block<1, TF>(Fg, n, Fg, n, Ug, Vg, ps, rb, cb); break;
-          case 2: dev::transform2_block<2, TF>(Fg, n, Fg, n, Ug, Vg, ps, rb, cb); break;
-          default: dev::transform2_block<3, TF>(Fg, n, Fg, n, Ug, Vg, ps, rb, cb); break;
-        }
+    if (first) {
+      switch (P) {
+        case 0: transform_pass<0, true, TF>(s, ps); break;
+        case 1: transform_pass<1, true, TF>(s, ps); break;
+        case 2: transform_pass<2, true, TF>(s, ps); break;
+        default: transform_pass<3, true, TF>(s, ps); break;
+      }
+    } else {
+      switch (P) {
+        case 1: transform_pass<1, false, TF>(s, ps); break;
+        case 2: transform_pass<2, false, TF>(s, ps); break;
+        default: transform_pass<3, false, TF>(s, ps); break;
       }
     }
     __syncthreads();
