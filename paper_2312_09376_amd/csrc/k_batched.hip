@@ -81,7 +81,7 @@ __device__ __forceinline__ void st4(gfloat *p, f4u v) {
 // a step); the sweeps use both regions.
 constexpr int kR0Doubles = BB * LDS_;       // 4160 doubles
 constexpr int kR1Doubles = BB * LDS_;
-static_assert(7 * BB * NR <= kR0Doubles + kR1Doubles, "sweep buffers exceed LDS");  // part, xs, ys, x0s
+static_assert(3 * BB * (NR + 1) <= kR0Doubles, "sweep buffers exceed region 0");
 static_assert(256 * NR + BT / 64 <= kR0Doubles, "residual buffers exceed region 0");
 
 struct Args {
@@ -948,145 +948,125 @@ __device__ __noinline__ void transform_vec_sys(const Sys &s, int d, double *Y, i
 // arithmetic type TF (FP32 for the low-precision pass: a value of Y is
 // rounded to FP32 when the sweep first reads it and every update is an FP32
 // operation; FP64 for the fallback), right-looking: for each diagonal block
-// b in sweep order, x_b = Dinv_b y_b (threads: 64 rows x 4 segments of 16,
-// reduced in LDS), then every row still to be solved takes
+// b in sweep order, x_b = Dinv_b y_b, then every row still to be solved takes
 // y_m -= F[m, block b] x_b as a matrix-core product of 16-row tiles of the
 // factor (16 loads per lane, issued one tile ahead) with x_b (16 values per
 // lane, held in registers for the step). Operand and output layout: mma16.h.
-// NRT: right-hand sides of the inverse product (>= N).
-template <bool LOWER, int NRT, typename TF>
+// The products with the diagonal block are matrix-core products too, 16 whole
+// rows per wavefront, their operands loaded during the step before: one
+// barrier each (FMA loops over 16-column segments, summed through LDS, made a
+// block's solve 10 us of dependent LDS reads and barriers).
+template <bool LOWER, typename TF>
 __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, double *L0) {
   typedef Mma16<TF> M;
   typedef typename Lds<TF>::T lds_t;
+  constexpr int XN = NR + 1;  // LDS row of an x block
   const TF RBT_AS_GLOBAL *F = (const TF RBT_AS_GLOBAL *)fmat<TF>(s);
   const TF RBT_AS_GLOBAL *Inv = (const TF RBT_AS_GLOBAL *)wave_uniform(s.Inv);
   double RBT_AS_GLOBAL *Y = (double RBT_AS_GLOBAL *)wave_uniform(Y_in);
   const int64_t ldy = wave_uniform(ldy_in);
   const int64_t n = wave_uniform(s.n);
   const int N = int(wave_uniform(s.nrhs));
-  const int tid = threadIdx.x, i = tid & 63, sg = tid >> 6;
+  const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lk = lane >> 4;
-  lds_t *Ll = (lds_t *)L0;
-  TF RBT_AS_LDS(*part)[BB][NRT] = reinterpret_cast<TF RBT_AS_LDS(*)[BB][NRT]>(Ll);  // [4][64][NRT]
-  TF RBT_AS_LDS(*xs)[NR] = reinterpret_cast<TF RBT_AS_LDS(*)[NR]>(Ll + 4 * BB * NRT);  // [64][16]
-  // FP32 refinement step: y_b and the first x_b
-  TF RBT_AS_LDS(*ys)[NR] = reinterpret_cast<TF RBT_AS_LDS(*)[NR]>(Ll + 4 * BB * NRT + BB * NR);
-  TF RBT_AS_LDS(*x0s)[NR] = reinterpret_cast<TF RBT_AS_LDS(*)[NR]>(Ll + 4 * BB * NRT + 2 * BB * NR);
+  lds_t *x0s = (lds_t *)L0, *x1s = x0s + BB * XN, *xs = x1s + BB * XN;  // [64][XN] each
   const int64_t nblk = (n + BB - 1) / BB;
+  const int i = 16 * wave + l16;  // the lane's row of the diagonal block as an operand
+  // the lane's entries of block b's inverse and (FP32) of the block itself,
+  // masked to their triangles: row i, columns 4 kk + lk
+  constexpr bool REFINE = sizeof(TF) == 4;
+  auto load_diag = [&](int64_t b, TF (&dv)[16], TF (&tv)[REFINE ? 16 : 1]) {
+    const int64_t r0 = b * BB;
+    const int kb = int(n - r0 < BB ? n - r0 : BB);
+    const TF RBT_AS_GLOBAL *Db = Inv + b * BB * BB;
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) dv[kk] = Db[i + (4 * kk + lk) * BB];
+    if constexpr (REFINE) {
+      const int ic = i < kb ? i : kb - 1;
+#pragma unroll
+      for (int kk = 0; kk < 16; ++kk) {
+        const int kx = 4 * kk + lk;
+        tv[kk] = F[(r0 + ic) + (r0 + (kx < kb ? kx : kb - 1)) * n];
+      }
+#pragma unroll
+      for (int kk = 0; kk < 16; ++kk) {
+        const int kx = 4 * kk + lk;
+        const bool in = i < kb && kx < kb;
+        tv[kk] = LOWER ? (i == kx ? TF(1) : (in && kx < i ? tv[kk] : TF(0)))
+                       : (in && kx >= i ? tv[kk] : (i == kx ? TF(1) : TF(0)));
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      const int kx = 4 * kk + lk;
+      dv[kk] = LOWER ? (i > kx ? dv[kk] : (i == kx ? TF(1) : TF(0))) : (i <= kx ? dv[kk] : TF(0));
+    }
+  };
+  // 16 rows of a product with the x block at xp
+  auto product = [&](const TF (&e)[16], const lds_t *xp, TF (&out)[4]) {
+    typename M::v4 a0 = {TF(0), TF(0), TF(0), TF(0)}, a1 = a0;
+#pragma unroll
+    for (int kk = 0; kk < 16; kk += 2) {
+      a0 = M::mma(e[kk], xp[(4 * kk + lk) * XN + l16], a0);
+      a1 = M::mma(e[kk + 1], xp[(4 * (kk + 1) + lk) * XN + l16], a1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[v] = a0[v] + a1[v];
+  };
+  // the lane's results are rows 16 wave + M::row(lk, v), right-hand side l16
+  auto to_lds = [&](lds_t *xp, const TF (&val)[4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xp[(16 * wave + M::row(lk, v)) * XN + l16] = val[v];
+  };
+  TF dv[16], dn[16], tv[REFINE ? 16 : 1], tn[REFINE ? 16 : 1];
+  load_diag(LOWER ? 0 : nblk - 1, dv, tv);
   for (int64_t t = 0; t < nblk; ++t) {
     const int64_t b = LOWER ? t : nblk - 1 - t;
     const int64_t r0 = b * BB;
     const int kb = int(n - r0 < BB ? n - r0 : BB);
-    // y_b -> LDS
-    if (sg == 0) {
+    TF y[4], x[4];
+    bool in[4];
 #pragma unroll
-      for (int c = 0; c < NR; ++c) {
-        const TF y = (i < kb && c < N) ? TF(Y[(r0 + i) + int64_t(c) * ldy]) : TF(0);
-        xs[i][c] = y;
-        if constexpr (sizeof(TF) == 4) ys[i][c] = y;
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int row = 16 * wave + M::row(lk, v);
+      in[v] = row < kb && l16 < N;
+      y[v] = in[v] ? TF(Y[(r0 + row) + int64_t(l16) * ldy]) : TF(0);
     }
+    to_lds(x0s, y);
     __syncthreads();
-    // x_b = Dinv y_b: part[sg][i][:] = sum over this segment's 16 columns of
-    // Dinv(i, kx) xs[kx][:], then the four segments are added
-    const TF RBT_AS_GLOBAL *Db = Inv + b * BB * BB;
-    // (entries read from the inverse where they are used: an array of them
-    // held through the loops below would be indexed dynamically)
-    auto dinv = [&](int q) {
-      const int kx = sg * 16 + q;
-      const TF d = Db[i + kx * BB];
-      return LOWER ? (i > kx ? d : (i == kx ? TF(1) : TF(0))) : (i <= kx ? d : TF(0));
-    };
-    auto part_sum = [&](int c) {
-      return (part[0][i][c] + part[1][i][c]) + (part[2][i][c] + part[3][i][c]);
-    };
-    {
-      TF acc[NRT];
-#pragma unroll
-      for (int c = 0; c < NRT; ++c) acc[c] = TF(0);
-#pragma unroll 2
-      for (int q = 0; q < 16; ++q) {
-        const TF v = dinv(q);
-#pragma unroll
-        for (int c = 0; c < NRT; ++c) acc[c] += v * xs[sg * 16 + q][c];
-      }
-#pragma unroll
-      for (int c = 0; c < NRT; ++c) part[sg][i][c] = acc[c];
-    }
-    __syncthreads();
-    if (sg == 0) {
-#pragma unroll
-      for (int c = 0; c < NR; ++c) {
-        TF x = TF(0);
-        if (c < NRT && i < kb && c < N) x = part_sum(c < NRT ? c : 0);
-        xs[i][c] = x;
-        if constexpr (sizeof(TF) == 4)
-          x0s[i][c] = x;
-        else if (i < kb && c < N)
-          Y[(r0 + i) + int64_t(c) * ldy] = double(x);
-      }
-    }
-    __syncthreads();
-    if constexpr (sizeof(TF) == 4) {
+    product(dv, x0s, x);
+    if constexpr (REFINE) {
       // FP32: one refinement step against the diagonal block itself, so the
       // block solve is not limited to kappa(block) u32 (the product with an
       // explicit inverse alone is): r = y_b - D x_b, x_b += Dinv r
-      {
-        const int ic = i < kb ? i : kb - 1;
-        TF acc[NRT];
+      TF r[4], dx[4];
 #pragma unroll
-        for (int c = 0; c < NRT; ++c) acc[c] = TF(0);
-#pragma unroll 2
-        for (int q = 0; q < 16; ++q) {
-          const int kx = sg * 16 + q;
-          const TF f = F[(r0 + ic) + (r0 + (kx < kb ? kx : kb - 1)) * n];
-          const bool in = i < kb && kx < kb;
-          const TF v = LOWER ? (i == kx ? TF(1) : (in && kx < i ? f : TF(0)))
-                             : (in && kx >= i ? f : (i == kx ? TF(1) : TF(0)));
-#pragma unroll
-          for (int c = 0; c < NRT; ++c) acc[c] += v * xs[kx][c];
-        }
-#pragma unroll
-        for (int c = 0; c < NRT; ++c) part[sg][i][c] = acc[c];
-      }
+      for (int v = 0; v < 4; ++v) x[v] = in[v] ? x[v] : TF(0);
+      to_lds(x1s, x);
       __syncthreads();
-      if (sg == 0) {
+      product(tv, x1s, r);
 #pragma unroll
-        for (int c = 0; c < NR; ++c)
-          xs[i][c] = (c < NRT && i < kb && c < N) ? ys[i][c] - part_sum(c < NRT ? c : 0) : TF(0);
-      }
+      for (int v = 0; v < 4; ++v) r[v] = in[v] ? y[v] - r[v] : TF(0);
+      to_lds(x0s, r);
       __syncthreads();
-      {
-        TF acc[NRT];
+      product(dv, x0s, dx);
 #pragma unroll
-        for (int c = 0; c < NRT; ++c) acc[c] = TF(0);
-#pragma unroll 2
-        for (int q = 0; q < 16; ++q) {
-          const TF v = dinv(q);
-#pragma unroll
-          for (int c = 0; c < NRT; ++c) acc[c] += v * xs[sg * 16 + q][c];
-        }
-#pragma unroll
-        for (int c = 0; c < NRT; ++c) part[sg][i][c] = acc[c];
-      }
-      __syncthreads();
-      if (sg == 0) {
-#pragma unroll
-        for (int c = 0; c < NR; ++c) {
-          TF x = x0s[i][c];
-          if (c < NRT && i < kb && c < N) x += part_sum(c < NRT ? c : 0);
-          xs[i][c] = x;
-          if (i < kb && c < N) Y[(r0 + i) + int64_t(c) * ldy] = double(x);
-        }
-      }
-      __syncthreads();
+      for (int v = 0; v < 4; ++v) x[v] += dx[v];
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      x[v] = in[v] ? x[v] : TF(0);
+      if (in[v]) Y[(r0 + 16 * wave + M::row(lk, v)) + int64_t(l16) * ldy] = double(x[v]);
+    }
+    to_lds(xs, x);
+    __syncthreads();
+    if (t + 1 < nblk) load_diag(LOWER ? b + 1 : b - 1, dn, tn);  // in flight during the update
     // rows still to be solved: after the block (L) or before it (U)
     const int64_t lo = LOWER ? r0 + kb : 0, hi = LOWER ? n : r0;
     if (hi > lo) {
       TF xb[16];
 #pragma unroll
-      for (int kk = 0; kk < 16; ++kk) xb[kk] = xs[lk + 4 * kk][l16];
+      for (int kk = 0; kk < 16; ++kk) xb[kk] = xs[(lk + 4 * kk) * XN + l16];
       const int64_t ntile = (hi - lo + 15) / 16;
       auto load_tile = [&](int64_t tt, TF (&av)[16]) {
         const int64_t m = lo + 16 * tt + l16;
@@ -1140,6 +1120,11 @@ __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, d
         for (int v = 0; v < 4; ++v) yv[v] = yn[v];
       }
     }
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      dv[kk] = dn[kk];
+      if constexpr (REFINE) tv[kk] = tn[kk];
+    }
     __syncthreads();
   }
 }
@@ -1163,11 +1148,19 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
   const double RBT_AS_GLOBAL *Bg = (const double RBT_AS_GLOBAL *)wave_uniform(s.Bm);
   double RBT_AS_GLOBAL *Rg = (double RBT_AS_GLOBAL *)wave_uniform(s.R);
   double amax = 0.0;
+  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lk = lane >> 4;
   for (int64_t m0 = 0; m0 < n; m0 += BT) {
     const int64_t m = m0 + tid;
-    double acc[NRT];
+    double acc[NRT < NR ? NRT : 1];
+    typename Mma16<double>::v4 acc4[4];  // NR: row tiles 16 q of the wavefront's 64 rows
+    double asum4[4];
 #pragma unroll
-    for (int c = 0; c < NRT; ++c) acc[c] = 0.0;
+    for (int c = 0; c < (NRT < NR ? NRT : 1); ++c) acc[c] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc4[q] = typename Mma16<double>::v4{0.0, 0.0, 0.0, 0.0};
+      asum4[q] = 0.0;
+    }
     double asum = 0.0;
     for (int64_t k0 = 0; k0 < n; k0 += KC) {
       const int kc = int(n - k0 < KC ? n - k0 : KC);
@@ -1177,7 +1170,33 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
         xs[kx][c] = (kx < kc && c < N) ? Xg[(k0 + kx) + int64_t(c) * ldx] : 0.0;
       }
       __syncthreads();
-      if (m < n) {
+      if constexpr (NRT == NR) {
+        // matrix cores: 64 rows per wavefront, 16 columns of A per batch of
+        // loads (the FMA loop below reads X from LDS for every product: 16
+        // values per column of A)
+        for (int kx = 0; kx < kc; kx += 16) {
+          double av[4][4];
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int64_t row = m0 + 64 * wave + 16 * q + l16;
+              const int k = kx + 4 * kk + lk;
+              av[kk][q] = Ag[(row < n ? row : n - 1) + (k0 + (k < kc ? k : kc - 1)) * lda];
+            }
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            const int k = kx + 4 * kk + lk;
+            const double xv = xs[k < KC ? k : KC - 1][l16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const double a = k < kc ? av[kk][q] : 0.0;
+              if (with_anorm) asum4[q] += fabs(a);
+              acc4[q] = Mma16<double>::mma(a, xv, acc4[q]);
+            }
+          }
+        }
+      } else if (m < n) {
         const double RBT_AS_GLOBAL *Ap = Ag + m + k0 * lda;
         // batches of 32 loads in flight (kc is a multiple of 32 except at the
         // end): all issued before the first product uses one
@@ -1205,7 +1224,24 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
         }
       }
     }
-    if (m < n) {
+    if constexpr (NRT == NR) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t r0 = m0 + 64 * wave + 16 * q;
+        if (with_anorm) {  // the four column groups of a row
+          double v = asum4[q];
+          v += __shfl_xor(v, 16);
+          v += __shfl_xor(v, 32);
+          if (r0 + l16 < n) amax = nanmax(amax, v);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t row = r0 + Mma16<double>::row(lk, v);
+          if (row < n && l16 < N)
+            Rg[row + int64_t(l16) * n] = Bg[row + int64_t(l16) * ldb] - acc4[q][v];
+        }
+      }
+    } else if (m < n) {
       amax = nanmax(amax, asum);
 #pragma unroll
       for (int c = 0; c < NRT; ++c)
@@ -1218,23 +1254,28 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
     if (tid == 0) *anorm = an;
     __syncthreads();
   }
+  // column maxima: a wavefront takes every fourth right-hand side, so only the
+  // error is reduced over the workgroup
   const double an = *anorm;
   double be = 0.0;
-  for (int c = 0; c < N; ++c) {
+  for (int c = wave; c < N; c += BT / 64) {
     double rm = 0.0, xm = 0.0, bm = 0.0;
-    for (int64_t m = tid; m < n; m += BT) {
+    for (int64_t m = lane; m < n; m += 64) {
       rm = nanmax(rm, fabs(Rg[m + int64_t(c) * n]));
       xm = nanmax(xm, fabs(Xg[m + int64_t(c) * ldx]));
       bm = nanmax(bm, fabs(Bg[m + int64_t(c) * ldb]));
     }
-    const double r = wg_nanmax(rm, red);
-    const double x = wg_nanmax(xm, red);
-    const double b = wg_nanmax(bm, red);
-    const double den = an * x + b;
-    const double e = den > 0.0 ? r / den : (r > 0.0 ? INFINITY : (r != r ? r : 0.0));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      rm = nanmax(rm, __shfl_xor(rm, o));
+      xm = nanmax(xm, __shfl_xor(xm, o));
+      bm = nanmax(bm, __shfl_xor(bm, o));
+    }
+    const double den = an * xm + bm;
+    const double e = den > 0.0 ? rm / den : (rm > 0.0 ? INFINITY : (rm != rm ? rm : 0.0));
     be = nanmax(be, e);
   }
-  return be;
+  return wg_nanmax(be, red);
 }
 
 // X = V (LU)^-1 U^T B with the factors of storage type TF, then classical
@@ -1256,8 +1297,8 @@ __device__ void refine_system(const Sys &s, int d, double tol, int max_iter, dou
     Xg[(e % n) + (e / n) * s.ldx] = Bg[(e % n) + (e / n) * s.ldb];
   __syncthreads();
   transform_vec_sys<RBT_OP_T>(s, d, s.Xm, s.ldx, s.U);
-  sweep<true, NRT, TF>(s, s.Xm, s.ldx, L0);
-  sweep<false, NRT, TF>(s, s.Xm, s.ldx, L0);
+  sweep<true, TF>(s, s.Xm, s.ldx, L0);
+  sweep<false, TF>(s, s.Xm, s.ldx, L0);
   if (s.sides != 1) transform_vec_sys<RBT_OP_N>(s, d, s.Xm, s.ldx, s.V);  // x = V x~
   int it = 0, stalled = 0;
   double be = 0.0, best = INFINITY;
@@ -1275,8 +1316,8 @@ __device__ void refine_system(const Sys &s, int d, double tol, int max_iter, dou
     if (be < best) best = be;
     if (stalled >= 2 || be != be) break;
     transform_vec_sys<RBT_OP_T>(s, d, s.R, n, s.U);
-    sweep<true, NRT, TF>(s, s.R, n, L0);
-    sweep<false, NRT, TF>(s, s.R, n, L0);
+    sweep<true, TF>(s, s.R, n, L0);
+    sweep<false, TF>(s, s.R, n, L0);
     if (s.sides != 1) transform_vec_sys<RBT_OP_N>(s, d, s.R, n, s.V);
     for (int64_t e = threadIdx.x; e < n * s.nrhs; e += BT)
       Xg[(e % n) + (e / n) * s.ldx] += Rg[e];
