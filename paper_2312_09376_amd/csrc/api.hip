@@ -1652,7 +1652,9 @@ extern "C" int rbt_solve_batched(int64_t batch, const double *const *A, const in
   if (work == nullptr) return -17;
   if (work_bytes < kBatchTableOffset + size_t(batch) * sizeof(BatchDesc)) return RBT_ERR_WORKSPACE;
   const int64_t cap = options().batch_wgs_per_cu * int64_t(device_cus());
-  const int grid = int(batch < cap ? batch : cap);
+  // (every system may be a team's; workgroups without a ticket end at once)
+  const int64_t most = batch * kBatchTeamMax;
+  const int grid = int(most < cap ? most : cap);
   RBT_HIP_CHECK(launch_batched(batch, work, work_bytes, A, lda, B, ldb, X, ldx, depth, seed, prec,
                                tol, max_iter, iters_dev, berr_dev, info_dev, path_dev, grid,
                                options().batch_ct2_min_n, S(stream)));

@@ -70,6 +70,28 @@ std::vector<char> batch_plan_image(int64_t batch, int depth, int prec, const Bat
   h.d_off_bytes = int64_t(z.d_off);
   h.total_bytes = int64_t(z.total);
   h.f64_off_bytes = int64_t(z.f64_off);
+  // Teams: a system whose own time on one workgroup is more than its fair
+  // share of the batch's (the sum over the 512 workgroups a GPU holds) would be
+  // what the batch waits for, so it takes the workgroups that bring it to
+  // about that share. Time goes with n^3 / 3 + 200 n^2 (measured at n = 300 and
+  // 1499: the n^2 part is the transform, the sweeps and the residuals).
+  auto cost = [](double n) { return n * n * (n / 3.0 + 200.0); };
+  double share = 0.0;
+  for (const BatchDesc &D : desc)
+    if (D.nrhs > 0) share += cost(double(D.n)) / 512.0;
+  auto members = [&](const BatchDesc &D) {
+    if (D.nrhs <= 0 || D.n < kBatchTeamMinN) return 1;
+    const double want = cost(double(D.n)) / share;
+    int t = 1;
+    while (t < kBatchTeamMax && double(t) < want && D.n >= 2 * 64 * (2 * t)) t *= 2;
+    return t;
+  };
+  for (const BatchDesc &D : desc) {  // (sorted: members never grow along the table)
+    const int t = members(D);
+    h.teams8 += t == 8;
+    h.teams4 += t == 4;
+    h.teams2 += t == 2;
+  }
   std::memcpy(image.data(), &h, sizeof(h));
   if (!desc.empty())
     std::memcpy(image.data() + kBatchTableOffset, desc.data(), desc.size() * sizeof(BatchDesc));

@@ -273,7 +273,14 @@ struct BatchHeader {
   int32_t depth, prec;
   int64_t f_off_bytes, d_off_bytes, total_bytes;  // FP32 area, FP64 area, workspace used
   int64_t f64_off_bytes;  // FP64 factor area of the fallback (0: none)
+  // systems at the head of the table that a team of 8, of 4 and of 2
+  // workgroups solves (the rest: one workgroup each)
+  int32_t teams8, teams4, teams2, pad1;
 };
+__host__ __device__ inline bool batched_teams_ok(const BatchHeader &h) {
+  return h.teams8 >= 0 && h.teams4 >= 0 && h.teams2 >= 0 &&
+         int64_t(h.teams8) + h.teams4 + h.teams2 <= h.batch;
+}
 struct BatchDesc {
   int64_t sys;      // index into the caller's arrays
   int64_t n, nrhs;
@@ -314,9 +321,22 @@ hipError_t launch_batched(int64_t batch, void *work, size_t work_bytes, const do
                           int prec, double tol, int max_iter, int32_t *iters, double *berr,
                           int32_t *info, int32_t *path, int grid, int64_t ct2_min_n,
                           hipStream_t s);
-// FP64 doubles of one batched system's area (U, V, inverse blocks of 64, residual)
-inline int64_t batched_sys_doubles(int64_t n, int64_t nrhs, int d) {
-  return 2 * n * d + ((n + 63) / 64) * 64 * 64 + n * nrhs;
+// Teams of workgroups on one large system: members at most, and the smallest
+// order (a member then has at least two 64-row strips of its own).
+constexpr int kBatchTeamMax = 8;
+constexpr int64_t kBatchTeamMinN = 512;
+// Words of a team's area, in doubles: barrier count, expired wait, zero pivot
+// and sweep block count (32 bits each), then
+// kBatchTeamMax partial maxima of the residual (||A||_inf and three per
+// right-hand side).
+constexpr int64_t kBatchTeamHead = 8;
+__host__ __device__ inline int64_t batched_team_doubles(int64_t n, int64_t nrhs) {
+  return n >= kBatchTeamMinN ? kBatchTeamHead + kBatchTeamMax * (1 + 3 * nrhs) : 0;
+}
+// FP64 doubles of one batched system's area (U, V, inverse blocks of 64,
+// residual, team area)
+__host__ __device__ inline int64_t batched_sys_doubles(int64_t n, int64_t nrhs, int d) {
+  return 2 * n * d + ((n + 63) / 64) * 64 * 64 + n * nrhs + batched_team_doubles(n, nrhs);
 }
 
 // k_gepp.hip : elimination with partial pivoting (the robust re-solve of the

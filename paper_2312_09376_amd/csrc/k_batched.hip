@@ -26,6 +26,20 @@
 // Solves: block sweeps over the factors with the inverses of the diagonal
 // blocks (FP32: plus one refinement step per block).
 //
+// Large systems of a batch that would otherwise wait for them are solved by
+// teams of 2, 4 or 8 workgroups (the plan decides how many systems; consecutive
+// tickets are the members). A member owns every T-th 64-row strip of the
+// factor and of Y: it updates its strips' tiles, solves its strips' blocks and
+// forms its part of the panels, the transform and the residual; between
+// phases the members meet at a barrier in the system's workspace area. Every
+// element sees the same operations as with one workgroup. (One system of order
+// 1500: 20.7 -> 3.7 ms; 64 of them: 23.3 -> 7.7; 512 of 37 to 1500, where the
+// largest otherwise end last: 26.9 -> 20.9.)
+// Progress: a member waits for members of the same team only. Tickets are
+// taken in order, so at most one team is incomplete at any time, and every
+// workgroup outside it works on a complete team or on its own, finishes and
+// takes the next ticket.
+//
 // The host plan (rbt_batched_plan) writes the header and the descriptor
 // table; the kernel checks the header against its arguments and does
 // nothing for a plan that does not match.
@@ -508,7 +522,103 @@ struct Sys {
   int64_t ldb;
   double *Xm;
   int64_t ldx;
+  int team, rank;    // workgroups on this system, and which of them this one is
+  double *tw;        // team area (team > 1)
+  uint32_t *met;     // LDS: arrivals at this team's barriers so far, and blocks
+                     // published by its sweeps so far
 };
+// A system of one workgroup and one of a team: the functions below are built
+// for each, since the member arithmetic and the waits, where there is one
+// member, cost a batch of small systems 5 % (1024 of 37 to 300: 1.19 against
+// 1.13 ms).
+struct SoloSys : Sys {
+  __device__ __forceinline__ static constexpr int members() { return 1; }
+  __device__ __forceinline__ static constexpr int member() { return 0; }
+};
+struct TeamSys : Sys {
+  __device__ __forceinline__ int members() const { return int(wave_uniform(team)); }
+  __device__ __forceinline__ int member() const { return int(wave_uniform(rank)); }
+};
+
+// Barrier of the workgroups on a system; memory written before it by any of
+// them is visible after it to all. One thread arrives with a release and
+// looks on with an acquire for the whole workgroup (the workgroup's barriers
+// before and after order the others' accesses with it). The release writes
+// back and the acquire invalidates the XCD's cache for everyone on it, so there
+// is one of each per workgroup and none while looking: an acquire at every
+// look, by every wavefront, took a 512-system batch from 27 to 52 ms. The wait
+// is bounded: a barrier that expires marks the system, which then reports NaN
+// (see solve_system).
+constexpr int64_t kTeamSpins = int64_t(1) << 24;
+__device__ __forceinline__ uint32_t *team_word(const Sys &s, int i) {
+  return reinterpret_cast<uint32_t *>(s.tw) + i;
+}
+__device__ __forceinline__ void team_sync(const SoloSys &) { __syncthreads(); }
+__device__ __noinline__ void team_sync(const TeamSys &s) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t *count = team_word(s, 0);
+    const uint32_t target = *s.met + uint32_t(s.team);
+    *s.met = target;
+    __scoped_atomic_fetch_add(count, 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
+    int64_t spins = 0;
+    while (int32_t(__scoped_atomic_load_n(count, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) - target) <
+           0) {
+      if (++spins > kTeamSpins) {
+        __scoped_atomic_store_n(team_word(s, 1), 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
+        break;
+      }
+#ifdef __AMDGCN__
+      __builtin_amdgcn_s_sleep(1);
+#endif
+    }
+    (void)__scoped_atomic_load_n(count, __ATOMIC_ACQUIRE, __MEMORY_SCOPE_DEVICE);
+  }
+  __syncthreads();
+}
+
+// Publication of one block's solution in a team's sweep: the owner stores the
+// entries with agent-scope atomics, waits until they are there and raises the
+// team's block count; the others look at the count and read the entries with
+// agent-scope atomics. No cache is written back or invalidated (the barrier
+// above does both, for every workgroup on the XCD, and a sweep has one of
+// these per block).
+__device__ __forceinline__ void publish(double RBT_AS_GLOBAL *p, double v) {
+  __scoped_atomic_store_n((uint64_t RBT_AS_GLOBAL *)p, __builtin_bit_cast(uint64_t, v),
+                          __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+}
+__device__ __forceinline__ double published(const double RBT_AS_GLOBAL *p) {
+  return __builtin_bit_cast(double, __scoped_atomic_load_n((const uint64_t RBT_AS_GLOBAL *)p,
+                                                           __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE));
+}
+__device__ __forceinline__ void team_block(const SoloSys &, bool) { __syncthreads(); }
+__device__ __noinline__ void team_block(const TeamSys &s, bool owner) {
+#ifdef __AMDGCN__
+  if (owner) __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores are complete
+#endif
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t *count = team_word(s, 3);
+    const uint32_t target = s.met[1] + 1;
+    s.met[1] = target;
+    if (owner) {
+      __scoped_atomic_store_n(count, target, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+    } else {
+      int64_t spins = 0;
+      while (int32_t(__scoped_atomic_load_n(count, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) -
+                     target) < 0) {
+        if (++spins > kTeamSpins) {
+          __scoped_atomic_store_n(team_word(s, 1), 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
+          break;
+        }
+#ifdef __AMDGCN__
+        __builtin_amdgcn_s_sleep(1);
+#endif
+      }
+    }
+  }
+  __syncthreads();
+}
 
 template <typename T>
 __device__ __forceinline__ T *fmat(const Sys &s) {
@@ -696,8 +806,8 @@ __device__ __noinline__ void diag_block(const Sys &s, int64_t k, int kb, double 
 // TF = float: FP32 factors (trailing update in FP32 or, BF16U, with BF16
 // operands; CT column tiles of 64 per round of the trailing update);
 // TF = double: FP64 factors (the fallback; FP64 trailing update).
-template <typename TF, bool BF16U, int CT = 1>
-__device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int *info_sh) {
+template <typename TF, bool BF16U, int CT = 1, typename S>
+__device__ __noinline__ void eliminate(const S &s, double *L0, double *L1, int *info_sh) {
   const int64_t n = wave_uniform(s.n);
   TF *F = fmat<TF>(s);
   TF *Inv = reinterpret_cast<TF *>(wave_uniform(s.Inv));
@@ -705,14 +815,35 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
   float(*Bs)[LDF] = reinterpret_cast<float(*)[LDF]>(L0 + (BB * LDF + 1) / 2);
   __bf16(*Ah)[LDH] = reinterpret_cast<__bf16(*)[LDH]>(L0);
   __bf16(*Bh)[LDH] = reinterpret_cast<__bf16(*)[LDH]>(L0 + (BB * LDH) / 4);
+  const int team = s.members(), rank = s.member();
+  // first row of this member's strips below the block at k, and their stride
+  const int64_t stride = int64_t(team) * BB;
   for (int64_t k = 0; k < n; k += BB) {
     const int kb = int(n - k < BB ? n - k : BB);
     // inverse block k / BB, counted in elements of the factors' type (the
     // sweeps index the area the same way)
     TF *Invb = Inv + (k / BB) * BB * BB;
-    diag_block<TF>(s, k, kb, L0, L1, Invb, info_sh);
+    const bool mine = int(k / BB) % team == rank;
+    if (mine) diag_block<TF>(s, k, kb, L0, L1, Invb, info_sh);
     const int64_t rest = n - k - kb;
     if (rest <= 0) break;
+    if (team > 1) {
+      // the other members take the inverses (and for FP32 L\U itself) from
+      // memory into the places where diag_block leaves them
+      team_sync(s);
+      if (!mine) {
+        typename Lds<TF>::T *Tw = (typename Lds<TF>::T *)L1;
+        const TF RBT_AS_GLOBAL *Ig = (const TF RBT_AS_GLOBAL *)Invb;
+        const TF RBT_AS_GLOBAL *Fk = (const TF RBT_AS_GLOBAL *)F + k + k * n;  // (kb = 64 here)
+#pragma unroll 4
+        for (int e = threadIdx.x; e < BB * BB; e += BT) {
+          const int r = e & 63, c = e >> 6;
+          Tw[c * LDS_ + r] = Ig[e];
+          if constexpr (sizeof(TF) == 4) Tw[(BB + c) * LDS_ + r] = Fk[r + c * n];
+        }
+        __syncthreads();
+      }
+    }
     f4 acc[2][2];
     typename Mma16<double>::v4 acc64[2][2];
     // panel products in the factors' arithmetic type. A product with an
@@ -731,8 +862,10 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
     lds_t *L0w = (lds_t *)L0;
     lds_t *X0s = L0w + BB * LDS_;        // FP32: the first product
     TF *L0t = reinterpret_cast<TF *>(L0);
+    const int next = int(k / BB + 1) % team;  // the member that owns the strip below the block
+    const int64_t own = k + BB + int64_t((rank - next + team) % team) * BB;
     // L21 = A21 U11^-1 (rows k+kb.., 64-row tiles)
-    for (int64_t r0 = k + kb; r0 < n; r0 += BB) {
+    for (int64_t r0 = own; r0 < n; r0 += stride) {
       const int rv = int(n - r0 < BB ? n - r0 : BB);
       // stage A21 tile as [k][r]: element (r, kx) at L0[kx * LDS_ + r]
       stage_c<TF>(L0t, F + r0 + k * n, n, rv, kb);
@@ -756,7 +889,7 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
     }
     __syncthreads();
     // U12 = L11^-1 A12 (64-column tiles)
-    for (int64_t c0 = k + kb; c0 < n; c0 += BB) {
+    for (int64_t c0 = k + kb + int64_t(rank) * BB; c0 < n; c0 += stride) {
       const int cv = int(n - c0 < BB ? n - c0 : BB);
       // stage A12 tile: element (kx, nx) at L0[nx * LDS_ + kx]
       stage_c<TF>(L0t, F + k + c0 * n, n, kb, cv);
@@ -780,7 +913,7 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
       __syncthreads();
       tile_store_c<TF>(accp, F + k + c0 * n, n, kb, cv);
     }
-    __syncthreads();
+    team_sync(s);
     // A22 -= L21 U12 (64 x 64 tiles; the L21 row tile stays in LDS)
     if constexpr (sizeof(TF) == 4) {
       // low precision: CT column tiles per round (the second U12 tile in
@@ -790,7 +923,7 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
       void *bdst[CT];
       bdst[0] = BF16U ? static_cast<void *>(Bh) : static_cast<void *>(Bs);
       if constexpr (CT > 1) bdst[1] = static_cast<void *>(L1);
-      for (int64_t r0 = k + kb; r0 < n; r0 += BB) {
+      for (int64_t r0 = own; r0 < n; r0 += stride) {
         const int rv = int(n - r0 < BB ? n - r0 : BB);
         if constexpr (BF16U)
           stage<true, false>(Ah, Fg + r0 + k * n, n, rv, kb);
@@ -851,7 +984,7 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
     const int bcol = tid >> 2, bseg = (tid & 3) * 16;  // U12 tile: column nx, rows kx
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1, l16 = lane & 15, lk = lane >> 4;
-    for (int64_t r0 = k + kb; r0 < n; r0 += BB) {
+    for (int64_t r0 = own; r0 < n; r0 += stride) {
       const int rv = int(n - r0 < BB ? n - r0 : BB);
       stage_c<double>(L0, F + r0 + k * n, n, rv, kb);  // (r, kx) at L0[kx * LDS_ + r]
       double bv[16], cn[2][2][4];
@@ -911,25 +1044,46 @@ __device__ __noinline__ void eliminate(const Sys &s, double *L0, double *L1, int
     }
     __syncthreads();
   }
+  if (team > 1) {
+    // first zero pivot over the members' diagonal blocks
+    if (threadIdx.x == 0 && *info_sh != 0) {
+      uint32_t *w = team_word(s, 2);
+      uint32_t seen = __scoped_atomic_load_n(w, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+      const uint32_t v = uint32_t(*info_sh);
+      while ((seen == 0 || v < seen) &&
+             !__scoped_atomic_compare_exchange_n(w, &seen, v, false, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE)) {
+      }
+    }
+    team_sync(s);
+    if (threadIdx.x == 0)
+      *info_sh = int(__scoped_atomic_load_n(team_word(s, 2), __ATOMIC_RELAXED,
+                                            __MEMORY_SCOPE_DEVICE));
+    __syncthreads();
+  }
 }
 
 // One-sided transform of the n x nrhs block Y (ld ldy) with coefficients C,
 // in passes of at most three layers (op T: layers d..1, op N: 1..d).
-template <int OP>
-__device__ __noinline__ void transform_vec_sys(const Sys &s, int d, double *Y, int64_t ldy_in,
+template <int OP, typename S>
+__device__ __noinline__ void transform_vec_sys(const S &s, int d, double *Y, int64_t ldy_in,
                                                const double *C) {
-  if (d == 0) return;
+  if (d == 0) {
+    team_sync(s);
+    return;
+  }
   double RBT_AS_GLOBAL *Yg = (double RBT_AS_GLOBAL *)wave_uniform(Y);
   const double RBT_AS_GLOBAL *Cg = (const double RBT_AS_GLOBAL *)wave_uniform(C);
   const int64_t ldy = wave_uniform(ldy_in), n = wave_uniform(s.n), q = wave_uniform(s.q);
   const int nrhs = int(wave_uniform(s.nrhs));
+  const int team = s.members(), rank = s.member();
   for (int k = 0; k < (d + 2) / 3; ++k) {
     // op T: passes (d-2..d), (d-5..d-3), ...; op N: (1..3), (4..6), ...
     const int hi = OP == RBT_OP_T ? d - 3 * k : (3 * k + 3 < d ? 3 * k + 3 : d);
     const int lo = OP == RBT_OP_T ? (hi - 2 > 1 ? hi - 2 : 1) : 3 * k + 1;
     const dev::Pass ps = dev::make_pass(n, q, d, lo, hi, s.rot, s.sides);
     const int ng = int(ps.ngroups);
-    for (int e = threadIdx.x; e < ng * nrhs; e += BT) {
+    for (int e = threadIdx.x + BT * rank; e < ng * nrhs; e += BT * team) {
       const int gr = e % ng, j = e / ng;
       const int64_t rb = dev::group_base(ps, gr);
       if (rb >= n) continue;
@@ -939,7 +1093,7 @@ __device__ __noinline__ void transform_vec_sys(const Sys &s, int d, double *Y, i
         default: dev::transform_vec_block<3, OP>(Yg, ldy, j, Cg, ps, rb); break;
       }
     }
-    __syncthreads();
+    team_sync(s);
   }
 }
 
@@ -956,8 +1110,8 @@ __device__ __noinline__ void transform_vec_sys(const Sys &s, int d, double *Y, i
 // rows per wavefront, their operands loaded during the step before: one
 // barrier each (FMA loops over 16-column segments, summed through LDS, made a
 // block's solve 10 us of dependent LDS reads and barriers).
-template <bool LOWER, typename TF>
-__device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, double *L0) {
+template <bool LOWER, typename TF, typename S>
+__device__ __noinline__ void sweep(const S &s, double *Y_in, int64_t ldy_in, double *L0) {
   typedef Mma16<TF> M;
   typedef typename Lds<TF>::T lds_t;
   constexpr int XN = NR + 1;  // LDS row of an x block
@@ -1019,6 +1173,7 @@ __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, d
     for (int v = 0; v < 4; ++v) xp[(16 * wave + M::row(lk, v)) * XN + l16] = val[v];
   };
   TF dv[16], dn[16], tv[REFINE ? 16 : 1], tn[REFINE ? 16 : 1];
+  const int team = s.members(), rank = s.member();
   load_diag(LOWER ? 0 : nblk - 1, dv, tv);
   for (int64_t t = 0; t < nblk; ++t) {
     const int64_t b = LOWER ? t : nblk - 1 - t;
@@ -1027,40 +1182,53 @@ __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, d
     TF y[4], x[4];
     bool in[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = 16 * wave + M::row(lk, v);
-      in[v] = row < kb && l16 < N;
-      y[v] = in[v] ? TF(Y[(r0 + row) + int64_t(l16) * ldy]) : TF(0);
-    }
-    to_lds(x0s, y);
-    __syncthreads();
-    product(dv, x0s, x);
-    if constexpr (REFINE) {
-      // FP32: one refinement step against the diagonal block itself, so the
-      // block solve is not limited to kappa(block) u32 (the product with an
-      // explicit inverse alone is): r = y_b - D x_b, x_b += Dinv r
-      TF r[4], dx[4];
+    for (int v = 0; v < 4; ++v) in[v] = 16 * wave + M::row(lk, v) < kb && l16 < N;
+    auto entry = [&](int v) { return Y + (r0 + 16 * wave + M::row(lk, v)) + int64_t(l16) * ldy; };
+    if (int(b) % team == rank) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = in[v] ? x[v] : TF(0);
-      to_lds(x1s, x);
+      for (int v = 0; v < 4; ++v) y[v] = in[v] ? TF(*entry(v)) : TF(0);
+      to_lds(x0s, y);
       __syncthreads();
-      product(tv, x1s, r);
+      product(dv, x0s, x);
+      if constexpr (REFINE) {
+        // FP32: one refinement step against the diagonal block itself, so the
+        // block solve is not limited to kappa(block) u32 (the product with an
+        // explicit inverse alone is): r = y_b - D x_b, x_b += Dinv r
+        TF r[4], dx[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) r[v] = in[v] ? y[v] - r[v] : TF(0);
-      to_lds(x0s, r);
+        for (int v = 0; v < 4; ++v) x[v] = in[v] ? x[v] : TF(0);
+        to_lds(x1s, x);
+        __syncthreads();
+        product(tv, x1s, r);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) r[v] = in[v] ? y[v] - r[v] : TF(0);
+        to_lds(x0s, r);
+        __syncthreads();
+        product(dv, x0s, dx);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] += dx[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        x[v] = in[v] ? x[v] : TF(0);
+        if (in[v]) {
+          if (team > 1)
+            publish(entry(v), double(x[v]));
+          else
+            *entry(v) = double(x[v]);
+        }
+      }
+      to_lds(xs, x);
+      team_block(s, true);
+    } else {
+      team_block(s, false);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = in[v] ? TF(published(entry(v))) : TF(0);
+      to_lds(xs, x);
       __syncthreads();
-      product(dv, x0s, dx);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] += dx[v];
     }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      x[v] = in[v] ? x[v] : TF(0);
-      if (in[v]) Y[(r0 + 16 * wave + M::row(lk, v)) + int64_t(l16) * ldy] = double(x[v]);
-    }
-    to_lds(xs, x);
-    __syncthreads();
-    if (t + 1 < nblk) load_diag(LOWER ? b + 1 : b - 1, dn, tn);  // in flight during the update
+    const int64_t bn = LOWER ? b + 1 : b - 1;  // the next block's operands, in flight during the update
+    if (t + 1 < nblk && int(bn) % team == rank) load_diag(bn, dn, tn);
     // rows still to be solved: after the block (L) or before it (U)
     const int64_t lo = LOWER ? r0 + kb : 0, hi = LOWER ? n : r0;
     if (hi > lo) {
@@ -1091,15 +1259,18 @@ __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, d
       };
       TF av[16], an[16];
       double yv[4], yn[4];
-      int64_t tt = wave;
+      // (this member's strips: four tiles each, one per wavefront)
+      const int64_t tstep = 4 * int64_t(team);
+      const int q0 = LOWER ? int(b) + 1 : 0;
+      int64_t tt = wave + 4 * int64_t((rank - q0 % team + team) % team);
       if (tt < ntile) {
         load_tile(tt, av);
         load_y(tt, yv);
       }
-      for (; tt < ntile; tt += 4) {
-        if (tt + 4 < ntile) {
-          load_tile(tt + 4, an);
-          load_y(tt + 4, yn);
+      for (; tt < ntile; tt += tstep) {
+        if (tt + tstep < ntile) {
+          load_tile(tt + tstep, an);
+          load_y(tt + tstep, yn);
         }
         typename M::v4 o = {TF(0), TF(0), TF(0), TF(0)};
 #pragma unroll
@@ -1133,8 +1304,8 @@ __device__ __noinline__ void sweep(const Sys &s, double *Y_in, int64_t ldy_in, d
 // with_anorm: also ||A||_inf into *anorm. One pass over A (rows on
 // threads, X staged in LDS by chunks of columns), then the column maxima of
 // |R|, |X|, |B| in a second, small pass.
-template <int NRT>
-__device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anorm, double *anorm) {
+template <int NRT, typename S>
+__device__ __noinline__ double residual(const S &s, double *L0, bool with_anorm, double *anorm) {
   const int64_t n = wave_uniform(s.n);
   const int N = int(wave_uniform(s.nrhs));
   const int64_t lda = wave_uniform(s.lda), ldx = wave_uniform(s.ldx), ldb = wave_uniform(s.ldb);
@@ -1149,7 +1320,11 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
   double RBT_AS_GLOBAL *Rg = (double RBT_AS_GLOBAL *)wave_uniform(s.R);
   double amax = 0.0;
   const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lk = lane >> 4;
-  for (int64_t m0 = 0; m0 < n; m0 += BT) {
+  // this member's rows [mlo, mhi)
+  const int team = s.members(), rank = s.member();
+  const int64_t part = ((n + team - 1) / team + 63) / 64 * 64;
+  const int64_t mlo = part * rank < n ? part * rank : n, mhi = mlo + part < n ? mlo + part : n;
+  for (int64_t m0 = mlo; m0 < mhi; m0 += BT) {
     const int64_t m = m0 + tid;
     double acc[NRT < NR ? NRT : 1];
     typename Mma16<double>::v4 acc4[4];  // NR: row tiles 16 q of the wavefront's 64 rows
@@ -1196,7 +1371,7 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
             }
           }
         }
-      } else if (m < n) {
+      } else if (m < mhi) {
         const double RBT_AS_GLOBAL *Ap = Ag + m + k0 * lda;
         // batches of 32 loads in flight (kc is a multiple of 32 except at the
         // end): all issued before the first product uses one
@@ -1232,16 +1407,16 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
           double v = asum4[q];
           v += __shfl_xor(v, 16);
           v += __shfl_xor(v, 32);
-          if (r0 + l16 < n) amax = nanmax(amax, v);
+          if (r0 + l16 < mhi) amax = nanmax(amax, v);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int64_t row = r0 + Mma16<double>::row(lk, v);
-          if (row < n && l16 < N)
+          if (row < mhi && l16 < N)
             Rg[row + int64_t(l16) * n] = Bg[row + int64_t(l16) * ldb] - acc4[q][v];
         }
       }
-    } else if (m < n) {
+    } else if (m < mhi) {
       amax = nanmax(amax, asum);
 #pragma unroll
       for (int c = 0; c < NRT; ++c)
@@ -1249,18 +1424,28 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
     }
   }
   __syncthreads();
+  // ||A||_inf, and the column maxima: a wavefront takes every fourth right-hand
+  // side, so only the error is reduced over the workgroup. A team's members
+  // leave theirs in the team area and all combine them.
+  double *mine = s.tw + kBatchTeamHead + rank * (1 + 3 * N);
   if (with_anorm) {
-    const double an = wg_nanmax(amax, red);
-    if (tid == 0) *anorm = an;
+    double an = wg_nanmax(amax, red);
+    if (team > 1) {
+      if (tid == 0) mine[0] = an;
+    } else if (tid == 0) {
+      *anorm = an;
+    }
     __syncthreads();
   }
-  // column maxima: a wavefront takes every fourth right-hand side, so only the
-  // error is reduced over the workgroup
-  const double an = *anorm;
   double be = 0.0;
+  auto column_error = [&](double rm, double xm, double bm) {
+    const double den = *anorm * xm + bm;
+    const double e = den > 0.0 ? rm / den : (rm > 0.0 ? INFINITY : (rm != rm ? rm : 0.0));
+    be = nanmax(be, e);
+  };
   for (int c = wave; c < N; c += BT / 64) {
     double rm = 0.0, xm = 0.0, bm = 0.0;
-    for (int64_t m = lane; m < n; m += 64) {
+    for (int64_t m = mlo + lane; m < mhi; m += 64) {
       rm = nanmax(rm, fabs(Rg[m + int64_t(c) * n]));
       xm = nanmax(xm, fabs(Xg[m + int64_t(c) * ldx]));
       bm = nanmax(bm, fabs(Bg[m + int64_t(c) * ldb]));
@@ -1271,9 +1456,34 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
       xm = nanmax(xm, __shfl_xor(xm, o));
       bm = nanmax(bm, __shfl_xor(bm, o));
     }
-    const double den = an * xm + bm;
-    const double e = den > 0.0 ? rm / den : (rm > 0.0 ? INFINITY : (rm != rm ? rm : 0.0));
-    be = nanmax(be, e);
+    if (team == 1) {
+      column_error(rm, xm, bm);
+    } else if (lane == 0) {
+      mine[1 + 3 * c] = rm;
+      mine[2 + 3 * c] = xm;
+      mine[3 + 3 * c] = bm;
+    }
+  }
+  if (team > 1) {
+    team_sync(s);
+    const double *all = s.tw + kBatchTeamHead;
+    if (with_anorm) {
+      if (tid == 0) {
+        double an = 0.0;
+        for (int q = 0; q < team; ++q) an = nanmax(an, all[q * (1 + 3 * N)]);
+        *anorm = an;
+      }
+      __syncthreads();
+    }
+    for (int c = wave; c < N; c += BT / 64) {
+      double rm = 0.0, xm = 0.0, bm = 0.0;
+      for (int q = 0; q < team; ++q) {
+        rm = nanmax(rm, all[q * (1 + 3 * N) + 1 + 3 * c]);
+        xm = nanmax(xm, all[q * (1 + 3 * N) + 2 + 3 * c]);
+        bm = nanmax(bm, all[q * (1 + 3 * N) + 3 + 3 * c]);
+      }
+      column_error(rm, xm, bm);
+    }
   }
   return wg_nanmax(be, red);
 }
@@ -1286,19 +1496,21 @@ __device__ __noinline__ double residual(const Sys &s, double *L0, bool with_anor
 // extrapolated, cannot reach tol within max_iter steps (the batch's slowest
 // systems are the large ones whose refinement fails; their hopeless steps
 // are spent before the fallback's elimination).
-template <int NRT, typename TF>
-__device__ void refine_system(const Sys &s, int d, double tol, int max_iter, double *L0,
+template <int NRT, typename TF, typename S>
+__device__ void refine_system(const S &s, int d, double tol, int max_iter, double *L0,
                               double *anorm_sh, int *it_out, double *be_out, bool project) {
   const int64_t n = s.n;
   double RBT_AS_GLOBAL *Xg = (double RBT_AS_GLOBAL *)s.Xm;
   const double RBT_AS_GLOBAL *Bg = (const double RBT_AS_GLOBAL *)s.Bm;
   const double RBT_AS_GLOBAL *Rg = (const double RBT_AS_GLOBAL *)s.R;
-  for (int64_t e = threadIdx.x; e < n * s.nrhs; e += BT)
+  const int team = s.members(), rank = s.member();
+  for (int64_t e = threadIdx.x + BT * rank; e < n * s.nrhs; e += BT * team)
     Xg[(e % n) + (e / n) * s.ldx] = Bg[(e % n) + (e / n) * s.ldb];
-  __syncthreads();
+  team_sync(s);
   transform_vec_sys<RBT_OP_T>(s, d, s.Xm, s.ldx, s.U);
   sweep<true, TF>(s, s.Xm, s.ldx, L0);
   sweep<false, TF>(s, s.Xm, s.ldx, L0);
+  team_sync(s);
   if (s.sides != 1) transform_vec_sys<RBT_OP_N>(s, d, s.Xm, s.ldx, s.V);  // x = V x~
   int it = 0, stalled = 0;
   double be = 0.0, best = INFINITY;
@@ -1318,10 +1530,11 @@ __device__ void refine_system(const Sys &s, int d, double tol, int max_iter, dou
     transform_vec_sys<RBT_OP_T>(s, d, s.R, n, s.U);
     sweep<true, TF>(s, s.R, n, L0);
     sweep<false, TF>(s, s.R, n, L0);
+    team_sync(s);
     if (s.sides != 1) transform_vec_sys<RBT_OP_N>(s, d, s.R, n, s.V);
-    for (int64_t e = threadIdx.x; e < n * s.nrhs; e += BT)
+    for (int64_t e = threadIdx.x + BT * rank; e < n * s.nrhs; e += BT * team)
       Xg[(e % n) + (e / n) * s.ldx] += Rg[e];
-    __syncthreads();
+    team_sync(s);
     ++it;
   }
   *it_out = it;
@@ -1333,8 +1546,8 @@ __device__ void refine_system(const Sys &s, int d, double tol, int max_iter, dou
 // its lanes the row groups. A function for each number of layers P, so that
 // each has the registers of its own block size (in one function the largest
 // one's spills and the conditional loads took 9.7 us for 256 blocks; now 4.2).
-template <int P, bool FIRST, typename TF>
-__device__ __noinline__ void transform_pass(const Sys &s, const dev::Pass &pass) {
+template <int P, bool FIRST, typename TF, typename S>
+__device__ __noinline__ void transform_pass(const S &s, const dev::Pass &pass) {
   const int64_t n = wave_uniform(s.n), lda = wave_uniform(s.lda);
   const double RBT_AS_GLOBAL *Ag = (const double RBT_AS_GLOBAL *)wave_uniform(s.A);
   const double RBT_AS_GLOBAL *Ug = (const double RBT_AS_GLOBAL *)wave_uniform(s.U);
@@ -1351,7 +1564,9 @@ __device__ __noinline__ void transform_pass(const Sys &s, const dev::Pass &pass)
   ps.rot = __builtin_amdgcn_readfirstlane(pass.rot);
   ps.sides = __builtin_amdgcn_readfirstlane(pass.sides);
   const int ng = int(ps.ngroups);
-  for (int gc = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)); gc < ng; gc += BT / 64) {
+  const int team = s.members(), rank = s.member();
+  for (int gc = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) + rank * (BT / 64); gc < ng;
+       gc += team * (BT / 64)) {
     const int64_t cb = dev::group_base(ps, gc);
     if (cb >= n) continue;
     for (int gr = threadIdx.x & 63; gr < ng; gr += 64) {
@@ -1369,8 +1584,8 @@ __device__ __noinline__ void transform_pass(const Sys &s, const dev::Pass &pass)
 // low-precision pass, FP64 for the fallback), in passes of at most three
 // layers from layer d down: the first reads A, the later ones the factor
 // storage in place (each block of a pass belongs to one thread).
-template <typename TF>
-__device__ void transform_into(const Sys &s, int d) {
+template <typename TF, typename S>
+__device__ void transform_into(const S &s, int d) {
   for (int hi = d, first = 1; first || hi >= 1; first = 0) {
     const int lo = d == 0 ? 1 : (hi - 2 > 1 ? hi - 2 : 1);
     const dev::Pass ps =
@@ -1390,19 +1605,19 @@ __device__ void transform_into(const Sys &s, int d) {
         default: transform_pass<3, false, TF>(s, ps); break;
       }
     }
-    __syncthreads();
+    team_sync(s);
     if (d == 0) break;
     hi = lo - 1;
   }
 }
 
-template <bool BF16U>
-__device__ void solve_system(const Args &a, const BatchDesc &D, float *fbase, double *dbase,
-                             double *f64base, double *L0, double *L1, int *info_sh,
-                             double *anorm_sh) {
+template <bool BF16U, typename S>
+__device__ void solve_system(const Args &a, const BatchDesc &D, int team_in, int rank_in, float *fbase,
+                             double *dbase, double *f64base, double *L0, double *L1, int *info_sh,
+                             double *anorm_sh, uint32_t *met_sh) {
   const int tid = threadIdx.x;
   const int d = a.depth;
-  Sys s;
+  S s;
   s.n = D.n;
   s.nrhs = D.nrhs;
   {  // m = 2^d g ceil(n / (2^d g)), q = m / 2^d
@@ -1417,6 +1632,10 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, float *fbase, do
   s.V = s.U + s.n * d;
   s.Inv = s.V + s.n * d;
   s.R = s.Inv + ((s.n + BB - 1) / BB) * BB * BB;
+  s.team = team_in;
+  s.rank = rank_in;
+  s.tw = s.R + s.n * s.nrhs;
+  s.met = met_sh;
   s.A = a.A[D.sys];
   s.lda = a.lda[D.sys];
   s.Bm = a.B[D.sys];
@@ -1424,16 +1643,21 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, float *fbase, do
   s.Xm = a.X[D.sys];
   s.ldx = a.ldx[D.sys];
   const int64_t n = s.n;
+  const int team = s.members(), rank = s.member();
   const uint64_t seed = dev::splitmix_at(a.seed, uint64_t(D.sys));
-  if (tid == 0) *info_sh = 0;
+  if (tid == 0) {
+    *info_sh = 0;
+    met_sh[0] = met_sh[1] = 0;
+  }
+  __syncthreads();
   // coefficients
-  for (int64_t e = tid; e < 2 * n * d; e += BT) {
+  for (int64_t e = tid + BT * rank; e < 2 * n * d; e += BT * team) {
     const int side = e >= n * d ? 1 : 0;
     const int64_t rem = e - side * n * d;
     s.U[e] = s.rot ? dev::rotation_coefficient(seed, rem % n, side, int(rem / n) + 1, n, s.q, d)
                    : dev::coefficient(seed, rem % n, side, int(rem / n) + 1);
   }
-  __syncthreads();
+  team_sync(s);
   const double tol = a.tol < 0.0 ? -a.tol * double(n) * 0x1.0p-52 : a.tol;
   int it = 0, path = 0;
   double be = 0.0;
@@ -1442,8 +1666,12 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, float *fbase, do
     if (pass == 1) {
       if (be <= tol || s.F64 == nullptr) break;
       path = 1;
-      if (tid == 0) *info_sh = 0;
-      __syncthreads();
+      if (tid == 0) {
+        *info_sh = 0;
+        if (team > 1 && rank == 0)
+          __scoped_atomic_store_n(team_word(s, 2), 0u, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+      }
+      team_sync(s);
     }
     if (pass == 0)
       transform_into<float>(s, d);
@@ -1473,6 +1701,15 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, float *fbase, do
     }
     it += it_p;
   }
+  if (team > 1) {
+    team_sync(s);
+    // a barrier that expired: no member's results can be relied on
+    if (__scoped_atomic_load_n(team_word(s, 1), __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) != 0) {
+      be = __builtin_nan("");
+      for (int64_t e = tid; e < n * s.nrhs; e += BT) s.Xm[(e % n) + (e / n) * s.ldx] = be;
+    }
+  }
+  if (rank != 0) return;
   if (tid == 0 && a.path) a.path[D.sys] = path;
   if (tid == 0) {
     if (a.iters) a.iters[D.sys] = it;
@@ -1489,6 +1726,7 @@ __global__ void __launch_bounds__(BT, 2) k_batched(Args a) {
   __shared__ int64_t tk_sh;
   __shared__ int info_sh;
   __shared__ double anorm_sh;
+  __shared__ uint32_t met_sh[2];
   BatchHeader *hdr = reinterpret_cast<BatchHeader *>(a.work);
   // a plan for other sizes, depth or precision, or a workspace too small for
   // it: no system is solved, and every system reports it (info -1, berr NaN,
@@ -1509,20 +1747,47 @@ __global__ void __launch_bounds__(BT, 2) k_batched(Args a) {
   double *dbase = reinterpret_cast<double *>(a.work + hdr->d_off_bytes);
   double *f64base =
       hdr->f64_off_bytes > 0 ? reinterpret_cast<double *>(a.work + hdr->f64_off_bytes) : nullptr;
-  // Each round takes one ticket; every ticket below `batch` is taken once
-  // over the grid, so no workgroup needs more than batch + 1 rounds. The
-  // bound makes the loop's end independent of the ticket word's value.
-  for (int64_t round = 0; round <= a.batch; ++round) {
+  // Each round takes one ticket; every ticket below their number is taken
+  // once over the grid, so no workgroup needs more than that and one rounds.
+  // The bound makes the loop's end independent of the ticket word's value. A
+  // grid that could not hold a whole team solves without teams.
+  const bool teams = gridDim.x >= unsigned(kBatchTeamMax) && batched_teams_ok(*hdr);
+  const int64_t t8 = teams ? hdr->teams8 : 0, t4 = teams ? hdr->teams4 : 0,
+                t2 = teams ? hdr->teams2 : 0;
+  const int64_t tickets = a.batch + 7 * t8 + 3 * t4 + t2;
+  for (int64_t round = 0; round <= tickets; ++round) {
     if (threadIdx.x == 0) tk_sh = atomicAdd(&hdr->ticket, 1);
     __syncthreads();
-    const int64_t t = wave_uniform(tk_sh);
+    const int64_t ticket = wave_uniform(tk_sh);
     __syncthreads();
-    if (t < 0 || t >= a.batch) break;
+    if (ticket < 0 || ticket >= tickets) break;
+    int64_t t = ticket;  // entry of the table
+    int team = 1, rank = 0;
+    if (ticket < 8 * t8) {
+      team = 8;
+      t = ticket / 8;
+      rank = int(ticket % 8);
+    } else if (ticket < 8 * t8 + 4 * t4) {
+      team = 4;
+      t = t8 + (ticket - 8 * t8) / 4;
+      rank = int((ticket - 8 * t8) % 4);
+    } else if (ticket < 8 * t8 + 4 * t4 + 2 * t2) {
+      team = 2;
+      t = t8 + t4 + (ticket - 8 * t8 - 4 * t4) / 2;
+      rank = int((ticket - 8 * t8 - 4 * t4) % 2);
+    } else {
+      t = ticket - 7 * t8 - 3 * t4 - t2;
+    }
     const BatchDesc D = desc[t];
     // systems without work (n = 0, or no right-hand side) are not solved;
     // the plan queues them last
     if (D.n > 0 && D.nrhs > 0) {
-      solve_system<BF16U>(a, D, fbase, dbase, f64base, L0, L1, &info_sh, &anorm_sh);
+      if (team == 1)
+        solve_system<BF16U, SoloSys>(a, D, 1, 0, fbase, dbase, f64base, L0, L1, &info_sh, &anorm_sh,
+                                     met_sh);
+      else
+        solve_system<BF16U, TeamSys>(a, D, team, rank, fbase, dbase, f64base, L0, L1, &info_sh,
+                                     &anorm_sh, met_sh);
     } else if (threadIdx.x == 0) {
       if (a.path) a.path[D.sys] = 0;
       if (a.iters) a.iters[D.sys] = 0;
@@ -1532,8 +1797,25 @@ __global__ void __launch_bounds__(BT, 2) k_batched(Args a) {
   }
 }
 
-__global__ void k_reset_ticket(void *work) {
-  if (threadIdx.x == 0) reinterpret_cast<BatchHeader *>(work)->ticket = 0;
+// Before a launch: the ticket, and the words of the teams' areas (of a plan
+// that the launch accepts).
+__global__ void __launch_bounds__(BT) k_reset_ticket(char *work, size_t work_bytes, int64_t batch,
+                                                     int depth, int prec) {
+  BatchHeader *hdr = reinterpret_cast<BatchHeader *>(work);
+  if (threadIdx.x == 0) hdr->ticket = 0;
+  if (hdr->batch != batch || hdr->depth != depth || hdr->prec != prec || hdr->total_bytes < 0 ||
+      size_t(hdr->total_bytes) > work_bytes || !batched_teams_ok(*hdr))
+    return;
+  const BatchDesc *desc = reinterpret_cast<const BatchDesc *>(work + kBatchTableOffset);
+  double *dbase = reinterpret_cast<double *>(work + hdr->d_off_bytes);
+  const int64_t teams = int64_t(hdr->teams8) + hdr->teams4 + hdr->teams2;
+  for (int64_t t = threadIdx.x; t < teams && t < batch; t += BT) {
+    const BatchDesc D = desc[t];
+    double *tw = dbase + D.d_off + batched_sys_doubles(D.n, D.nrhs, depth) -
+                 batched_team_doubles(D.n, D.nrhs);
+    uint32_t *w = reinterpret_cast<uint32_t *>(tw);
+    w[0] = w[1] = w[2] = w[3] = 0;
+  }
 }
 
 }  // namespace
@@ -1568,7 +1850,8 @@ hipError_t launch_batched(int64_t batch, void *work, size_t work_bytes, const do
   a.kind = butterfly_kind();
   a.sides = butterfly_sides();
   a.ct2_min_n = ct2_min_n;
-  hipLaunchKernelGGL(k_reset_ticket, dim3(1), dim3(64), 0, s, work);
+  hipLaunchKernelGGL(k_reset_ticket, dim3(1), dim3(BT), 0, s, static_cast<char *>(work), work_bytes,
+                     batch, depth, prec);
   const dim3 g{unsigned(grid)}, b{unsigned(BT)};
   if (prec == RBT_BF16)
     hipLaunchKernelGGL((k_batched<true>), g, b, 0, s, a);
