@@ -1,22 +1,32 @@
 // Diagonal-block kernel of the blocked elimination without pivoting.
 //
-// One workgroup of 512 threads factors a kb x kb diagonal block (kb <= 128)
-// in place, A = L U with unit-lower L (Sec. 1, step 2: GENP). The block is
-// held in LDS (column-major, leading dimension 129 so that row-wise and
-// column-wise lane patterns are both bank-conflict free) and eliminated in
-// eight 16-column steps:
-//   1. the 16-column panel is factored right-looking, rank-1, by four of the
-//      eight wavefronts, one row per lane; every wavefront keeps its own copy of
-//      the panel's top 16 rows, so each pivot row is broadcast within the
-//      wavefront with readlane and the 16 steps need no workgroup barrier;
-//   2. the 16-row block of U to its right is solved by forward substitution
-//      with the panel's unit-lower 16 x 16 block (four lanes per column);
-//   3. the trailing block takes a rank-16 update on the FP64 matrix cores,
-//      16 x 16 tiles shared out over the eight wavefronts (two per SIMD, so
-//      one wavefront's LDS accesses overlap the other's products); each tile's
-//      accumulator starts from the LDS values and the L operand is negated.
-// Rows and columns beyond kb hold the identity, so they never disturb the
-// active part. The arithmetic type C is FP64 for FP64 factors; for the FP32
+// One workgroup of 1024 threads factors a kb x kb diagonal block (kb <= 128)
+// in place, A = L U with unit-lower L (Sec. 1, step 2: GENP), in eight
+// 16-column steps on the block held in LDS (column-major, leading dimension
+// 129 so that row-wise and column-wise lane patterns are both bank-conflict
+// free). Every diagonal block is on the elimination's critical path and
+// leaves the rest of the device idle, so what counts is the chain of 128
+// pivots (a division, a multiplication, an update each); the rest is
+// arranged to run beside it. In step p, columns c0 = 16 p .. c0 + 15:
+//   - wavefronts 0 and 1 factor the panel right-looking, one row per lane;
+//   - wavefronts 2 and 3 compute the 16-row block of U to its right, one row
+//     per lane and four columns of each 16-column tile per group of 16 lanes;
+//     all four keep a copy of the panel's top 16 rows in each group of 16
+//     lanes, so a pivot row reaches its consumers as a DPP row broadcast
+//     inside the multiply-add, and the 16 pivots need no barrier;
+//   - wavefronts 4 to 15 meanwhile apply step p - 1 to the tiles right of and
+//     below both, on the matrix cores, and store the finished columns;
+//   - then all apply step p to the column tile and the row tile of step p + 1,
+//     a 16 x 16 tile each (accumulators start from the LDS values, the L
+//     operand is negated).
+// Step 0 takes the panel and its row block straight from memory while
+// wavefronts 4 to 15 stage the rest. Rows and columns beyond kb hold the
+// identity, so they never disturb the active part. Measured for 128 columns:
+// 36.7 -> 28.3 us (FP64) and 27.6 -> 21.8 us (FP32) against panel, row block and update
+// one after the other on eight wavefronts with the pivot rows broadcast by
+// readlane; a panel on its own takes 4200 cycles and 5000 to 7000 beside the
+// products, which share the FP64 and FP32 units with it.
+// The arithmetic type C is FP64 for FP64 factors; for the FP32
 // factors of the mixed-precision elimination it is FP32 (LDS, broadcasts,
 // the FP32 matrix cores), or FP64 as an option, in which case the block is
 // widened on load and rounded once on store. A zero pivot is recorded in
@@ -31,9 +41,111 @@ namespace {
 
 constexpr int NB = kNB;  // 128
 constexpr int LD = NB + 1;
-constexpr int PW = 16;   // panel width
-constexpr int NT = 512;  // threads
+constexpr int PW = 16;    // panel width
+constexpr int NT = 1024;  // threads
 constexpr int NW = NT / 64;
+constexpr int UW0 = 2;    // first wavefront of the row block
+constexpr int XW0 = 4;    // first wavefront of the trailing update
+constexpr int XW = NW - XW0;
+
+// v of lane K of each group of 16 lanes, to the whole group.
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xF, 0xF, true));
+}
+template <int K>
+__device__ __forceinline__ double row_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + K, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + K, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
+// x[j] += m * (y[j] of lane K of the group of 16), j = 0 .. N - 1. The
+// broadcast is the first operand of v_fmac, a form that the compiler does not
+// make for FP64 by itself (it moves both halves first); the leading s_nop is
+// the distance that a DPP operand needs from the instruction that wrote it.
+#define RBT_FMAC_OP(T, D, S0, M, K) \
+  "v_fmac_" T "_dpp " D ", " S0 ", " M " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define RBT_FMAC_ROWS(C, T)                                                                     \
+  template <int K, int N>                                                                       \
+  __device__ __forceinline__ void fmac_rows(C *x, const C *y, C m) {                            \
+    if constexpr (N >= 4) {                                                                     \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%4", "%8", "%9")                              \
+                  RBT_FMAC_OP(T, "%1", "%5", "%8", "%9") RBT_FMAC_OP(T, "%2", "%6", "%8", "%9") \
+                      RBT_FMAC_OP(T, "%3", "%7", "%8", "%9")                                    \
+              : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])                                  \
+              : "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]), "v"(m), "n"(K));                    \
+      fmac_rows<K, N - 4>(x + 4, y + 4, m);                                                     \
+    } else if constexpr (N >= 2) {                                                              \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%2", "%4", "%5")                              \
+                  RBT_FMAC_OP(T, "%1", "%3", "%4", "%5")                                        \
+              : "+v"(x[0]), "+v"(x[1])                                                          \
+              : "v"(y[0]), "v"(y[1]), "v"(m), "n"(K));                                          \
+      fmac_rows<K, N - 2>(x + 2, y + 2, m);                                                     \
+    } else if constexpr (N == 1) {                                                              \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%1", "%2", "%3")                              \
+              : "+v"(x[0])                                                                      \
+              : "v"(y[0]), "v"(m), "n"(K));                                                     \
+    }                                                                                           \
+  }                                                                                             \
+  /* x[j] += m * (x[j] of lane K of the group), m of lane K zero */                             \
+  template <int K, int N>                                                                       \
+  __device__ __forceinline__ void fmac_rows(C *x, C m) {                                        \
+    if constexpr (N >= 4) {                                                                     \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%0", "%4", "%5")                              \
+                  RBT_FMAC_OP(T, "%1", "%1", "%4", "%5") RBT_FMAC_OP(T, "%2", "%2", "%4", "%5") \
+                      RBT_FMAC_OP(T, "%3", "%3", "%4", "%5")                                    \
+              : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])                                  \
+              : "v"(m), "n"(K));                                                                \
+      fmac_rows<K, N - 4>(x + 4, m);                                                            \
+    } else if constexpr (N >= 2) {                                                              \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%0", "%2", "%3")                              \
+                  RBT_FMAC_OP(T, "%1", "%1", "%2", "%3")                                        \
+              : "+v"(x[0]), "+v"(x[1])                                                          \
+              : "v"(m), "n"(K));                                                                \
+      fmac_rows<K, N - 2>(x + 2, m);                                                            \
+    } else if constexpr (N == 1) {                                                              \
+      __asm__("s_nop 1\n\t" RBT_FMAC_OP(T, "%0", "%0", "%1", "%2") : "+v"(x[0]) : "v"(m), "n"(K)); \
+    }                                                                                           \
+  }
+RBT_FMAC_ROWS(double, "f64")
+RBT_FMAC_ROWS(float, "f32")
+#undef RBT_FMAC_ROWS
+#undef RBT_FMAC_OP
+
+// Pivots K .. 15 of a panel: t holds the top 16 rows (a row per lane, in each
+// group of 16 lanes), x what else the pivots update: PANEL, a row of the panel
+// below the top per lane (its entry K becomes the multiplier); otherwise
+// entries of the top's rows in 16 columns right of the panel. rp is the
+// reciprocal of pivot K. The column of the next pivot is updated first, and its
+// division (the chain) is issued between the other updates.
+template <int K, bool PANEL, typename C>
+__device__ __forceinline__ void pivot_steps(C (&t)[PW], C (&x)[PW], int l16, C rp) {
+  const C mt = -t[K] * (l16 > K ? rp : C(0));  // rows up to the pivot's keep their values
+  const C lx = PANEL ? x[K] * rp : C(0);
+  if constexpr (K + 1 < PW) {
+    fmac_rows<K, 1>(t + K + 1, mt);
+    __asm__("s_nop 1" : "+v"(t[K + 1]));  // (the broadcast's distance from it)
+    const C q = row_bcast<K + 1>(t[K + 1]);
+    C rn = C(1) / q;  // one division per pivot (scaling as in LAPACK's getf2)
+    if constexpr (PANEL)
+      fmac_rows<K, PW - 1 - K>(x + K + 1, t + K + 1, -lx);
+    else
+      fmac_rows<K, PW>(x, mt);
+    fmac_rows<K, PW - 2 - K>(t + K + 2, mt);
+    if constexpr (PANEL) x[K] = lx;
+    t[K] = l16 > K ? -mt : t[K];
+    __builtin_amdgcn_sched_barrier(0);
+    pivot_steps<K + 1, PANEL>(t, x, l16, rn);
+  } else {
+    if constexpr (PANEL)
+      x[K] = lx;
+    else
+      fmac_rows<K, PW>(x, mt);
+    t[K] = l16 > K ? -mt : t[K];
+  }
+}
 
 template <typename T, typename C>
 __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64_t lda,
@@ -43,172 +155,184 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
   __shared__ C S[NB * LD];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lk = lane >> 4;
+  const int nt = (kb + PW - 1) / PW;  // 16-column tiles
 
-  // Staging: every load of a batch is issued before any is consumed, so the
-  // batch costs one memory latency instead of one per element.
-  {
-    const int r = tid & (NB - 1), c0 = tid >> 7;  // row, first column (0..3)
-    // unconditional loads at clamped valid indices, all 32 in flight,
-    // masked afterwards
-    T v[NB * NB / NT];
-    const int rr = r < kb ? r : kb - 1;
+  // entry (r, c) of the block, identity beyond kb: the load is unconditional at
+  // clamped indices, so that a batch of them is in flight together
+  auto raw = [&](int r, int c) {
+    return A[(r < kb ? r : kb - 1) + int64_t(c < kb ? c : kb - 1) * lda];
+  };
+  auto entry = [&](T v, int r, int c) {
+    return (r < kb && c < kb) ? C(v) : (r == c ? C(1) : C(0));
+  };
+  // tile (i, j) -= (tile column q of L, row tile i) (tile row q of U, column tile j)
+  auto update_tile = [&](int q, int i, int j) {
+    const C *pa = S + (PW * q + lk) * LD + PW * i + l16;
+    const C *pb = S + (PW * j + l16) * LD + PW * q + lk;
+    C *pc = S + (PW * j + l16) * LD + PW * i + M::row(lk, 0);
+    constexpr int RS = M::row(0, 1);  // rows between the lane's results
+    c4 acc;
+    C a[4], b[4];
 #pragma unroll
-    for (int i = 0; i < NB * NB / NT; ++i) {
-      const int c = c0 + (NT / NB) * i;
-      v[i] = A[rr + int64_t(c < kb ? c : kb - 1) * lda];
+    for (int kk = 0; kk < 4; ++kk) {
+      a[kk] = -pa[4 * kk * LD];
+      b[kk] = pb[4 * kk];
     }
 #pragma unroll
-    for (int i = 0; i < NB * NB / NT; ++i) {
-      const int c = c0 + (NT / NB) * i;
-      S[c * LD + r] = (r < kb && c < kb) ? C(v[i]) : ((r == c) ? C(1) : C(0));
+    for (int v = 0; v < 4; ++v) acc[v] = pc[RS * v];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = M::mma(a[kk], b[kk], acc);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) pc[RS * v] = acc[v];
+  };
+  auto store_half = [&](int c, int h) {  // 64 rows of column c
+    const int r = 64 * h + lane;
+    if (r < kb && c < kb) A[r + int64_t(c) * lda] = T(S[c * LD + r]);
+  };
+
+  // Wavefronts 0 to 3: t, the top row of the step; x, on 0 and 1 the lane's row
+  // below the panel, on 2 and 3 the top row's entries in column tiles
+  // p + 1 + 4 (wave - 2) and the three after it, lane group lk columns 4 lk ..
+  // 4 lk + 3 of each. A wavefront has a part in step p only where its rows or
+  // tiles exist.
+  C t[PW], x[PW];
+  auto below = [&](int p) { return PW * (p + 1) + 64 * wave + lane; };
+  auto tile0 = [&](int p) { return p + 1 + 4 * (wave - UW0); };
+  auto panel = [&](int p) {
+    return wave == 0 || (wave < UW0 && PW * (p + 1) + 64 * wave < PW * nt);
+  };
+  auto row_block = [&](int p) { return wave >= UW0 && wave < XW0 && tile0(p) < nt; };
+  auto last = [](int i) { return i < NB ? i : NB - 1; };
+  if (panel(0)) {
+    T vt[PW], vx[PW];
+    const int r = last(below(0));
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      vt[j] = raw(l16, j);
+      vx[j] = raw(r, j);
+    }
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      t[j] = entry(vt[j], l16, j);
+      x[j] = entry(vx[j], r, j);
+    }
+  } else if (row_block(0)) {
+    T vt[PW], vx[PW];
+    auto col = [&](int j) { return last(PW * (tile0(0) + j / 4) + 4 * lk + j % 4); };
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      vt[j] = raw(l16, j);
+      vx[j] = raw(l16, col(j));
+    }
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      t[j] = entry(vt[j], l16, j);
+      x[j] = entry(vx[j], l16, col(j));
+    }
+  } else if (wave >= XW0) {
+    // the rest of the block, rows and columns 16 .. 127 (indices beyond the
+    // last repeat it)
+    constexpr int NI = (NB - PW + XW - 1) / XW;
+    T v[2 * NI];
+    const int r0 = PW + lane, r1 = last(PW + 64 + lane);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = last(PW + (wave - XW0) + XW * i);
+      v[2 * i] = raw(r0, c);
+      v[2 * i + 1] = raw(r1, c);
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = last(PW + (wave - XW0) + XW * i);
+      S[c * LD + r0] = entry(v[2 * i], r0, c);
+      S[c * LD + r1] = entry(v[2 * i + 1], r1, c);
     }
   }
-  __syncthreads();
-
-  for (int c0 = 0; c0 < kb; c0 += PW) {
-    // ---- 1. panel factorization (rows >= c0, columns c0..c0+15) by all
-    // four wavefronts: lanes 0..15 of every wavefront hold the panel's top
-    // 16 rows and update their own copy (the copies see identical
-    // operations), so each pivot row is broadcast within the wavefront with
-    // readlane and no barrier is needed; lanes 16..63 hold one row below
-    // them each (48 per wavefront). Rows above the pivot take a zero
-    // multiplier. ----
-    if (wave < 4) {
-      const bool top = lane < PW;
-      const int row = top ? c0 + lane : c0 + PW + wave * 48 + (lane - PW);
-      const bool valid = row < NB;
-      const int rr = valid ? row : NB - 1;
-      C x[PW];
+  if (wave < XW0) __builtin_amdgcn_s_setprio(3);  // the chain's wavefronts issue first
+#pragma unroll 1
+  for (int p = 0; p < nt; ++p) {
+    const int c0 = PW * p, c1 = c0 + PW;
+    if (panel(p)) {
+      pivot_steps<0, true>(t, x, l16, C(1) / row_bcast<0>(t[0]));
+      if (wave == 0) {  // first zero pivot of the panel: lane j holds pivot j in t[j]
+        C d = t[0];
 #pragma unroll
-      for (int j = 0; j < PW; ++j) x[j] = S[(c0 + j) * LD + rr];
-      // The loop body is kept free of branches (a zero pivot is found after
-      // it; the reciprocal and the scaled entry are pinned before the
-      // selects), so that the compiler can start a pivot's division while
-      // the previous pivot's updates are still issuing.
-#pragma unroll
-      for (int cc = 0; cc < PW; ++cc) {
-        C prow[PW];
-#pragma unroll
-        for (int j = cc; j < PW; ++j) prow[j] = wave_bcast(x[j], cc);
-        const C p = prow[cc];
-        const bool act = top ? lane > cc : valid;
-        C rp = C(1) / p;  // one division per pivot (scaling as in LAPACK's getf2)
-        __asm__ volatile("" : "+v"(rp));
-        C lm = x[cc] * rp;
-        __asm__ volatile("" : "+v"(lm));
-        const C l = act ? lm : C(0);
-        x[cc] = act ? l : x[cc];
-#pragma unroll
-        for (int j = cc + 1; j < PW; ++j) x[j] -= l * prow[j];
-      }
-      {  // first zero pivot of the panel: top lane j of wavefront 0 holds pivot j in x[j]
-        C d = x[0];
-#pragma unroll
-        for (int j = 1; j < PW; ++j) d = lane == j ? x[j] : d;
-        const unsigned long long z = __ballot(top && c0 + lane < kb && d == C(0));
-        if (wave == 0 && lane == 0 && z != 0 && info != nullptr)
+        for (int j = 1; j < PW; ++j) d = l16 == j ? t[j] : d;
+        const unsigned long long z = __ballot(lane < PW && c0 + lane < kb && d == C(0));
+        if (lane == 0 && z != 0 && info != nullptr)
           atomicCAS(info, 0, int32_t(gofs + c0 + __ffsll(z)));
-      }
-      if ((top && wave == 0) || (!top && valid)) {
+        if (lane < PW) {
+          C *q = S + c0 * LD + c0 + l16;
 #pragma unroll
-        for (int j = 0; j < PW; ++j) S[(c0 + j) * LD + row] = x[j];
-      }
-    }
-    __syncthreads();
-
-    const int c1 = c0 + PW;  // first column/row after the panel
-    if (c1 >= NB) break;
-    // ---- 2. U block row: rows c0..c0+15, columns c1..127, by forward
-    // substitution with the unit-lower 16 x 16 block: four lanes per column
-    // (lane q of a quad holds rows q, q + 4, q + 8, q + 12), column c1 + g
-    // for quad g, the pivot entry passed on by a quad broadcast and the next
-    // pivot's coefficients read during this one. Every entry sees the same
-    // operations in the same order as one-lane-per-column substitution. ----
-    {
-      const int g = tid >> 2, q = tid & 3;
-      const int colA = c1 + g;
-      const bool hasA = colA < NB;
-      const int ca = hasA ? colA : NB - 1;
-      C ya[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) ya[jj] = S[ca * LD + c0 + q + 4 * jj];
-      C tn[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) tn[jj] = S[c0 * LD + c0 + q + 4 * jj];
-#pragma unroll
-      for (int j = 0; j < PW; ++j) {  // pivot j: entries i > j lose L(i, j) y_j
-        const int jc = j >> 2, qc = j & 3;
-        C t[4];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) t[jj] = tn[jj];
-        if (j + 1 < PW) {
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) tn[jj] = S[(c0 + j + 1) * LD + c0 + q + 4 * jj];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const C ba = quad_bcast(ya[jc], qc);
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          if (4 * jj + 3 <= j) continue;
-          const bool upd = 4 * jj > j || q + 4 * jj > j;
-          const C na = fma_c(-t[jj], ba, ya[jj]);
-          ya[jj] = upd ? na : ya[jj];
+          for (int j = 0; j < PW; ++j) q[j * LD] = t[j];
         }
       }
-      if (hasA) {
+      if (below(p) < NB) {
+        C *q = S + c0 * LD + below(p);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) S[colA * LD + c0 + q + 4 * jj] = ya[jj];
+        for (int j = 0; j < PW; ++j) q[j * LD] = x[j];
       }
+    } else if (row_block(p)) {
+      pivot_steps<0, false>(t, x, l16, C(1) / row_bcast<0>(t[0]));
+      C *q = S + (PW * tile0(p) + 4 * lk) * LD + c0 + l16;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        if (tile0(p) + h < nt) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) q[(PW * h + j) * LD] = x[4 * h + j];
+        }
+      }
+    } else if (wave >= XW0 && p > 0) {
+      // step p - 1 on the tiles beyond step p's, and the columns that it
+      // finished to memory
+      // (from p = 3 on wavefronts 1 and 3 have no part: the products go to their
+      // SIMDs, since one that issues them slows a chain beside it)
+      const int m = nt - 1 - p;
+      const bool odd = m <= 4;
+      const int first = odd ? (wave - XW0) >> 1 : wave - XW0;
+      const int step = odd ? XW / 2 : XW;
+      for (int i = first, j = 0; m > 0 && !(odd && (wave & 1) == 0); i += step) {
+        while (i >= m && j < m) {
+          i -= m;
+          ++j;
+        }
+        if (j >= m) break;
+        update_tile(p - 1, p + 1 + i, p + 1 + j);
+      }
+      for (int e = wave - XW0; e < 2 * PW; e += XW) store_half(c0 - PW + (e >> 1), e & 1);
     }
     __syncthreads();
-    // ---- 3. trailing rank-16 update on 16 x 16 tiles, two per wavefront
-    // at a time (tiles t and t + NW), so their LDS loads overlap ----
-    const int nt = (NB - c1) / PW;
-    const int ntt = nt * nt;
-    for (int t = wave; t < ntt; t += 2 * NW) {
-      const bool two = t + NW < ntt;
-      const int tb = two ? t + NW : t;
-      const int i0 = c1 + PW * (t % nt), j0 = c1 + PW * (t / nt);
-      const int i1 = c1 + PW * (tb % nt), j1 = c1 + PW * (tb / nt);
-      c4 acc0, acc1;
-      C a0[4], b0[4], a1[4], b1[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        acc0[v] = S[(j0 + l16) * LD + i0 + M::row(lk, v)];
-        acc1[v] = S[(j1 + l16) * LD + i1 + M::row(lk, v)];
-      }
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int k = c0 + 4 * kk + lk;
-        a0[kk] = -S[k * LD + i0 + l16];
-        b0[kk] = S[(j0 + l16) * LD + k];
-        a1[kk] = -S[k * LD + i1 + l16];
-        b1[kk] = S[(j1 + l16) * LD + k];
-      }
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        acc0 = M::mma(a0[kk], b0[kk], acc0);
-        acc1 = M::mma(a1[kk], b1[kk], acc1);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        S[(j0 + l16) * LD + i0 + M::row(lk, v)] = acc0[v];
-        if (two) S[(j1 + l16) * LD + i1 + M::row(lk, v)] = acc1[v];
-      }
-    }
+    // step p on the column tile and the row tile of step p + 1
+    const int m = nt - 1 - p;
+    if (wave < 2 * m - 1)
+      update_tile(p, wave < m ? p + 1 + wave : p + 1, wave < m ? p + 1 : p + 2 + wave - m);
+    if (m == 0) break;
     __syncthreads();
-  }
-
-  {
-    const int rr = tid & (NB - 1), c0 = tid >> 7;
-#pragma unroll 16
-    for (int i = 0; i < NB * NB / NT; ++i) {
-      const int c = c0 + (NT / NB) * i;
-      if (rr < kb && c < kb) A[rr + int64_t(c) * lda] = T(S[c * LD + rr]);
+    if (wave < XW0) {
+      const C *q = S + c1 * LD + c1 + l16;
+#pragma unroll
+      for (int j = 0; j < PW; ++j) t[j] = q[j * LD];
+      if (wave < UW0) {
+        q = S + c1 * LD + last(below(p + 1));
+#pragma unroll
+        for (int j = 0; j < PW; ++j) x[j] = q[j * LD];
+      } else {
+        q = S + (PW * tile0(p + 1) + 4 * lk) * LD + c1 + l16;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          const C *qh = tile0(p + 1) + h < nt ? q + PW * h * LD : S;  // (not used beyond nt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[4 * h + j] = qh[j * LD];
+        }
+      }
+    } else {  // (no values to keep: without this the registers of both arrays stay taken)
+#pragma unroll
+      for (int j = 0; j < PW; ++j) __asm__("" : "=v"(t[j]), "=v"(x[j]));
     }
   }
+  for (int e = wave; e < 2 * PW; e += NW) store_half(PW * (nt - 1) + (e >> 1), e & 1);
 }
 
 }  // namespace
