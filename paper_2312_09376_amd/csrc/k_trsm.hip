@@ -17,12 +17,16 @@
 // strip, so the steps need no workgroup barrier (LDS accesses of one
 // wavefront complete in issue order). 140 KB of LDS: one workgroup per CU.
 //
-// Substitution inside a diagonal block: the 64 lanes hold 16 independent
-// right-hand sides x 4 lanes (a quad), lane q of a quad holding entries
-// q, q + 4, q + 8, q + 12. At pivot j the owner lane scales its entry and
-// a quad broadcast (DPP) hands it to the other three, which update their
-// entries. Every entry sees the same operations in the same order as in
-// one-lane-per-right-hand-side substitution.
+// Substitution inside a diagonal block: lane l16 of each group of 16 lanes
+// holds entry l16 of four right-hand sides, which is how the matrix-core
+// product leaves them, and its 16 coefficients in registers. At pivot j lane j
+// scales its entries and the update takes them as a DPP row broadcast inside
+// the multiply-add: no LDS access and no shuffle in the chain of 16 pivots.
+// Every entry sees the same operations in the same order as in
+// one-lane-per-right-hand-side substitution. (With four lanes per right-hand
+// side, their coefficients read from LDS a pivot ahead: both solves of a panel
+// step at n = 1000 18.2 us, now 17.7; the inverses of the diagonal blocks,
+// where no pivot scales, 16.6 and 14.5.)
 //
 // Left solves, op(T) X = B in place (B: kb x N):
 //   LN  T = L (unit lower)     forward  (panel U12 = L11^-1 A12, L y = b)
@@ -45,6 +49,7 @@
 // load and rounded once on store.
 #include "internal.h"
 #include "mma16.h"
+#include "row16.h"
 
 namespace rbt {
 
@@ -90,44 +95,20 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// In-place substitution with one 16 x 16 diagonal block, quad layout: the
-// calling lane holds x[jj] = entry q + 4 jj of its right-hand side; tq[j * 16
-// + jj] is the coefficient of pivot j for entry q + 4 jj (reciprocal for
-// j's own entry; zero where unused); pivots j >= bs are skipped. FWD: entries
-// after the pivot are updated, else entries before it.
-template <bool FWD, bool UNIT, typename C>
-__device__ __forceinline__ void quad_substitute(C (&x)[4], const C *tq, int q, int bs) {
-  C tn[4];
-  const int j0 = FWD ? 0 : IB - 1;
+// In-place substitution with one 16 x 16 diagonal block: x[v] = entry l16 of
+// four right-hand sides; m[j] = minus the coefficient of pivot j for entry l16,
+// zero where it has none; rd = the reciprocal of the lane's own pivot.
+template <bool FWD, bool UNIT, int S, typename C>
+__device__ __forceinline__ void substitute(C (&x)[4], const C (&m)[IB], C rd, int l16) {
+  if constexpr (S < IB) {
+    constexpr int J = FWD ? S : IB - 1 - S;
+    if constexpr (!UNIT) {
+      const C f = l16 == J ? rd : C(1);
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) tn[jj] = tq[j0 * IB + jj];
-#pragma unroll
-  for (int s = 0; s < IB; ++s) {
-    const int j = FWD ? s : IB - 1 - s;
-    const int jc = j >> 2, qc = j & 3;
-    C t[4];
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) t[jj] = tn[jj];
-    if (s + 1 < IB) {  // next pivot's coefficients in flight during this one
-      const int jn = FWD ? j + 1 : j - 1;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) tn[jj] = tq[jn * IB + jj];
+      for (int v = 0; v < 4; ++v) x[v] *= f;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    if (j < bs) {
-      if constexpr (!UNIT) {
-        const C xs = x[jc] * t[jc];
-        x[jc] = q == qc ? xs : x[jc];
-      }
-      const C b = quad_bcast(x[jc], qc);
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        if (FWD ? (4 * jj + 3 <= j) : (4 * jj >= j)) continue;  // no entry of jj on that side
-        const C nx = fma_c(-t[jj], b, x[jj]);
-        const bool all = FWD ? (4 * jj > j) : (4 * jj + 3 < j);
-        x[jj] = (all || (FWD ? q + 4 * jj > j : q + 4 * jj < j)) ? nx : x[jj];
-      }
-    }
+    fmac_rows<J, 4>(x, m[J]);
+    substitute<FWD, UNIT, S + 1>(x, m, rd, l16);
   }
 }
 
@@ -140,6 +121,7 @@ __device__ __forceinline__ void quad_substitute(C (&x)[4], const C *tq, int q, i
 template <typename C>
 struct TrsmSmem {
   __attribute__((aligned(16))) C dblk[NBK * BLK];
+  C drec[NB];  // reciprocals of the diagonal
   __attribute__((aligned(16))) C oblk[NOFF * BLK];
   __attribute__((aligned(16))) C strip[4][NB * SLD];
 };
@@ -160,9 +142,8 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
     T += r0 + r0 * ldt;
     B += b * bstride;
   }
-  // dblk: op(T)(i, j) of diagonal block b at b*256 + j*16 + (i%4)*4 + i/4
-  // (reciprocal on the diagonal of non-unit modes); ablk: off-diagonal block
-  // (I, J), J before I, at p*256 + lane*4 + kk = op(T)(16I + l16, 16J + 4kk +
+  // dblk: -op(T)(i, j) of diagonal block b at b*256 + j*16 + i where pivot j
+  // updates entry i, else zero; ablk: off-diagonal block (I, J), J before I, at p*256 + lane*4 + kk = op(T)(16I + l16, 16J + 4kk +
   // lk), p = I(I-1)/2 + J (forward) or J(J-1)/2 + I (backward)
   C *dblk = sm.dblk;
   C *ablk = sm.oblk;
@@ -184,9 +165,9 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
 #pragma unroll
     for (int b = 0; b < NBK; ++b) {
       const int gi = IB * b + i, gj = IB * b + j;
-      C v = (gi < kb && gj < kb) ? C(raw[b]) : (i == j ? C(1) : C(0));
-      if (!unit_diag<MODE>() && i == j) v = C(1) / v;
-      dblk[b * BLK + j * IB + (i & 3) * 4 + (i >> 2)] = v;
+      const C v = (gi < kb && gj < kb) ? C(raw[b]) : (i == j ? C(1) : C(0));
+      if (!unit_diag<MODE>() && i == j) sm.drec[gi] = C(1) / v;
+      dblk[b * BLK + j * IB + i] = (FWD ? i > j : i < j) ? -v : C(0);
     }
     TT oraw[NOFF];
 #pragma unroll
@@ -232,9 +213,16 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
   __syncthreads();
 
   const int nbk = (kb + IB - 1) / IB;
-  const int cc = lane >> 2, q = lane & 3;  // substitution: right-hand side cc, entries q + 4 jj
   for (int step = 0; step < nbk; ++step) {
     const int I = FWD ? step : nbk - 1 - step;
+    C m[IB], x[4];
+#pragma unroll
+    for (int j = 0; j < IB; ++j) m[j] = dblk[I * BLK + j * IB + l16];
+    const C rd = unit_diag<MODE>() ? C(1) : sm.drec[IB * I + l16];
+    C *xs = strip + (IB * I + l16) * SLD + M::row(lk, 0);
+    constexpr int RS = M::row(0, 1);  // right-hand sides between the lane's entries
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = xs[RS * v];
     c4 acc0 = {C(0), C(0), C(0), C(0)}, acc1 = {C(0), C(0), C(0), C(0)};
 #pragma unroll
     for (int s2 = 0; s2 < NBK - 1; ++s2) {
@@ -244,24 +232,18 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
         const c2 a01 = *reinterpret_cast<const c2 *>(ablk + p * BLK + lane * 4);
         const c2 a23 = *reinterpret_cast<const c2 *>(ablk + p * BLK + lane * 4 + 2);
         const int k0 = IB * J + lk;
-        acc0 = M::mma(a01[0], strip[(k0) * SLD + l16], acc0);
-        acc1 = M::mma(a01[1], strip[(k0 + 4) * SLD + l16], acc1);
-        acc0 = M::mma(a23[0], strip[(k0 + 8) * SLD + l16], acc0);
-        acc1 = M::mma(a23[1], strip[(k0 + 12) * SLD + l16], acc1);
+        // (right-hand sides x entries: the lane's column is its entry)
+        acc0 = M::mma(strip[(k0) * SLD + l16], a01[0], acc0);
+        acc1 = M::mma(strip[(k0 + 4) * SLD + l16], a01[1], acc1);
+        acc0 = M::mma(strip[(k0 + 8) * SLD + l16], a23[0], acc0);
+        acc1 = M::mma(strip[(k0 + 12) * SLD + l16], a23[1], acc1);
       }
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) strip[(IB * I + M::row(lk, v)) * SLD + l16] -= acc0[v] + acc1[v];
-    wave_sync();
-    const int bs = kb - IB * I < IB ? kb - IB * I : IB;
-    const int o = IB * I;
-    C x[4];
+    for (int v = 0; v < 4; ++v) x[v] -= acc0[v] + acc1[v];
+    substitute<FWD, unit_diag<MODE>(), 0>(x, m, rd, l16);
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) x[jj] = strip[(o + q + 4 * jj) * SLD + cc];
-    quad_substitute<FWD, unit_diag<MODE>()>(x, dblk + I * BLK + q * 4, q, bs);
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      strip[(o + q + 4 * jj) * SLD + cc] = (q + 4 * jj < bs) ? x[jj] : C(0);
+    for (int v = 0; v < 4; ++v) xs[RS * v] = IB * I + l16 < kb ? x[v] : C(0);
     wave_sync();
   }
 
@@ -293,8 +275,8 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
   typedef Mma16<C> Mm;
   typedef typename Mm::v4 c4;
   typedef C c2 __attribute__((ext_vector_type(2)));
-  // dblk: U(r, c) of diagonal block b at b*256 + r*16 + (c%4)*4 + c/4
-  // (reciprocal on the diagonal); ublk: block (I, J), I < J, at p*256 +
+  // dblk: -U(r, c) of diagonal block b at b*256 + r*16 + c for r < c, else
+  // zero; ublk: block (I, J), I < J, at p*256 +
   // lane*4 + kk = U(16I + 4kk + lk, 16J + l16), p = J(J-1)/2 + I
   C *dblk = sm.dblk;
   C *ublk = sm.oblk;
@@ -312,9 +294,9 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
 #pragma unroll
     for (int b = 0; b < NBK; ++b) {
       const int gi = IB * b + r, gj = IB * b + c;
-      C v = (gi < kb && gj < kb) ? C(raw[b]) : (r == c ? C(1) : C(0));
-      if (r == c) v = C(1) / v;
-      dblk[b * BLK + r * IB + (c & 3) * 4 + (c >> 2)] = v;
+      const C v = (gi < kb && gj < kb) ? C(raw[b]) : (r == c ? C(1) : C(0));
+      if (r == c) sm.drec[gi] = C(1) / v;
+      dblk[b * BLK + r * IB + c] = r < c ? -v : C(0);
     }
     TT uraw[NOFF];
 #pragma unroll
@@ -352,8 +334,15 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
   __syncthreads();
 
   const int nbk = (kb + IB - 1) / IB;
-  const int rq = lane >> 2, q = lane & 3;  // substitution: row rq, entries q + 4 jj
   for (int J = 0; J < nbk; ++J) {
+    C m[IB], x[4];
+#pragma unroll
+    for (int j = 0; j < IB; ++j) m[j] = dblk[J * BLK + j * IB + l16];
+    const C rd = sm.drec[IB * J + l16];
+    C *xs = strip + (IB * J + l16) * SLD + Mm::row(lk, 0);
+    constexpr int RS = Mm::row(0, 1);  // rows between the lane's entries
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = xs[RS * v];
     c4 acc0 = {C(0), C(0), C(0), C(0)}, acc1 = {C(0), C(0), C(0), C(0)};
 #pragma unroll
     for (int I = 0; I < NBK - 1; ++I) {
@@ -369,17 +358,10 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
       }
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) strip[(IB * J + l16) * SLD + Mm::row(lk, v)] -= acc0[v] + acc1[v];
-    wave_sync();
-    const int bs = kb - IB * J < IB ? kb - IB * J : IB;
-    const int o = IB * J;
-    C x[4];
+    for (int v = 0; v < 4; ++v) x[v] -= acc0[v] + acc1[v];
+    substitute<true, false, 0>(x, m, rd, l16);
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) x[jj] = strip[(o + q + 4 * jj) * SLD + rq];
-    quad_substitute<true, false>(x, dblk + J * BLK + q * 4, q, bs);
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      strip[(o + q + 4 * jj) * SLD + rq] = (q + 4 * jj < bs) ? x[jj] : C(0);
+    for (int v = 0; v < 4; ++v) xs[RS * v] = IB * J + l16 < kb ? x[v] : C(0);
     wave_sync();
   }
 

@@ -59,16 +59,6 @@ __device__ __forceinline__ float quad_bcast_k(float v) {
   return __int_as_float(
       __builtin_amdgcn_update_dpp(0, __float_as_int(v), K * 0x55, 0xF, 0xF, false));
 }
-template <typename C>
-__device__ __forceinline__ C quad_bcast(C v, int k) {  // k: compile-time after unrolling
-  switch (k) {
-    case 0: return quad_bcast_k<0>(v);
-    case 1: return quad_bcast_k<1>(v);
-    case 2: return quad_bcast_k<2>(v);
-    default: return quad_bcast_k<3>(v);
-  }
-}
-
 __device__ __forceinline__ double fma_c(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_c(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
