@@ -1,4 +1,4 @@
-// Triangular sweeps for few right-hand sides (groups of 16) as ONE persistent
+// Triangular sweeps for few right-hand sides (groups of 4 to 16) as ONE persistent
 // launch per sweep, for the solves after the elimination (Sec. 1, step 3:
 // L y = b~, U x~ = y) and the adjoint solves.
 //
@@ -38,24 +38,24 @@
 // one barrier. One right-hand side: a row belongs to a quad of lanes, 32
 // columns each, summed over the quad by DPP. More: the matrix cores, a lane
 // holding row l % 16 and every fourth group of columns of the block
-// (16x16x4 products for 9 to 16 right-hand sides and in FP32; in FP64 up to
-// 8 the 4x4x4 product on four row groups, whose cost goes with the
-// right-hand sides: 16 cycles per four of them against 64 for sixteen). With
+// (16x16x4 products for groups of 16; for groups of 4 and 8 the 4x4x4 FP64 and
+// 4x4x1 FP32 products on four row groups, whose cost goes with the right-hand
+// sides: 16 and 8 cycles per four of them against 64 and 32 for sixteen). With
 // lanes on 128 rows x 4 segments, FMA loops over x in LDS and a sum over the
 // segments through LDS after each product, the step from block to block was
 // LDS-bound for several right-hand sides. Microseconds per block then and now
-// (FP64, n = 4096, not transposed / transposed): 16 right-hand sides 43 / 48 and
-// 12.6, 8 of them 14.9 / 19.6 and 7.4, 4 of them 9.0 / 13.7 and 4.2 / 4.9, one 5.2 / 7.9
-// and 3.2 / 3.4 (n = 20000: 5.8 / 10.0 and 4.0).
+// (FP64, n = 4096, not transposed / transposed): a group of 16 right-hand sides
+// 43 / 48 and 12.6, of 8 of them 14.9 / 19.6 and 7.4, of 4 of them 9.0 / 13.7 and
+// 4.2 / 4.9, one 5.2 / 7.9 and 3.2 / 3.4 (n = 20000: 5.8 / 10.0 and 4.0).
 //
 // Columns of a block are dealt to the lanes of a row in pairs (FP64; groups
 // of four in FP32): step q = qq V + h takes column qq 4 V + sl V + h in lane
 // group sl, so that the transposed modes, where a row is contiguous, read
 // 64-byte runs with 16-byte loads.
 //
-// More than 16 right-hand sides are groups of 16 in the same launch, their
-// tickets interleaved: the groups run side by side, each on its own chain,
-// and share the blocks through the caches.
+// More right-hand sides than a group takes are several groups in the same
+// launch, their tickets interleaved: the groups run side by side, each on its
+// own chain, and share the blocks through the caches. group_width() chooses.
 //
 // Arithmetic type C: FP64 for FP64 factors. For the FP32 factors of the
 // mixed-precision solve it is FP32: the right-hand side (FP64 storage, the
@@ -230,6 +230,48 @@ struct Prod4 {
     }
   }
 };
+// Sums over the lanes l, l + 16, l + 32, l + 48 of four values, value l / 16 to
+// lane l: each swap leaves one half (the even rows) of two values in the first
+// result and the other in the second.
+__device__ __forceinline__ float sum_and_scatter(float v0, float v1, float v2, float v3) {
+  auto bits = [](float v) { return unsigned(__float_as_int(v)); };
+  auto sum = [](auto r) { return __int_as_float(int(r[0])) + __int_as_float(int(r[1])); };
+  const float s0 = sum(__builtin_amdgcn_permlane32_swap(bits(v0), bits(v2), false, false));
+  const float s1 = sum(__builtin_amdgcn_permlane32_swap(bits(v1), bits(v3), false, false));
+  return sum(__builtin_amdgcn_permlane16_swap(bits(s0), bits(s1), false, false));
+}
+
+// FP32 matrix cores, 4 x 4 x 1 on 16 blocks: four row blocks times four groups
+// of columns of the block. Lane l supplies A[row l % 16] and B[column l % 4] of
+// the group l / 16; its four results are rows 4 ((l / 4) % 4) + v of the group's
+// partial sum, added over the groups at the end (row l / 16 of the four).
+template <bool TRANS>
+struct Prod<4, TRANS, float> {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  static constexpr int NV = 1, XN = 5;
+  static __device__ __forceinline__ int rl(int lane) { return lane & 15; }
+  static __device__ __forceinline__ int sl(int lane) { return lane >> 4; }
+  static __device__ __forceinline__ int row(int lane, int) {
+    return 4 * ((lane >> 2) & 3) + (lane >> 4);
+  }
+  static __device__ __forceinline__ int col(int lane, int) { return lane & 3; }
+  static __device__ __forceinline__ bool owns(int) { return true; }
+  template <int V>
+  static __device__ __forceinline__ int slot(int k) {
+    return 4 * ((k / (4 * V)) * V + k % V) + (k / V) % 4;
+  }
+  template <int V>
+  static __device__ __forceinline__ void mul(const float (&e)[STEPS], const float *xs, int lane,
+                                             float (&out)[NV]) {
+    const float *x = xs + (lane >> 4) * XN + (lane & 3);
+    v4 a[4] = {};
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q)
+      a[q & 3] = __builtin_amdgcn_mfma_f32_4x4x1f32(e[q], x[4 * q * XN], a[q & 3], 0, 0, 0);
+    const v4 t = (a[0] + a[1]) + (a[2] + a[3]);
+    out[0] = sum_and_scatter(t[0], t[1], t[2], t[3]);
+  }
+};
 template <bool TRANS>
 struct Prod<4, TRANS, double> : Prod4<4> {};
 template <bool TRANS>
@@ -278,7 +320,7 @@ template <int NT, TriMode MODE, typename TF, bool REFINE, typename C>
 __global__ void __launch_bounds__(TPB)
     k_sweep(int64_t n, int64_t nrhs, const TF *__restrict__ A, int64_t ld,
             const C *__restrict__ Winv, double *B, int64_t ldb, int32_t *sync, double *P,
-            int64_t nb, int groups, int64_t spin_limit, const int32_t *gate) {
+            int64_t nb, int groups, int width, int64_t spin_limit, const int32_t *gate) {
   // (the gate is read before any ticket is taken: every workgroup of a gated
   // launch returns here)
   if (gated(gate)) return;
@@ -305,10 +347,10 @@ __global__ void __launch_bounds__(TPB)
   const int64_t ticket = __builtin_amdgcn_readfirstlane(tk);  // (block indices in scalar registers)
   if (ticket >= nb * groups) return;
   const int64_t t = ticket / groups;
-  const int64_t c16 = (ticket - t * groups) * kSkinnyMax;  // the group's first right-hand side
-  const int N = int(nrhs - c16 < kSkinnyMax ? nrhs - c16 : kSkinnyMax);
-  B += c16 * ldb;
-  double *pub = P + c16 * n;  // entry (row, c) of the group at pub[row N + c]
+  const int64_t g0 = (ticket - t * groups) * width;  // the group's first right-hand side
+  const int N = int(nrhs - g0 < width ? nrhs - g0 : width);
+  B += g0 * ldb;
+  double *pub = P + g0 * n;  // entry (row, c) of the group at pub[row N + c]
   int32_t *err = sync + kSweepErrWord;  // sticky: cleared by the entry points, not per sweep
   const int64_t b = FWD ? t : nb - 1 - t;
   const int64_t r0 = b * kNB;
@@ -487,7 +529,8 @@ hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *W
   // kappa(block) u32 only); FP64 arithmetic on FP32 factors needs none
   constexpr bool REFINE = std::is_same<TF, double>::value || std::is_same<C, float>::value;
   const int64_t nb = (n + kNB - 1) / kNB;
-  const int64_t groups = (nrhs + kSkinnyMax - 1) / kSkinnyMax;
+  const int64_t width = nrhs < NT ? nrhs : NT;  // right-hand sides per group
+  const int64_t groups = (nrhs + width - 1) / width;
   if (nb * groups > 0x7fffffff) return hipErrorInvalidValue;
   // ticket and legacy words, and P; the sticky error word sync[3] is left alone
   const int64_t count = n * nrhs;
@@ -496,7 +539,7 @@ hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *W
                      P, count);
   hipLaunchKernelGGL((k_sweep<NT, MODE, TF, REFINE, C>), dim3(unsigned(nb * groups)), dim3(TPB), 0,
                      s, n, nrhs, LU, ld, Winv, B, ldb, sync, P, nb, int(groups),
-                     sweep_spin_limit(), refine_gate());
+                     int(width), sweep_spin_limit(), refine_gate());
   return hipGetLastError();
 }
 
@@ -511,6 +554,36 @@ hipError_t sweep_n(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t 
   }
 }
 
+// Right-hand sides per group (4, 8 or 16; FP32 arithmetic: 4 or 16). Narrow
+// groups have short chains (microseconds per block below, measured at n = 5003 to
+// 12000), and each group reads the factors once, at about 7.5 TB/s where many
+// groups stream them through the caches. Both directions of one FP64 solve in ms with
+// groups of 4 / 8 / 16: n = 1000, 16 right-hand sides 0.12 / 0.16 / 0.24; n = 5003, 64 of
+// them 0.61 / 0.80 / 1.07 and 384 of them 2.01 / 1.60 / 1.35; n = 20000, 8 of them 2.25 / 2.62
+// (one group), 32 of them 3.72 / 3.65 / 5.09 and 128 of them 12.4 / 7.9 / 5.9. FP32 at
+// n = 8191, 8 right-hand sides: a sweep of two groups of 4 0.23, of one of 16 0.42.
+template <typename TF, typename C>
+int group_width(int64_t n, int64_t nrhs) {
+  constexpr bool F32 = std::is_same<C, float>::value;
+  constexpr bool REFINE = std::is_same<TF, double>::value || F32;
+  const double chain[3] = {F32 ? 3.7 : (REFINE ? 4.7 : 3.0), REFINE ? 7.9 : 4.4,
+                           F32 ? 6.6 : (REFINE ? 13.2 : 7.4)};
+  const double blocks = double((n + kNB - 1) / kNB);
+  const double read = double(n) * double(n) * sizeof(TF) / 2 / 7.5e6;
+  int best = 4;
+  double least = 0.0;
+  for (int k = 0; k < 3; ++k) {
+    const int w = 4 << k;
+    if (w == 8 && F32) continue;
+    const double cost = blocks * chain[k] + double((nrhs + w - 1) / w) * read;
+    if (k == 0 || cost < least) {
+      best = w;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 template <typename TF, typename C>
 hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t ld,
                      const C *Winv, double *B, int64_t ldb, int32_t *sync, double *P,
@@ -522,11 +595,14 @@ hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_
     P = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
   }
   if (nrhs == 1) return sweep_n<1>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
-  if constexpr (std::is_same<C, double>::value) {
-    if (nrhs <= 4) return sweep_n<4>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
-    if (nrhs <= 8) return sweep_n<8>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+  switch (group_width<TF, C>(n, nrhs)) {
+    case 4: return sweep_n<4>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    case 8:
+      if constexpr (std::is_same<C, double>::value)
+        return sweep_n<8>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+      [[fallthrough]];
+    default: return sweep_n<16>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
   }
-  return sweep_n<16>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
 }
 
 }  // namespace

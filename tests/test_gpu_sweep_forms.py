@@ -1,6 +1,6 @@
 """The triangular sweeps in every form the dispatch can choose: one
-right-hand side, 4, 8 and 16 per matrix-core group, several groups side by
-side (17 and more), the block solves beyond 384, both transposes, orders
+right-hand side, groups of 4, 8 and 16 (by order and number of right-hand
+sides), several groups side by side, the last of them ragged, the block solves beyond 384, both transposes, orders
 around one and two blocks, a leading dimension above n, and a workspace with
 no room for more than one group. FP64 factors: against the oracle's
 triangular solves. FP32 factors: the refined solution and adjoint."""
@@ -57,6 +57,24 @@ def test_getrs_forms(rbt, n, k, trans):
     assert relfro(host(X), expected(LUo, B, trans)) <= 1e-12
 
 
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("n,k", [(2049, 383), (4200, 375)])
+def test_wide_groups(rbt, n, k, trans):
+    """Groups of 8 and of 16: the residual within the bound of two triangular
+    solves, 2 n eps |L| |U| |X| (the product for the residual adds as much)."""
+    A = workloads.device_shifted(n, 1)
+    LU, _ = rbt.genp(A)
+    B = workloads.device_randn(n, k, 2)
+    X = rbt.getrs(LU, B.clone(), trans=trans)
+    L = torch.tril(LU, -1) + torch.eye(n, dtype=LU.dtype, device="cuda")
+    U = torch.triu(LU)
+    if trans:
+        L, U = U.t().contiguous(), L.t().contiguous()
+    R = (B - L @ (U @ X)).abs()
+    bound = 4 * n * EPS * (L.abs() @ (U.abs() @ X.abs()))
+    assert bool((R <= bound).all())
+
+
 @pytest.mark.parametrize("k", [16, 40])
 def test_getrs_workspace_without_publication_buffer(rbt, k):
     """A workspace that ends with the sweeps' area (smaller than
@@ -72,7 +90,7 @@ def test_getrs_workspace_without_publication_buffer(rbt, k):
     assert relfro(host(X), expected(LUo, B, 0)) <= 1e-12
 
 
-@pytest.mark.parametrize("n,k", [(129, 1), (257, 3), (300, 16), (515, 17), (260, 40)])
+@pytest.mark.parametrize("n,k", [(129, 1), (257, 3), (300, 16), (515, 17), (260, 40), (1100, 383)])
 def test_mixed_forms(rbt, n, k):
     A = workloads.dominant(n, seed=n)
     B = workloads.randn(n, k, seed=4)
