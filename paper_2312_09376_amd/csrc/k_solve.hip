@@ -3,10 +3,10 @@
 // Eq. 7, the column updates of iterative refinement (Sec. 5) and the
 // outer product of the adjoint.
 //
-// These are HBM-bound (one read of the matrix, a few columns of output), so
-// they run as plain FMA kernels with lanes along rows (coalesced column
-// runs of the column-major matrix) and the small right-hand-side block in
-// LDS; the matrix-core GEMM is kept for wide right-hand sides.
+// These are HBM-bound (one read of the matrix, a few columns of output). The
+// products with the matrix run on the matrix cores (k_rows_product), so that
+// up to 16 right-hand sides cost about what one does; the GEMM is kept for
+// many right-hand sides.
 #include "internal.h"
 
 namespace rbt {
@@ -15,58 +15,6 @@ namespace {
 
 constexpr int kRows = 256;       // rows per workgroup
 constexpr int64_t kChunk = 256;  // columns per split-K chunk of the residual
-
-// partial[(c N + n) M + m] = sum_{k in chunk c} A[m, k] X[k, n];
-// ABS: abspart[c M + m] = sum_{k in chunk c} |A[m, k]|.
-template <int NMAX, bool ABS>
-__global__ void __launch_bounds__(kRows) k_gemv_partial(int64_t M, int N, int64_t K,
-                                                        const double *__restrict__ A,
-                                                        int64_t lda,
-                                                        const double *__restrict__ X,
-                                                        int64_t ldx,
-                                                        double *__restrict__ partial,
-                                                        double *__restrict__ abspart,
-                                                        const int32_t *gate) {
-  if (gated(gate)) return;
-  __shared__ double xs[kChunk][NMAX];
-  const int64_t c = blockIdx.y;
-  const int64_t k0 = c * kChunk;
-  const int kc = int((K - k0) < kChunk ? (K - k0) : kChunk);
-  for (int idx = threadIdx.x; idx < kc * NMAX; idx += kRows) {
-    const int k = idx / NMAX, n = idx % NMAX;
-    xs[k][n] = n < N ? X[(k0 + k) + int64_t(n) * ldx] : 0.0;
-  }
-  __syncthreads();
-  const int64_t m = int64_t(blockIdx.x) * kRows + threadIdx.x;
-  if (m >= M) return;
-  double acc[NMAX];
-#pragma unroll
-  for (int n = 0; n < NMAX; ++n) acc[n] = 0.0;
-  double s0 = 0.0, s1 = 0.0;
-  const double *Ap = A + m + k0 * lda;
-  int k = 0;
-#pragma unroll 4
-  for (; k + 2 <= kc; k += 2) {
-    const double a0 = Ap[int64_t(k) * lda];
-    const double a1 = Ap[int64_t(k + 1) * lda];
-#pragma unroll
-    for (int n = 0; n < NMAX; ++n) acc[n] += a0 * xs[k][n] + a1 * xs[k + 1][n];
-    if (ABS) {
-      s0 += fabs(a0);
-      s1 += fabs(a1);
-    }
-  }
-  for (; k < kc; ++k) {
-    const double a0 = Ap[int64_t(k) * lda];
-#pragma unroll
-    for (int n = 0; n < NMAX; ++n) acc[n] += a0 * xs[k][n];
-    if (ABS) s0 += fabs(a0);
-  }
-#pragma unroll
-  for (int n = 0; n < NMAX; ++n)
-    if (n < N) partial[(c * N + n) * M + m] = acc[n];
-  if (ABS) abspart[c * M + m] = s0 + s1;
-}
 
 __device__ __forceinline__ double nanmax(double a, double b) {
   // NaN-propagating maximum: a NaN residual must never look converged
@@ -86,81 +34,224 @@ __device__ double block_nanmax(double v, double *sh) {
   return r;
 }
 
-// R = B - sum_c partial; per workgroup: max_m |R[:, n]|, |X[:, n]|, |B[:, n]|
-// and (ABS) max_m sum_c abspart = a block maximum of the row sums of |A|.
-// blockstat[(blk * (3 NMAX + 1)) + ...] layout: [3 n + 0..2] per column, then anorm.
-template <int NMAX, bool ABS>
-__global__ void __launch_bounds__(kRows) k_resid_reduce(
-    int64_t M, int N, int64_t chunks, const double *__restrict__ partial,
-    const double *__restrict__ abspart, const double *__restrict__ Bm, int64_t ldb,
-    const double *__restrict__ X, int64_t ldx, double *__restrict__ R, int64_t ldr,
-    double *__restrict__ blockstat, const int32_t *gate) {
+// O = G - op(A) X (G null: op(A) X) for op(A) = A or A^T (n x n) on the FP64
+// matrix cores, in one pass over A. A workgroup forms 16 RT rows and 16 CT
+// right-hand sides; its eight wavefronts take every eighth run of 32 columns
+// of op(A), the next run's loads in flight, and their sums are added through LDS
+// in a fixed order. Also per workgroup, for up to 16 right-hand sides:
+// blockstat[blk (3 N + 1) + 3 c + 0..2] = max |O|, |X|, |G| over its rows, and
+// (ABS) entry 3 N of it, or blockstat[blk] for more right-hand sides, the
+// maximum over its rows of the row sums of |op(A)|.
+// Bound by reading A once for up to 16 right-hand sides (n = 8191: 110 to 114 us,
+// 4.8 TB/s, a copy's rate being 5.3) and by the matrix cores and the readings of
+// X for more. With 8 right-hand sides at n = 8191 the product as partial sums over
+// chunks of 256 columns and their sum by a second kernel, one workgroup per 256
+// rows, took 111 and 95 us, the transposed one from LDS 357; with 64 at n = 5003 a
+// GEMM of 79 tiles of 64 x 64 took 392 us, this 216.
+constexpr int kRunK = 32;    // columns of op(A) per run of a wavefront
+constexpr int kWaves = 8;
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+template <bool TRANS, int RT, int CT, bool ABS>
+__global__ void __launch_bounds__(64 * kWaves)
+    k_rows_product(int64_t n, int nrhs, const double *__restrict__ A, int64_t lda,
+                   const double *__restrict__ X, int64_t ldx, const double *__restrict__ G,
+                   int64_t ldg, double *__restrict__ O, int64_t ldo,
+                   double *__restrict__ blockstat, const int32_t *gate) {
   if (gated(gate)) return;
-  __shared__ double sh[kRows];
-  const int64_t m = int64_t(blockIdx.x) * kRows + threadIdx.x;
-  const bool ok = m < M;
-  double *bs = blockstat + int64_t(blockIdx.x) * (3 * NMAX + 1);
-  for (int n = 0; n < N; ++n) {
-    double r = 0.0, xv = 0.0, bv = 0.0;
-    if (ok) {
-      double s = 0.0;
-      for (int64_t c = 0; c < chunks; ++c) s += partial[(c * N + n) * M + m];
-      bv = Bm[m + int64_t(n) * ldb];
-      r = bv - s;
-      R[m + int64_t(n) * ldr] = r;
-      xv = X[m + int64_t(n) * ldx];
+  __shared__ double red[kWaves][RT][CT][4][64];
+  __shared__ double absred[ABS ? kWaves : 1][RT][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int64_t m0 = int64_t(blockIdx.x) * (16 * RT);
+  const int c0 = int(blockIdx.y) * (16 * CT);
+  // operand rows and right-hand sides beyond the last repeat it (not stored)
+  const double *ap[RT], *xp[CT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int64_t m = m0 + 16 * i + l16 < n ? m0 + 16 * i + l16 : n - 1;
+    ap[i] = TRANS ? A + m * lda : A + m;
+  }
+#pragma unroll
+  for (int t = 0; t < CT; ++t) {
+    const int c = c0 + 16 * t + l16 < nrhs ? c0 + 16 * t + l16 : nrhs - 1;
+    xp[t] = X + int64_t(c) * ldx;
+  }
+  // the lane's columns of a run: k0 + 8 q + 2 lk + {0, 1}, q = 0..3
+  double a[RT][8], x[CT][8], an[RT][8], xn[CT][8];
+  auto load = [&](int64_t k0, double (&av)[RT][8], double (&xv)[CT][8]) {
+    if (k0 + kRunK <= n) {
+      const int64_t k = k0 + 2 * lk;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          if constexpr (TRANS) {
+            const d2u v = *reinterpret_cast<const d2u *>(ap[i] + k + 8 * q);
+            av[i][2 * q] = v[0];
+            av[i][2 * q + 1] = v[1];
+          } else {
+            av[i][2 * q] = ap[i][(k + 8 * q) * lda];
+            av[i][2 * q + 1] = ap[i][(k + 8 * q + 1) * lda];
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const d2u v = *reinterpret_cast<const d2u *>(xp[t] + k + 8 * q);
+          xv[t][2 * q] = v[0];
+          xv[t][2 * q + 1] = v[1];
+        }
+      }
+    } else {  // the last, partial run: clamped loads, zero beyond
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t k = k0 + 8 * (e >> 1) + 2 * lk + (e & 1);
+        const int64_t kc = k < n ? k : n - 1;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          const double v = TRANS ? ap[i][kc] : ap[i][kc * lda];
+          av[i][e] = k < n ? v : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const double v = xp[t][kc];
+          xv[t][e] = k < n ? v : 0.0;
+        }
+      }
     }
-    const double mr = block_nanmax(fabs(r), sh);
-    const double mx = block_nanmax(fabs(xv), sh);
-    const double mb = block_nanmax(fabs(bv), sh);
-    if (threadIdx.x == 0) {
-      bs[3 * n] = mr;
-      bs[3 * n + 1] = mx;
-      bs[3 * n + 2] = mb;
+  };
+  d4 acc[RT][CT];
+  double as[RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    as[i] = 0.0;
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[i][t] = d4{0.0, 0.0, 0.0, 0.0};
+  }
+  int64_t k0 = int64_t(wave) * kRunK;
+  if (k0 < n) load(k0, a, x);
+  while (k0 < n) {
+    const int64_t kn = k0 + kWaves * kRunK;
+    if (kn < n) load(kn, an, xn);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        if constexpr (ABS) as[i] += fabs(a[i][e]);
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+          acc[i][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][e], x[t][e], acc[i][t], 0, 0, 0);
+      }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) a[i][e] = an[i][e];
+#pragma unroll
+      for (int t = 0; t < CT; ++t) x[t][e] = xn[t][e];
+    }
+    k0 = kn;
+  }
+  // acc[i][t][v]: row 16 i + lk + 4 v, right-hand side 16 t + l16
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][i][t][v][lane] = acc[i][t][v];
+    if constexpr (ABS) absred[wave][i][lane] = as[i];
+  }
+  __syncthreads();
+  constexpr int ROWS = 16 * RT;  // rows of a right-hand side stand in consecutive lanes
+  const bool stats = nrhs <= kSkinnyMax;
+  double *bs = blockstat + int64_t(blockIdx.x) * (stats ? 3 * nrhs + 1 : 1);
+  for (int e = tid; e < ROWS * 16 * CT; e += 64 * kWaves) {
+    const int r = e % ROWS, c = e / ROWS, i = r >> 4, t = c >> 4;
+    const int src = (r & 3) * 16 + (c & 15), v = (r & 15) >> 2;
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += red[w][i][t][v][src];
+    const int64_t m = m0 + r;
+    const int col = c0 + c;
+    double o = 0.0, xv = 0.0, g = 0.0;
+    if (m < n && col < nrhs) {
+      if (G != nullptr) {
+        g = G[m + int64_t(col) * ldg];
+        o = g - sum;
+        xv = X[m + int64_t(col) * ldx];
+      } else {
+        o = sum;
+      }
+      O[m + int64_t(col) * ldo] = o;
+    }
+    if (stats && G != nullptr) {
+      o = fabs(o);
+      xv = fabs(xv);
+      g = fabs(g);
+#pragma unroll
+      for (int d = 1; d < ROWS; d <<= 1) {
+        o = nanmax(o, __shfl_xor(o, d));
+        xv = nanmax(xv, __shfl_xor(xv, d));
+        g = nanmax(g, __shfl_xor(g, d));
+      }
+      if (r == 0 && col < nrhs) {
+        bs[3 * col] = o;
+        bs[3 * col + 1] = xv;
+        bs[3 * col + 2] = g;
+      }
     }
   }
-  if (ABS) {
-    double s = 0.0;
-    if (ok)
-      for (int64_t c = 0; c < chunks; ++c) s += abspart[c * M + m];
-    const double ma = block_nanmax(s, sh);
-    if (threadIdx.x == 0) bs[3 * NMAX] = ma;
+  if constexpr (ABS) {
+    if (blockIdx.y == 0 && wave == 0) {
+      double sum = 0.0;
+      if (lane < ROWS && m0 + lane < n)
+        for (int w = 0; w < kWaves; ++w)
+          for (int h = 0; h < 4; ++h) sum += absred[w][lane >> 4][16 * h + (lane & 15)];
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) sum = nanmax(sum, __shfl_xor(sum, d));
+      if (lane == 0) bs[stats ? 3 * nrhs : 0] = sum;
+    }
   }
 }
 
-// Final reduction over workgroups: anorm (if ABS) and the backward error.
-template <int NMAX, bool ABS>
-__global__ void __launch_bounds__(kRows) k_berr_blocks(int64_t nblk, int N,
-                                                       const double *__restrict__ blockstat,
-                                                       double *__restrict__ anorm,
-                                                       double *__restrict__ berr,
-                                                       const int32_t *gate) {
+// Final reduction over the workgroups of k_rows_product, N <= 16 right-hand
+// sides: anorm (ABS) and the backward error of Eq. 7. A wavefront takes every
+// fourth right-hand side.
+template <bool ABS>
+__global__ void __launch_bounds__(kRows) k_berr_rows(int64_t nblk, int N,
+                                                     const double *__restrict__ blockstat,
+                                                     double *__restrict__ anorm,
+                                                     double *__restrict__ berr,
+                                                     const int32_t *gate) {
   if (gated(gate)) return;
-  __shared__ double sh[kRows];
-  const int stride = 3 * NMAX + 1;
-  double a;
-  if (ABS) {
+  __shared__ double sh[kRows / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int stride = 3 * N + 1;
+  auto column = [&](int e) {  // maximum of entry e over the blocks, in every lane
     double v = 0.0;
-    for (int64_t b = threadIdx.x; b < nblk; b += kRows) v = nanmax(v, blockstat[b * stride + 3 * NMAX]);
-    a = block_nanmax(v, sh);
-    if (threadIdx.x == 0) anorm[0] = a;
+    for (int64_t b = lane; b < nblk; b += 64) v = nanmax(v, blockstat[b * stride + e]);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) v = nanmax(v, __shfl_xor(v, d));
+    return v;
+  };
+  double an;
+  if (ABS) {
+    an = column(3 * N);
+    if (threadIdx.x == 0) anorm[0] = an;
   } else {
-    a = anorm[0];
+    an = anorm[0];
   }
   double be = 0.0;
-  for (int n = 0; n < N; ++n) {
-    double r = 0.0, x = 0.0, bb = 0.0;
-    for (int64_t b = threadIdx.x; b < nblk; b += kRows) {
-      r = nanmax(r, blockstat[b * stride + 3 * n]);
-      x = nanmax(x, blockstat[b * stride + 3 * n + 1]);
-      bb = nanmax(bb, blockstat[b * stride + 3 * n + 2]);
-    }
-    r = block_nanmax(r, sh);
-    x = block_nanmax(x, sh);
-    bb = block_nanmax(bb, sh);
-    be = nanmax(be, r / (a * x + bb));
+  for (int c = wave; c < N; c += kRows / 64) {
+    const double r = column(3 * c), x = column(3 * c + 1), g = column(3 * c + 2);
+    be = nanmax(be, r / (an * x + g));
   }
-  if (threadIdx.x == 0) berr[0] = be;
+  if (lane == 0) sh[wave] = be;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kRows / 64; ++w) be = nanmax(be, sh[w]);
+    berr[0] = be;
+  }
 }
 
 // ---- wide right-hand sides (N > 16): GEMM residual, separate norms ----
@@ -320,91 +411,6 @@ __global__ void __launch_bounds__(kRows) k_colabs(int64_t n, const double *__res
   if (threadIdx.x == 0) out[i] = sh[0];
 }
 
-// Transposed residual R = G - A^T L for N <= NMAX right-hand sides, with
-// the column sums of |A| (||A^T||_inf = ||A||_1) fused when ABS. A
-// workgroup owns tcols<NMAX>() columns of A (a quarter per wavefront) and
-// walks the rows in chunks of kRows: the chunk of L is staged in LDS and
-// reused by every column, each wavefront reads its columns of A as
-// coalesced runs, and the dot products are reduced across the wavefront at
-// the end. A is read once.
-template <int NMAX>
-constexpr int tcols() {
-  return NMAX >= 16 ? 8 : 16;
-}
-template <int NMAX, bool ABS>
-__global__ void __launch_bounds__(kRows) k_gemvT_sub(int64_t n, int N, const double *__restrict__ A,
-                                                     int64_t lda, const double *__restrict__ L,
-                                                     int64_t ldl, const double *__restrict__ G,
-                                                     int64_t ldg, double *__restrict__ R,
-                                                     int64_t ldr, double *__restrict__ colabs) {
-  constexpr int CW = tcols<NMAX>() / 4;  // columns per wavefront
-  __shared__ double Ls[kRows][NMAX];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j0 = int64_t(blockIdx.x) * tcols<NMAX>() + wave * CW;
-  double acc[CW][NMAX];
-  double aab[CW];
-#pragma unroll
-  for (int q = 0; q < CW; ++q) {
-    aab[q] = 0.0;
-#pragma unroll
-    for (int c = 0; c < NMAX; ++c) acc[q][c] = 0.0;
-  }
-  for (int64_t i0 = 0; i0 < n; i0 += kRows) {
-    __syncthreads();
-    {
-      const int64_t i = i0 + threadIdx.x;
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c)
-        Ls[threadIdx.x][c] = (i < n && c < N) ? L[i + int64_t(c) * ldl] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 2
-    for (int u = 0; u < kRows / 64; ++u) {
-      const int r = lane + 64 * u;
-      const int64_t i = i0 + r;
-      const bool rin = i < n;
-#pragma unroll
-      for (int q = 0; q < CW; ++q) {
-        const int64_t j = j0 + q;
-        // clamped, unconditional load; masked by rin / the column bound
-        const int64_t jc = j < n ? j : n - 1;
-        const double a0 = A[(rin ? i : n - 1) + jc * lda];
-        const double a = (rin && j < n) ? a0 : 0.0;
-        if constexpr (ABS) aab[q] += fabs(a);
-#pragma unroll
-        for (int c = 0; c < NMAX; ++c) acc[q][c] += a * Ls[r][c];
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < CW; ++q) {
-#pragma unroll
-    for (int c = 0; c < NMAX; ++c) {
-      double v = acc[q][c];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      acc[q][c] = v;
-    }
-    if constexpr (ABS) {
-      double v = aab[q];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      aab[q] = v;
-    }
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int q = 0; q < CW; ++q) {
-      const int64_t j = j0 + q;
-      if (j >= n) continue;
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c)
-        if (c < N) R[j + int64_t(c) * ldr] = G[j + int64_t(c) * ldg] - acc[q][c];
-      if constexpr (ABS) colabs[j] = aab[q];
-    }
-  }
-}
-
 __global__ void k_refine_step(const double *__restrict__ berr, double tol, int32_t *gate,
                               int32_t *iters) {
   if (threadIdx.x != 0 || *gate != 0) return;
@@ -420,21 +426,6 @@ __global__ void k_fill_i32(int32_t *p, int32_t v) {
 
 __global__ void k_fill_f64(double *p, double v) {
   if (threadIdx.x == 0) p[0] = v;
-}
-
-// Y[m, n] = sum over split-K chunks of partial (the product A X of
-// k_gemv_partial without the residual).
-template <int NMAX>
-__global__ void __launch_bounds__(kRows) k_gemv_sum(int64_t M, int N, int64_t chunks,
-                                                    const double *__restrict__ partial,
-                                                    double *__restrict__ Y, int64_t ldy) {
-  const int64_t m = int64_t(blockIdx.x) * kRows + threadIdx.x;
-  if (m >= M) return;
-  for (int n = 0; n < N; ++n) {
-    double s = 0.0;
-    for (int64_t c = 0; c < chunks; ++c) s += partial[(c * N + n) * M + m];
-    Y[m + int64_t(n) * ldy] = s;
-  }
 }
 
 // Krylov vector kernels (GMRES in FP64 on column blocks of <= kSkinnyMax
@@ -487,33 +478,71 @@ dim3 col_grid(int64_t n, int64_t nrhs) {
   return dim3(unsigned((n + kRows - 1) / kRows), unsigned(nrhs < 65535 ? nrhs : 65535));
 }
 
-template <int NMAX>
-hipError_t resid_t(int64_t n, int N, const double *A, int64_t lda, const double *X, int64_t ldx,
-                   const double *B, int64_t ldb, double *R, int64_t ldr, bool with_anorm,
-                   double *partial, double *abspart, double *blockstat, double *anorm,
-                   double *berr, hipStream_t s) {
-  const int64_t chunks = (n + kChunk - 1) / kChunk;
-  const int64_t nblk = (n + kRows - 1) / kRows;
-  const dim3 g2 = dim3(unsigned(nblk), unsigned(chunks));
-  if (with_anorm) {
-    hipLaunchKernelGGL((k_gemv_partial<NMAX, true>), g2, dim3(kRows), 0, s, n, N, n, A, lda, X, ldx, partial, abspart, refine_gate());
-    hipLaunchKernelGGL((k_resid_reduce<NMAX, true>), dim3(unsigned(nblk)), dim3(kRows), 0, s, n, N, chunks, partial, abspart, B, ldb, X, ldx, R, ldr, blockstat, refine_gate());
-    hipLaunchKernelGGL((k_berr_blocks<NMAX, true>), dim3(1), dim3(kRows), 0, s, nblk, N, blockstat, anorm, berr, refine_gate());
-  } else {
-    hipLaunchKernelGGL((k_gemv_partial<NMAX, false>), g2, dim3(kRows), 0, s, n, N, n, A, lda, X, ldx, partial, abspart, refine_gate());
-    hipLaunchKernelGGL((k_resid_reduce<NMAX, false>), dim3(unsigned(nblk)), dim3(kRows), 0, s, n, N, chunks, partial, abspart, B, ldb, X, ldx, R, ldr, blockstat, refine_gate());
-    hipLaunchKernelGGL((k_berr_blocks<NMAX, false>), dim3(1), dim3(kRows), 0, s, nblk, N, blockstat, anorm, berr, refine_gate());
+// Whether k_rows_product takes a residual with more than 16 right-hand sides
+// rather than a GEMM of 64 x 64 tiles: where those leave the device short of
+// work, up to one tile per compute unit if all are whole, two if some are
+// partial (n, right-hand sides, us as a GEMM / so: 5003, 64, 422 / 181; 4096, 128, 268 /
+// 181; 4096, 256, 294 / 341; 8191, 128, 803 / 665; 8191, 256, 1002 / 1299).
+bool few_gemm_tiles(int64_t n, int64_t nrhs) {
+  const int64_t tiles = ((n + 63) / 64) * ((nrhs + 63) / 64);
+  return tiles < (n % 64 == 0 && nrhs % 64 == 0 ? 256 : 512);
+}
+
+// 16-row tiles per workgroup of k_rows_product for up to 16 right-hand sides:
+// one until that makes a workgroup per compute unit, then two, which read
+// longer runs of a column (one / two tiles, us: n = 4096 32 / 39, 4097 60 / 41,
+// 8191 155 / 124).
+int rows_tiles(int64_t n) { return n <= 4096 ? 1 : 2; }
+
+// O = G - op(A) X or op(A) X, and the workgroups' statistics; their number.
+template <bool TRANS, bool ABS>
+int64_t launch_rows_product(int64_t n, int64_t nrhs, const double *A, int64_t lda, const double *X,
+                            int64_t ldx, const double *G, int64_t ldg, double *O, int64_t ldo,
+                            double *blockstat, hipStream_t s) {
+  const int rt = nrhs <= kSkinnyMax ? rows_tiles(n) : 1;
+  const int ct = nrhs <= kSkinnyMax ? 1 : (nrhs <= 32 ? 2 : 4);
+  const int64_t blocks = (n + 16 * rt - 1) / (16 * rt);
+  const dim3 grid = dim3(unsigned(blocks), unsigned((nrhs + 16 * ct - 1) / (16 * ct)));
+#define RBT_ROWS(RT, CT)                                                                         \
+  if (rt == RT && ct == CT)                                                                      \
+    hipLaunchKernelGGL((k_rows_product<TRANS, RT, CT, ABS>), grid, dim3(64 * kWaves), 0, s, n,   \
+                       int(nrhs), A, lda, X, ldx, G, ldg, O, ldo, blockstat, refine_gate());
+  RBT_ROWS(1, 1)
+  RBT_ROWS(2, 1)
+  RBT_ROWS(1, 2)
+  RBT_ROWS(1, 4)
+#undef RBT_ROWS
+  return blocks;
+}
+template <bool TRANS>
+hipError_t rows_residual(int64_t n, int64_t nrhs, const double *A, int64_t lda, const double *X,
+                         int64_t ldx, const double *G, int64_t ldg, double *O, int64_t ldo,
+                         bool with_anorm, double *blockstat, double *anorm, double *berr,
+                         hipStream_t s) {
+  const int64_t blocks =
+      with_anorm ? launch_rows_product<TRANS, true>(n, nrhs, A, lda, X, ldx, G, ldg, O, ldo, blockstat, s)
+                 : launch_rows_product<TRANS, false>(n, nrhs, A, lda, X, ldx, G, ldg, O, ldo, blockstat, s);
+  if (nrhs <= kSkinnyMax) {
+    if (with_anorm)
+      hipLaunchKernelGGL((k_berr_rows<true>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, refine_gate());
+    else
+      hipLaunchKernelGGL((k_berr_rows<false>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, refine_gate());
+  } else if (with_anorm) {
+    hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(kRows), 0, s, blocks, blockstat, anorm);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
+// Of callers' workspaces, so the amount does not shrink: rbt_solve_ex_noalloc
+// refuses the orders whose workspace exceeds its array. k_rows_product's
+// statistics take blocks (3 N + 1) of it (blocks <= n / 16 + 1) for up to 16
+// right-hand sides; more use abspart (chunks n), blockstat and colstat.
 size_t resid_scratch_doubles(int64_t n, int64_t nrhs) {
   const int64_t chunks = (n + kChunk - 1) / kChunk;
   const int64_t nblk = (n + kRows - 1) / kRows;
   const int64_t nn = nrhs < 1 ? 1 : nrhs;
-  // partial (chunks * max(nrhs,16) * n) + abspart (chunks * n) + blockstat + colstat
   const int64_t w = nn > kSkinnyMax ? 0 : nn;
   return size_t(chunks) * n * (w + 1) + size_t(nblk) * (3 * kSkinnyMax + 1) + 3 * size_t(nn) + 64;
 }
@@ -528,20 +557,19 @@ hipError_t launch_residual_berr(int64_t n, int64_t nrhs, const double *A, int64_
   }
   const int64_t chunks = (n + kChunk - 1) / kChunk;
   const int64_t nblk = (n + kRows - 1) / kRows;
-  if (nrhs <= kSkinnyMax) {
-    double *partial = scratch;
-    double *abspart = partial + chunks * n * nrhs;
-    double *blockstat = abspart + chunks * n;
-    const int N = int(nrhs);
-    if (N <= 1) return resid_t<1>(n, N, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, partial, abspart, blockstat, anorm, berr, s);
-    if (N <= 4) return resid_t<4>(n, N, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, partial, abspart, blockstat, anorm, berr, s);
-    if (N <= 8) return resid_t<8>(n, N, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, partial, abspart, blockstat, anorm, berr, s);
-    return resid_t<16>(n, N, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, partial, abspart, blockstat, anorm, berr, s);
-  }
-  // wide: norms by their own pass, residual by the matrix-core GEMM
+  if (nrhs <= kSkinnyMax)
+    return rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, s);
   double *abspart = scratch;
   double *blockstat = abspart + chunks * n;
   double *colstat = blockstat + nblk * (3 * kSkinnyMax + 1);
+  if (few_gemm_tiles(n, nrhs)) {
+    hipError_t e = rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_colmax, dim3(unsigned(nrhs)), dim3(kRows), 0, s, n, R, ldr, X, ldx, B, ldb, colstat);
+    hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr);
+    return hipGetLastError();
+  }
+  // wide: norms by their own pass, residual by the matrix-core GEMM
   if (with_anorm) {
     hipLaunchKernelGGL(k_rowabs_partial, dim3(unsigned(nblk), unsigned(chunks)), dim3(kRows), 0, s, n, A, lda, abspart);
     hipLaunchKernelGGL(k_rowabs_reduce, dim3(unsigned(nblk)), dim3(kRows), 0, s, n, chunks, abspart, blockstat);
@@ -608,26 +636,7 @@ hipError_t launch_matvec(int64_t n, int64_t nrhs, const double *A, int64_t lda, 
                          int64_t ldx, double *Y, int64_t ldy, double *scratch, hipStream_t s) {
   if (n <= 0 || nrhs <= 0) return hipSuccess;
   if (nrhs > kSkinnyMax) return hipErrorInvalidValue;
-  const int64_t chunks = (n + kChunk - 1) / kChunk;
-  const int64_t nblk = (n + kRows - 1) / kRows;
-  const dim3 g2 = dim3(unsigned(nblk), unsigned(chunks));
-  const int N = int(nrhs);
-  double *partial = scratch;
-#define RBT_MATVEC(NM)                                                                          \
-  hipLaunchKernelGGL((k_gemv_partial<NM, false>), g2, dim3(kRows), 0, s, n, N, n, A, lda, X,   \
-                     ldx, partial, (double *)nullptr, refine_gate());                                          \
-  hipLaunchKernelGGL((k_gemv_sum<NM>), dim3(unsigned(nblk)), dim3(kRows), 0, s, n, N, chunks,   \
-                     partial, Y, ldy);
-  if (N <= 1) {
-    RBT_MATVEC(1)
-  } else if (N <= 4) {
-    RBT_MATVEC(4)
-  } else if (N <= 8) {
-    RBT_MATVEC(8)
-  } else {
-    RBT_MATVEC(16)
-  }
-#undef RBT_MATVEC
+  launch_rows_product<false, false>(n, nrhs, A, lda, X, ldx, nullptr, 0, Y, ldy, scratch, s);
   return hipGetLastError();
 }
 
@@ -658,7 +667,7 @@ hipError_t launch_colscale(int64_t n, int N, const double *W, int64_t ldw, const
 
 // R = G - A^T L (the residual of the adjoint system A^T L = G) and its Eq. 7
 // backward error with ||A^T||_inf = ||A||_1 (with_anorm: computed here into
-// *anorm, else read). scratch: n + 3 nrhs doubles.
+// *anorm, else read). scratch as launch_residual_berr.
 hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int64_t lda,
                                   const double *L, int64_t ldl, const double *G, int64_t ldg,
                                   double *R, int64_t ldr, bool with_anorm, double *scratch,
@@ -669,28 +678,11 @@ hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int6
   }
   double *colabs = scratch;
   double *colstat = scratch + n;
-  if (nrhs <= kSkinnyMax) {
-    const int N = int(nrhs);
-#define RBT_GEMVT(NM)                                                                          \
-  const dim3 g(unsigned((n + tcols<NM>() - 1) / tcols<NM>()));                                \
-  if (with_anorm)                                                                              \
-    hipLaunchKernelGGL((k_gemvT_sub<NM, true>), g, dim3(kRows), 0, s, n, N, A, lda, L, ldl, G,  \
-                       ldg, R, ldr, colabs);                                                   \
-  else                                                                                         \
-    hipLaunchKernelGGL((k_gemvT_sub<NM, false>), g, dim3(kRows), 0, s, n, N, A, lda, L, ldl, G, \
-                       ldg, R, ldr, colabs);
-    if (N <= 1) {
-      RBT_GEMVT(1)
-    } else if (N <= 4) {
-      RBT_GEMVT(4)
-    } else if (N <= 8) {
-      RBT_GEMVT(8)
-    } else {
-      RBT_GEMVT(16)
-    }
-#undef RBT_GEMVT
-    if (with_anorm)
-      hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(kRows), 0, s, n, colabs, anorm);
+  if (nrhs <= kSkinnyMax)
+    return rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, s);
+  if (few_gemm_tiles(n, nrhs)) {
+    hipError_t e = rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, s);
+    if (e != hipSuccess) return e;
   } else {
     if (with_anorm) {
       hipLaunchKernelGGL(k_colabs, dim3(unsigned(n)), dim3(kRows), 0, s, n, A, lda, colabs);
