@@ -197,6 +197,30 @@ int read_sweep_err(const int32_t *sync, hipStream_t s) {
   return e != 0 ? RBT_ERR_SYNC : 0;
 }
 
+// Backward error and sweep error word, read back together: left by the kernel
+// that forms the error at anorm[kBerrPair ..] (one copy of 16 bytes in place of
+// two of 8 and 4).
+constexpr int kBerrPair = 48;
+BerrHost berr_host(double *anorm, const int32_t *sync) {
+  return BerrHost{anorm + kBerrPair, sync + kSweepErrWord};
+}
+int read_berr(const BerrHost &host, double *be, hipStream_t s) {
+  double pair[2] = {0.0, 0.0};
+  RBT_HIP_CHECK(hipMemcpyAsync(pair, host.pair, sizeof(pair), hipMemcpyDeviceToHost, s));
+  RBT_HIP_CHECK(hipStreamSynchronize(s));
+  *be = pair[0];
+  return pair[1] != 0.0 ? RBT_ERR_SYNC : 0;
+}
+
+// The end of an entry point that synchronizes: the error word is read again only
+// where sweeps have run since it last was (a refinement that ends before
+// max_iter ends on a reading).
+int finish(const int32_t *sync, bool read, hipStream_t s) {
+  if (!read) return read_sweep_err(sync, s);
+  RBT_HIP_CHECK(hipStreamSynchronize(s));
+  return 0;
+}
+
 template <typename T>
 T *at(void *base, size_t off) {
   return reinterpret_cast<T *>(static_cast<char *>(base) + off);
@@ -535,9 +559,9 @@ int getrs_fp64(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B,
     // one persistent launch per sweep: inverse + one refinement step per block
     double *P = nrhs <= kSkinnyMax ? nullptr : pub;
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::UT : TriMode::LN, n, nrhs, LU, ld, winv, B, ldb,
-                               sync, s, P));
+                               sync, s, P, SweepOf::First));
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::LT : TriMode::UN, n, nrhs, LU, ld, winv, B, ldb,
-                               sync, s, P));
+                               sync, s, P, SweepOf::Second));
     return 0;
   }
   const int64_t nb = nblocks(n);
@@ -588,24 +612,34 @@ hipError_t generate_t(int64_t n, int d, uint64_t seed, double *U, double *V, hip
   StageScope t(kStageGenerate, s, 16.0 * double(n) * d);
   return launch_generate(geometry(n, d), seed, U, V, s);
 }
-// x = V x~ (op N) or V^T g (op T): nothing for the one-sided RBT (V = I).
-hipError_t transform_v_t(const Geometry &g, int64_t nrhs, double *B, int64_t ldb,
-                         const double *V, int op, hipStream_t s);
 hipError_t transform2_t(const Geometry &g, const double *A, int64_t lda, void *out, int64_t ldo,
                         int prec, const double *U, const double *V, hipStream_t s) {
   const double elt_out = prec == RBT_FP32 ? 4.0 : 8.0;
   StageScope t(kStageTransform2, s, (8.0 + elt_out) * double(g.n) * g.n);
   return launch_transform2(g, A, lda, out, ldo, prec, U, V, s);
 }
-hipError_t transform_vec_t(const Geometry &g, int64_t nrhs, double *B, int64_t ldb,
-                           const double *C, int op, hipStream_t s) {
+// Out = op(C) In; Out += op(C) In (which overwrites In).
+hipError_t transform_vec_t(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
+                           double *Out, int64_t ldo, const double *C, int op, hipStream_t s) {
   StageScope t(kStageTransformVec, s, 16.0 * double(g.n) * nrhs);
-  return launch_transform_vec(g, nrhs, B, ldb, C, op, s);
+  return launch_transform_vec(g, nrhs, In, ldi, Out, ldo, C, op, s);
 }
-hipError_t transform_v_t(const Geometry &g, int64_t nrhs, double *B, int64_t ldb,
-                         const double *V, int op, hipStream_t s) {
-  if (g.sides == 1) return hipSuccess;
-  return transform_vec_t(g, nrhs, B, ldb, V, op, s);
+hipError_t transform_vec_add_t(const Geometry &g, int64_t nrhs, double *In, int64_t ldi,
+                               double *Out, int64_t ldo, const double *C, int op, hipStream_t s) {
+  StageScope t(kStageTransformVec, s, 24.0 * double(g.n) * nrhs);
+  return launch_transform_vec_add(g, nrhs, In, ldi, Out, ldo, C, op, s);
+}
+// The same with V, the identity in the one-sided form.
+hipError_t transform_v_t(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
+                         double *Out, int64_t ldo, const double *V, int op, hipStream_t s) {
+  if (g.sides != 1) return transform_vec_t(g, nrhs, In, ldi, Out, ldo, V, op, s);
+  if (In == Out && ldi == ldo) return hipSuccess;
+  return launch_copy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
+}
+hipError_t transform_v_add_t(const Geometry &g, int64_t nrhs, double *In, int64_t ldi, double *Out,
+                             int64_t ldo, const double *V, int op, hipStream_t s) {
+  if (g.sides != 1) return transform_vec_add_t(g, nrhs, In, ldi, Out, ldo, V, op, s);
+  return launch_axpy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
 }
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
             int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s) {
@@ -655,30 +689,36 @@ int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int
     for (int pass = 0; pass < 2; ++pass) {
       const TriMode m = pass == 0 ? (trans ? TriMode::UT : TriMode::LN)
                                   : (trans ? TriMode::LT : TriMode::UN);
+      const SweepOf of = pass == 0 ? SweepOf::First : SweepOf::Second;
       if (f64)
-        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv, Bc, ldb, sync, s, P));
+        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv, Bc, ldb, sync, s, P, of));
       else
-        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv32, Bc, ldb, sync, s, P));
+        RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv32, Bc, ldb, sync, s, P, of));
     }
   }
   return 0;
 }
 
-// R <- V (L U)^-1 U^T R: the solve of Eq. 1 with the factors of A~ (f64:
-// arithmetic of the triangular solves with FP32 factors, see getrs_t).
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
             int trans, const double *winv, int32_t *sync, double *pub, bool /*f64*/,
             hipStream_t s) {
   return getrs_t(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s);
 }
+// R <- V (L U)^-1 U^T S, the solve of Eq. 1 with the factors of A~ (S may be R;
+// f64: arithmetic of the triangular solves with FP32 factors, see getrs_t), or
+// with X: X += V (L U)^-1 U^T S, with R for the intermediate.
 template <typename TF>
-int apply_solve(const Geometry &g, int64_t nrhs, const TF *LU, int64_t ld, double *R, int64_t ldr,
-                const double *U, const double *V, const double *winv, int32_t *sync, double *pub,
-                bool f64, hipStream_t s) {
-  RBT_HIP_CHECK(transform_vec_t(g, nrhs, R, ldr, U, RBT_OP_T, s));
+int apply_solve(const Geometry &g, int64_t nrhs, const TF *LU, int64_t ld, const double *S,
+                int64_t lds, double *R, int64_t ldr, const double *U, const double *V,
+                const double *winv, int32_t *sync, double *pub, bool f64, hipStream_t s,
+                double *X = nullptr, int64_t ldx = 0) {
+  RBT_HIP_CHECK(transform_vec_t(g, nrhs, S, lds, R, ldr, U, RBT_OP_T, s));
   const int rc = getrs_t(g.n, nrhs, LU, ld, R, ldr, 0, winv, sync, pub, f64, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(transform_v_t(g, nrhs, R, ldr, V, RBT_OP_N, s));
+  if (X != nullptr)
+    RBT_HIP_CHECK(transform_v_add_t(g, nrhs, R, ldr, X, ldx, V, RBT_OP_N, s));
+  else
+    RBT_HIP_CHECK(transform_v_t(g, nrhs, R, ldr, R, ldr, V, RBT_OP_N, s));
   return 0;
 }
 
@@ -696,16 +736,16 @@ int refine_classic(int64_t n, int64_t nrhs, const double *A, int64_t lda, const 
                    bool *stalled = nullptr) {
   int it = 0;
   double be_prev = 0.0;
+  const BerrHost host = berr_host(anorm, sync);
   for (;;) {
     {
       StageScope t(kStageResidual, s, 8.0 * double(n) * n);
       RBT_HIP_CHECK(launch_residual_berr(n, nrhs, A, lda, X, ldx, B, ldb, R, n, it == 0, scratch,
-                                         anorm, berr, s));
+                                         anorm, berr, s, host));
     }
     if (it >= max_iter) break;
     double be_host = 0.0;
-    RBT_HIP_CHECK(hipMemcpyAsync(&be_host, berr, sizeof(double), hipMemcpyDeviceToHost, s));
-    if (const int e = read_sweep_err(sync, s)) return e;  // also waits for be_host
+    if (const int e = read_berr(host, &be_host, s)) return e;
     if (be_host <= tol) break;
     // guarded use: a non-finite error, or a correction that did not halve
     // the error, means these factors cannot reach tol (the caller falls back)
@@ -714,9 +754,9 @@ int refine_classic(int64_t n, int64_t nrhs, const double *A, int64_t lda, const 
       break;
     }
     be_prev = be_host;
-    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, pub, f64, s);
+    const int rc =
+        apply_solve(g, nrhs, LU, ldlu, R, n, R, n, U, V, winv, sync, pub, f64, s, X, ldx);
     if (rc) return rc;
-    RBT_HIP_CHECK(launch_axpy_cols(n, nrhs, R, n, X, ldx, s));
     ++it;
   }
   *it_out = it;
@@ -747,9 +787,9 @@ int refine_classic_device(int64_t n, int64_t nrhs, const double *A, int64_t lda,
   RefineGate on(gate);
   for (int it = 0; it < max_iter; ++it) {
     RBT_HIP_CHECK(launch_refine_step(berr, tol, gate, iters, s));
-    const int rc = apply_solve(g, nrhs, LU, ldlu, R, n, U, V, winv, sync, nullptr, f64, s);
+    const int rc =
+        apply_solve(g, nrhs, LU, ldlu, R, n, R, n, U, V, winv, sync, nullptr, f64, s, X, ldx);
     if (rc) return rc;
-    RBT_HIP_CHECK(launch_axpy_cols(n, nrhs, R, n, X, ldx, s));
     StageScope t(kStageResidual, s, 8.0 * double(n) * n);
     RBT_HIP_CHECK(launch_residual_berr(n, nrhs, A, lda, X, ldx, B, ldb, R, n, false, scratch,
                                        anorm, berr, s));
@@ -814,7 +854,7 @@ int refine_gmres(int64_t n, int64_t nrhs, const double *A, int64_t lda, const TF
       }
       bool stop = false;
       // z = M^-1 r, v_0 = z / ||z||
-      rc = apply_solve(g, nc, LU, ldlu, R, n, U, V, winv, sync, nullptr, true, s);
+      rc = apply_solve(g, nc, LU, ldlu, R, n, R, n, U, V, winv, sync, nullptr, true, s);
       if (rc) return rc;
       RBT_HIP_CHECK(launch_coldots(n, nc, 1, R, 0, R, n, nrm, s));
       RBT_HIP_CHECK(launch_colscale(n, nc, R, n, nrm, Vb, s));
@@ -839,7 +879,7 @@ int refine_gmres(int64_t n, int64_t nrhs, const double *A, int64_t lda, const TF
           StageScope t(kStageResidual, s, 8.0 * double(n) * n);
           RBT_HIP_CHECK(launch_matvec(n, nc, A, lda, Vj, n, W, n, scratch, s));
         }
-        rc = apply_solve(g, nc, LU, ldlu, W, n, U, V, winv, sync, nullptr, true, s);
+        rc = apply_solve(g, nc, LU, ldlu, W, n, W, n, U, V, winv, sync, nullptr, true, s);
         if (rc) return rc;
         RBT_HIP_CHECK(launch_coldots(n, nc, j + 1, Vb, vs, W, n, dots, s));
         RBT_HIP_CHECK(launch_colcombo(n, nc, j + 1, Vb, vs, dots, -1.0, W, n, s));
@@ -1059,7 +1099,8 @@ extern "C" int rbt_transform_vec(int64_t n, int64_t nrhs, double *B, int64_t ldb
   if (n > 0 && depth > 0 && dC == nullptr) return -5;
   if (bad_depth(depth)) return -6;
   if (op != RBT_OP_T && op != RBT_OP_N) return -7;
-  RBT_HIP_CHECK(launch_transform_vec(geometry(n, depth), nrhs, B, ldb, dC, op, S(stream)));
+  RBT_HIP_CHECK(
+      launch_transform_vec(geometry(n, depth), nrhs, B, ldb, B, ldb, dC, op, S(stream)));
   return 0;
 }
 
@@ -1114,7 +1155,7 @@ extern "C" int rbt_solve_ex(int64_t n, int64_t nrhs, double *A, int64_t lda, dou
   double *V = U + n * depth;
   RBT_HIP_CHECK(generate_t(n, depth, seed, U, V, s));
   RBT_HIP_CHECK(transform2_t(g, A, lda, A, lda, RBT_FP64, U, V, s));
-  RBT_HIP_CHECK(transform_vec_t(g, nrhs, B, ldb, U, RBT_OP_T, s));
+  RBT_HIP_CHECK(transform_vec_t(g, nrhs, B, ldb, B, ldb, U, RBT_OP_T, s));
   double *winv = at<double>(work, L.o_winv);
   int rc = genp_fp64(n, A, lda, info_dev, s);
   if (rc) return rc;
@@ -1124,7 +1165,7 @@ extern "C" int rbt_solve_ex(int64_t n, int64_t nrhs, double *A, int64_t lda, dou
   RBT_HIP_CHECK(clear_sweep_err(at<int32_t>(work, L.o_sync), s));
   rc = getrs_t(n, nrhs, A, lda, B, ldb, 0, winv, at<int32_t>(work, L.o_sync), pub, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(transform_v_t(g, nrhs, B, ldb, V, RBT_OP_N, s));
+  RBT_HIP_CHECK(transform_v_t(g, nrhs, B, ldb, B, ldb, V, RBT_OP_N, s));
   return 0;
 }
 
@@ -1249,10 +1290,10 @@ extern "C" int rbt_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_
   double *pub = at<double>(work, L.o_ygat);
   rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   int32_t *sync = at<int32_t>(work, L.o_sync);
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
-  rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, pub, true, s);
+  rc = apply_solve(g, nrhs, (const double *)LU, ldlu, B, ldb, X, ldx, U, V, winv, sync, pub, true,
+                   s);
   if (rc) return rc;
   if (options().capturable) {
     // no host test: an expired sweep wait shows as a NaN backward error
@@ -1265,9 +1306,8 @@ extern "C" int rbt_solve_refine(int64_t n, int64_t nrhs, const double *A, int64_
   rc = refine_classic(n, nrhs, A, lda, (const double *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv, sync,
                       pub, R, scratch, anorm, berr, tol, max_iter, &it, true, s);
   if (rc) return rc;
-  if (iters_dev)
-    RBT_HIP_CHECK(hipMemcpyAsync(iters_dev, &it, sizeof(int32_t), hipMemcpyHostToDevice, s));
-  return read_sweep_err(sync, s);  // synchronizes
+  if (iters_dev) RBT_HIP_CHECK(launch_fill_i32(iters_dev, it, s));
+  return finish(sync, it < max_iter, s);
 }
 
 namespace rbt {
@@ -1321,11 +1361,11 @@ int mixed_impl(int64_t n, int64_t nrhs, const double *A, int64_t lda, float *LU,
   const bool f64 = options().mixed_fp64_inner != 0 || solver == RBT_IR_GMRES;
   rc = diag_inverses_t(n, LU, ldlu, winv, f64, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
   int32_t *sync = at<int32_t>(work, L.o_sync);
   RBT_HIP_CHECK(clear_sweep_err(sync, s));
   double *pub = at<double>(work, L.o_ygat);
-  rc = apply_solve(g, nrhs, (const float *)LU, ldlu, X, ldx, U, V, winv, sync, pub, f64, s);
+  rc = apply_solve(g, nrhs, (const float *)LU, ldlu, B, ldb, X, ldx, U, V, winv, sync, pub, f64,
+                   s);
   if (rc) return rc;
   if (iters_cap != nullptr) {
     int32_t *words = reinterpret_cast<int32_t *>(small + 32);
@@ -1341,7 +1381,7 @@ int mixed_impl(int64_t n, int64_t nrhs, const double *A, int64_t lda, float *LU,
     rc = refine_classic(n, nrhs, A, lda, (const float *)LU, ldlu, B, ldb, X, ldx, g, U, V, winv,
                         sync, pub, R, scratch, anorm, berr, tol, max_iter, it_out, f64, s, stalled);
   if (rc) return rc;
-  return read_sweep_err(sync, s);  // synchronizes
+  return finish(sync, solver != RBT_IR_GMRES && *it_out < max_iter, s);
 }
 
 int mixed_args(int64_t n, int64_t nrhs, const double *A, int64_t lda, const float *LU,
@@ -1446,8 +1486,8 @@ extern "C" int rbt_solve_mixed_guarded(int64_t n, int64_t nrhs, const double *A,
     double *pub = at<double>(work, L.o_ygat);
     rc = diag_inverses_t(n, nrhs, LU64, ldlu64, winv, pub, s);
     if (rc) return rc;
-    RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
-    rc = apply_solve(g, nrhs, (const double *)LU64, ldlu64, X, ldx, U, V, winv, sync, pub, true, s);
+    rc = apply_solve(g, nrhs, (const double *)LU64, ldlu64, B, ldb, X, ldx, U, V, winv, sync, pub, true,
+                   s);
     if (rc) return rc;
     int it64 = 0;
     bool stalled64 = false;
@@ -1563,8 +1603,8 @@ extern "C" int rbt_solve_guarded(int64_t n, int64_t nrhs, const double *A, int64
     rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
     if (rc) return rc;
     RBT_HIP_CHECK(clear_sweep_err(sync, s));
-    RBT_HIP_CHECK(launch_copy_cols(n, nrhs, B, ldb, X, ldx, s));
-    rc = apply_solve(g, nrhs, (const double *)LU, ldlu, X, ldx, U, V, winv, sync, pub, true, s);
+    rc = apply_solve(g, nrhs, (const double *)LU, ldlu, B, ldb, X, ldx, U, V, winv, sync, pub, true,
+                   s);
     if (rc) return rc;
     int it = 0;
     bool stalled = false;
@@ -1741,41 +1781,42 @@ extern "C" int rbt_solve_backward_mixed(int64_t n, int64_t nrhs, const float *LU
   const bool f64 = options().mixed_fp64_inner != 0;
   int rc = diag_inverses_t(n, LU, ldlu, winv, f64, s);
   if (rc) return rc;
-  auto adjoint_solve = [&](double *Y, int64_t ldy) -> int {
-    RBT_HIP_CHECK(transform_v_t(g, nrhs, Y, ldy, V, RBT_OP_T, s));
+  // dB += (add) or = A^-T S with the factors, Y for the intermediate
+  auto adjoint_solve = [&](const double *S, int64_t lds, double *Y, int64_t ldy, bool add) -> int {
+    RBT_HIP_CHECK(transform_v_t(g, nrhs, S, lds, Y, ldy, V, RBT_OP_T, s));
     const int r = getrs_t(n, nrhs, LU, ldlu, Y, ldy, 1, winv, sync, at<double>(work, L.o_ygat), f64,
                           s);
     if (r) return r;
-    RBT_HIP_CHECK(transform_vec_t(g, nrhs, Y, ldy, U, RBT_OP_N, s));
+    if (add)
+      RBT_HIP_CHECK(transform_vec_add_t(g, nrhs, Y, ldy, dB, lddb, U, RBT_OP_N, s));
+    else
+      RBT_HIP_CHECK(transform_vec_t(g, nrhs, Y, ldy, dB, lddb, U, RBT_OP_N, s));
     return 0;
   };
-  RBT_HIP_CHECK(launch_copy_cols(n, nrhs, G, ldg, dB, lddb, s));
-  rc = adjoint_solve(dB, lddb);
+  rc = adjoint_solve(G, ldg, dB, lddb, false);
   if (rc) return rc;
+  const BerrHost host = berr_host(anorm, sync);
   int it = 0;
   for (;;) {
     {
       StageScope t(kStageResidual, s, 8.0 * double(n) * n);
       RBT_HIP_CHECK(launch_residual_berr_T(n, nrhs, A, lda, dB, lddb, G, ldg, R, n, it == 0,
-                                           scratch, anorm, berr, s));
+                                           scratch, anorm, berr, s, host));
     }
     if (it >= max_iter) break;
     double be_host = 0.0;
-    RBT_HIP_CHECK(hipMemcpyAsync(&be_host, berr, sizeof(double), hipMemcpyDeviceToHost, s));
-    if (const int e = read_sweep_err(sync, s)) return e;  // also waits for be_host
+    if (const int e = read_berr(host, &be_host, s)) return e;
     if (be_host <= tol) break;
-    rc = adjoint_solve(R, n);
+    rc = adjoint_solve(R, n, R, n, true);
     if (rc) return rc;
-    RBT_HIP_CHECK(launch_axpy_cols(n, nrhs, R, n, dB, lddb, s));
     ++it;
   }
   if (dA != nullptr) {
     StageScope t(kStageOuter, s, 8.0 * double(n) * n);
     RBT_HIP_CHECK(launch_neg_outer(n, nrhs, dB, lddb, X, ldx, dA, ldda, s));
   }
-  if (iters_dev)
-    RBT_HIP_CHECK(hipMemcpyAsync(iters_dev, &it, sizeof(int32_t), hipMemcpyHostToDevice, s));
-  return read_sweep_err(sync, s);  // synchronizes
+  if (iters_dev) RBT_HIP_CHECK(launch_fill_i32(iters_dev, it, s));
+  return finish(sync, it < max_iter, s);
 }
 
 extern "C" int rbt_set_option(int option, int64_t value) {
@@ -1888,15 +1929,14 @@ extern "C" int rbt_solve_backward(int64_t n, int64_t nrhs, const double *LU, int
   double *winv = at<double>(work, L.o_winv);
   // Lambda = A^-T G = U (A~^-T (V^T G)),  A~ = U^T A V = L U_f
   RBT_HIP_CHECK(generate_t(n, depth, seed, U, V, s));
-  RBT_HIP_CHECK(launch_copy_cols(n, nrhs, G, ldg, dB, lddb, s));
-  RBT_HIP_CHECK(transform_v_t(g, nrhs, dB, lddb, V, RBT_OP_T, s));
+  RBT_HIP_CHECK(transform_v_t(g, nrhs, G, ldg, dB, lddb, V, RBT_OP_T, s));
   double *pub = at<double>(work, L.o_ygat);
   int rc = diag_inverses_t(n, nrhs, LU, ldlu, winv, pub, s);
   if (rc) return rc;
   RBT_HIP_CHECK(clear_sweep_err(at<int32_t>(work, L.o_sync), s));
   rc = getrs_t(n, nrhs, LU, ldlu, dB, lddb, 1, winv, at<int32_t>(work, L.o_sync), pub, s);
   if (rc) return rc;
-  RBT_HIP_CHECK(transform_vec_t(g, nrhs, dB, lddb, U, RBT_OP_N, s));
+  RBT_HIP_CHECK(transform_vec_t(g, nrhs, dB, lddb, dB, lddb, U, RBT_OP_N, s));
   if (dA != nullptr) {
     StageScope t(kStageOuter, s, 8.0 * double(n) * n);
     RBT_HIP_CHECK(launch_neg_outer(n, nrhs, dB, lddb, X, ldx, dA, ldda, s));

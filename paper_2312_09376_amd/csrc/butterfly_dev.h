@@ -244,11 +244,12 @@ __device__ __forceinline__ void transform2_block(PA __restrict__ A, int64_t lda,
       }
 }
 
-// One-sided pass on column j of B for the group at rb. op T (U^T b):
-// layers hi..lo, mix then scale; op N (V x~): layers lo..hi, scale then mix.
-template <int P, int OP, typename PB, typename PC>
-__device__ __forceinline__ void transform_vec_block(PB __restrict__ B, int64_t ldb, int64_t j,
-                                                    PC __restrict__ C, const Pass &ps,
+// One-sided pass on column j of In for the group at rb, to Out (which may be
+// In), or added to Out (ADD). op T (U^T b): layers hi..lo, mix then scale; op N
+// (V x~): layers lo..hi, scale then mix.
+template <int P, int OP, bool ADD, typename PI, typename PO, typename PC>
+__device__ __forceinline__ void transform_vec_block(PI In, int64_t ldi, PO Out, int64_t ldo,
+                                                    int64_t j, PC __restrict__ C, const Pass &ps,
                                                     int64_t rb) {
   constexpr int G = 1 << P;
   int64_t ri[G];
@@ -260,7 +261,7 @@ __device__ __forceinline__ void transform_vec_block(PB __restrict__ B, int64_t l
   }
   double x[G];
 #pragma unroll
-  for (int p = 0; p < G; ++p) x[p] = B[(rv[p] ? ri[p] : rb) + j * ldb];  // (as above)
+  for (int p = 0; p < G; ++p) x[p] = In[(rv[p] ? ri[p] : rb) + j * ldi];  // (as above)
 #pragma unroll
   for (int p = 0; p < G; ++p) x[p] = rv[p] ? x[p] : 0.0;
 #pragma unroll
@@ -311,7 +312,12 @@ __device__ __forceinline__ void transform_vec_block(PB __restrict__ B, int64_t l
   }
 #pragma unroll
   for (int p = 0; p < G; ++p)
-    if (rv[p]) B[ri[p] + j * ldb] = x[p];
+    if (rv[p]) Out[ri[p] + j * ldo] = ADD ? Out[ri[p] + j * ldo] + x[p] : x[p];
+}
+template <int P, int OP, typename PB, typename PC>
+__device__ __forceinline__ void transform_vec_block(PB B, int64_t ldb, int64_t j, PC C,
+                                                    const Pass &ps, int64_t rb) {
+  transform_vec_block<P, OP, false>(B, ldb, B, ldb, j, C, ps, rb);
 }
 
 }  // namespace dev

@@ -105,8 +105,12 @@ hipError_t launch_generate(const Geometry &g, uint64_t seed, double *U, double *
 hipError_t launch_transform2(const Geometry &g, const double *A, int64_t lda, void *out,
                              int64_t ldo, int out_prec, const double *U, const double *V,
                              hipStream_t s);
-hipError_t launch_transform_vec(const Geometry &g, int64_t nrhs, double *B, int64_t ldb,
-                                const double *C, int op, hipStream_t s);
+// Out = op(C) In (Out may be In); Out += op(C) In, which overwrites In
+hipError_t launch_transform_vec(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
+                                double *Out, int64_t ldo, const double *C, int op, hipStream_t s);
+hipError_t launch_transform_vec_add(const Geometry &g, int64_t nrhs, double *In, int64_t ldi,
+                                    double *Out, int64_t ldo, const double *C, int op,
+                                    hipStream_t s);
 
 // k_gemm.hip : C (M x N) op= A (M x K) * B (K x N), FP64, column-major.
 // Triangular modes read a packed block inverse W (ld = kNB): strictly lower
@@ -215,18 +219,33 @@ constexpr int kSweepErrWord = 3;
 // RBT_OPT_SWEEP_SPIN_LIMIT; negative: every wait expires at once).
 int64_t sweep_spin_limit();
 // pub: publication buffer of n * nrhs doubles elsewhere, for any number of
-// right-hand sides (groups of kSkinnyMax side by side); null: the one in the
-// sync area, nrhs <= kSkinnyMax.
+// right-hand sides; null: the one in the sync area, nrhs <= kSkinnyMax.
+// The two sweeps of a solve, one after the other on a stream, are First and
+// Second: where the sync area holds the publications of both (up to half of
+// kSkinnyMax right-hand sides), the first one's launch prepares it for both.
+// A sweep by itself is Alone.
+enum class SweepOf { Alone, First, Second };
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const double *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
-                        double *pub = nullptr);
+                        double *pub = nullptr, SweepOf of = SweepOf::Alone);
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
-                        double *pub = nullptr);
+                        double *pub = nullptr, SweepOf of = SweepOf::Alone);
 // FP32 arithmetic with FP32 inverses (B stays FP64 storage)
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const float *Winv, double *B, int64_t ldb, int32_t *sync, hipStream_t s,
-                        double *pub = nullptr);
+                        double *pub = nullptr, SweepOf of = SweepOf::Alone);
+// Where the kernel that forms a backward error also leaves it for one copy to the
+// host, with the sweeps' error word: pair[0] = error, pair[1] = word (nullable).
+struct BerrHost {
+  double *pair = nullptr;
+  const int32_t *err = nullptr;
+  __device__ void store(double be) const {
+    if (pair == nullptr) return;
+    pair[0] = be;
+    pair[1] = double(err[0]);
+  }
+};
 // doubles of scratch needed by launch_residual_berr
 size_t resid_scratch_doubles(int64_t n, int64_t nrhs);
 // R = B - A X; berr = Eq. 7 (max over columns); with_anorm: also ||A||_inf -> *anorm
@@ -234,7 +253,7 @@ size_t resid_scratch_doubles(int64_t n, int64_t nrhs);
 hipError_t launch_residual_berr(int64_t n, int64_t nrhs, const double *A, int64_t lda,
                                 const double *X, int64_t ldx, const double *B, int64_t ldb,
                                 double *R, int64_t ldr, bool with_anorm, double *scratch,
-                                double *anorm, double *berr, hipStream_t s);
+                                double *anorm, double *berr, hipStream_t s, BerrHost host = {});
 // Y = A X (n x nrhs, nrhs <= kSkinnyMax); scratch as launch_residual_berr.
 hipError_t launch_matvec(int64_t n, int64_t nrhs, const double *A, int64_t lda, const double *X,
                          int64_t ldx, double *Y, int64_t ldy, double *scratch, hipStream_t s);
@@ -254,7 +273,7 @@ hipError_t launch_colscale(int64_t n, int N, const double *W, int64_t ldw, const
 hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int64_t lda,
                                   const double *L, int64_t ldl, const double *G, int64_t ldg,
                                   double *R, int64_t ldr, bool with_anorm, double *scratch,
-                                  double *anorm, double *berr, hipStream_t s);
+                                  double *anorm, double *berr, hipStream_t s, BerrHost host = {});
 hipError_t launch_axpy_cols(int64_t n, int64_t nrhs, const double *D, int64_t ldd, double *X,
                             int64_t ldx, hipStream_t s);
 hipError_t launch_copy_cols(int64_t n, int64_t nrhs, const double *S, int64_t lds, double *D,

@@ -70,10 +70,10 @@ __global__ void __launch_bounds__(256) k_transform2(const TI *__restrict__ A, in
   }
 }
 
-// One-sided pass on an n x nrhs block.
-template <int P, int OP>
-__global__ void __launch_bounds__(256) k_transform_vec(double *__restrict__ B, int64_t ldb,
-                                                       int64_t nrhs,
+// One-sided pass on an n x nrhs block, to Out (which may be In) or added to it.
+template <int P, int OP, bool ADD>
+__global__ void __launch_bounds__(256) k_transform_vec(const double *In, int64_t ldi, double *Out,
+                                                       int64_t ldo, int64_t nrhs,
                                                        const double *__restrict__ C, Pass ps,
                                                        const int32_t *gate) {
   if (gated(gate)) return;
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) k_transform_vec(double *__restrict__ B, i
   const int64_t rb = group_base(ps, gr);
   if (rb >= ps.n) return;
   for (int64_t j = blockIdx.y; j < nrhs; j += gridDim.y)
-    dev::transform_vec_block<P, OP>(B, ldb, j, C, ps, rb);
+    dev::transform_vec_block<P, OP, ADD>(In, ldi, Out, ldo, j, C, ps, rb);
 }
 
 Pass make_pass(const Geometry &g, int lo, int hi) {
@@ -104,15 +104,15 @@ hipError_t launch_pass2(const Pass &ps, const TI *A, int64_t lda, TO *out, int64
   return hipGetLastError();
 }
 
-template <int OP>
-hipError_t launch_pass_vec(const Pass &ps, double *B, int64_t ldb, int64_t nrhs, const double *C,
-                           hipStream_t s) {
+template <int OP, bool ADD>
+hipError_t launch_pass_vec(const Pass &ps, const double *In, int64_t ldi, double *Out, int64_t ldo,
+                           int64_t nrhs, const double *C, hipStream_t s) {
   const int P = ps.hi - ps.lo + 1;
   dim3 grid(unsigned((ps.ngroups + 255) / 256), unsigned(nrhs < 65535 ? nrhs : 65535));
   switch (P) {
-    case 1: hipLaunchKernelGGL((k_transform_vec<1, OP>), grid, dim3(256), 0, s, B, ldb, nrhs, C, ps, refine_gate()); break;
-    case 2: hipLaunchKernelGGL((k_transform_vec<2, OP>), grid, dim3(256), 0, s, B, ldb, nrhs, C, ps, refine_gate()); break;
-    default: hipLaunchKernelGGL((k_transform_vec<3, OP>), grid, dim3(256), 0, s, B, ldb, nrhs, C, ps, refine_gate()); break;
+    case 1: hipLaunchKernelGGL((k_transform_vec<1, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
+    case 2: hipLaunchKernelGGL((k_transform_vec<2, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
+    default: hipLaunchKernelGGL((k_transform_vec<3, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
   }
   return hipGetLastError();
 }
@@ -167,27 +167,50 @@ hipError_t launch_transform2(const Geometry &g, const double *A, int64_t lda, vo
   return hipSuccess;
 }
 
-hipError_t launch_transform_vec(const Geometry &g, int64_t nrhs, double *B, int64_t ldb,
-                                const double *C, int op, hipStream_t s) {
-  if (g.n == 0 || nrhs == 0 || g.d == 0) return hipSuccess;
-  if (op == RBT_OP_T) {
-    int hi = g.d;
-    while (hi >= 1) {
-      const int lo = hi - 2 >= 1 ? hi - 2 : 1;
-      hipError_t e = launch_pass_vec<RBT_OP_T>(make_pass(g, lo, hi), B, ldb, nrhs, C, s);
-      if (e != hipSuccess) return e;
-      hi = lo - 1;
-    }
-  } else {
-    int lo = 1;
-    while (lo <= g.d) {
-      const int hi = lo + 2 <= g.d ? lo + 2 : g.d;
-      hipError_t e = launch_pass_vec<RBT_OP_N>(make_pass(g, lo, hi), B, ldb, nrhs, C, s);
-      if (e != hipSuccess) return e;
-      lo = hi + 1;
-    }
+// Passes of at most three layers. Not added: the first one goes to Out, the
+// others work on it in place. Added (Work = In): in place on In, the last one to
+// Out.
+static hipError_t transform_vec_passes(const Geometry &g, int64_t nrhs, const double *In,
+                                       int64_t ldi, double *Work, double *Out, int64_t ldo,
+                                       const double *C, int op, hipStream_t s) {
+  const bool add = Work != nullptr;
+  const int passes = (g.d + 2) / 3;
+  for (int k = 0; k < passes; ++k) {
+    // op T: layers (d-2..d), (d-5..d-3), ...; op N: (1..3), (4..6), ...
+    const int hi = op == RBT_OP_T ? g.d - 3 * k : (3 * k + 3 < g.d ? 3 * k + 3 : g.d);
+    const int lo = op == RBT_OP_T ? (hi - 2 > 1 ? hi - 2 : 1) : 3 * k + 1;
+    const bool last = k + 1 == passes;
+    const double *from = add || k == 0 ? In : Out;
+    double *to = add && !last ? Work : Out;
+    const int64_t ldf = add || k == 0 ? ldi : ldo, ldt = add && !last ? ldi : ldo;
+    const Pass ps = make_pass(g, lo, hi);
+    hipError_t e;
+    if (op == RBT_OP_T)
+      e = add && last ? launch_pass_vec<RBT_OP_T, true>(ps, from, ldf, to, ldt, nrhs, C, s)
+                      : launch_pass_vec<RBT_OP_T, false>(ps, from, ldf, to, ldt, nrhs, C, s);
+    else
+      e = add && last ? launch_pass_vec<RBT_OP_N, true>(ps, from, ldf, to, ldt, nrhs, C, s)
+                      : launch_pass_vec<RBT_OP_N, false>(ps, from, ldf, to, ldt, nrhs, C, s);
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_transform_vec(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
+                                double *Out, int64_t ldo, const double *C, int op,
+                                hipStream_t s) {
+  if (g.n == 0 || nrhs == 0) return hipSuccess;
+  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, nullptr, Out, ldo, C, op, s);
+  if (In == Out && ldi == ldo) return hipSuccess;
+  return launch_copy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
+}
+
+hipError_t launch_transform_vec_add(const Geometry &g, int64_t nrhs, double *In, int64_t ldi,
+                                    double *Out, int64_t ldo, const double *C, int op,
+                                    hipStream_t s) {
+  if (g.n == 0 || nrhs == 0) return hipSuccess;
+  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, In, Out, ldo, C, op, s);
+  return launch_axpy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
 }
 
 }  // namespace rbt

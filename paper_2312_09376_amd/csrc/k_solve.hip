@@ -221,7 +221,7 @@ template <bool ABS>
 __global__ void __launch_bounds__(kRows) k_berr_rows(int64_t nblk, int N,
                                                      const double *__restrict__ blockstat,
                                                      double *__restrict__ anorm,
-                                                     double *__restrict__ berr,
+                                                     double *__restrict__ berr, BerrHost host,
                                                      const int32_t *gate) {
   if (gated(gate)) return;
   __shared__ double sh[kRows / 64];
@@ -251,6 +251,7 @@ __global__ void __launch_bounds__(kRows) k_berr_rows(int64_t nblk, int N,
   if (threadIdx.x == 0) {
     for (int w = 1; w < kRows / 64; ++w) be = nanmax(be, sh[w]);
     berr[0] = be;
+    host.store(be);
   }
 }
 
@@ -321,13 +322,15 @@ __global__ void __launch_bounds__(kRows) k_colmax(int64_t n, const double *__res
 
 // berr = max_c colstat_r / (anorm * colstat_x + colstat_b)   (Eq. 7 per column)
 __global__ void k_berr_final(int64_t nrhs, const double *__restrict__ colstat,
-                             const double *__restrict__ anorm, double *__restrict__ berr) {
+                             const double *__restrict__ anorm, double *__restrict__ berr,
+                             BerrHost host) {
   if (threadIdx.x != 0) return;
   const double a = anorm[0];
   double m = 0.0;
   for (int64_t c = 0; c < nrhs; ++c)
     m = nanmax(m, colstat[3 * c] / (a * colstat[3 * c + 1] + colstat[3 * c + 2]));
   berr[0] = m;
+  host.store(m);
 }
 
 __global__ void __launch_bounds__(kRows) k_axpy_cols(int64_t n, int64_t nrhs,
@@ -518,15 +521,15 @@ template <bool TRANS>
 hipError_t rows_residual(int64_t n, int64_t nrhs, const double *A, int64_t lda, const double *X,
                          int64_t ldx, const double *G, int64_t ldg, double *O, int64_t ldo,
                          bool with_anorm, double *blockstat, double *anorm, double *berr,
-                         hipStream_t s) {
+                         BerrHost host, hipStream_t s) {
   const int64_t blocks =
       with_anorm ? launch_rows_product<TRANS, true>(n, nrhs, A, lda, X, ldx, G, ldg, O, ldo, blockstat, s)
                  : launch_rows_product<TRANS, false>(n, nrhs, A, lda, X, ldx, G, ldg, O, ldo, blockstat, s);
   if (nrhs <= kSkinnyMax) {
     if (with_anorm)
-      hipLaunchKernelGGL((k_berr_rows<true>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, refine_gate());
+      hipLaunchKernelGGL((k_berr_rows<true>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, host, refine_gate());
     else
-      hipLaunchKernelGGL((k_berr_rows<false>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, refine_gate());
+      hipLaunchKernelGGL((k_berr_rows<false>), dim3(1), dim3(kRows), 0, s, blocks, int(nrhs), blockstat, anorm, berr, host, refine_gate());
   } else if (with_anorm) {
     hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(kRows), 0, s, blocks, blockstat, anorm);
   }
@@ -550,7 +553,7 @@ size_t resid_scratch_doubles(int64_t n, int64_t nrhs) {
 hipError_t launch_residual_berr(int64_t n, int64_t nrhs, const double *A, int64_t lda,
                                 const double *X, int64_t ldx, const double *B, int64_t ldb,
                                 double *R, int64_t ldr, bool with_anorm, double *scratch,
-                                double *anorm, double *berr, hipStream_t s) {
+                                double *anorm, double *berr, hipStream_t s, BerrHost host) {
   if (n <= 0 || nrhs <= 0) {
     hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, berr, 0.0);
     return hipGetLastError();
@@ -558,15 +561,15 @@ hipError_t launch_residual_berr(int64_t n, int64_t nrhs, const double *A, int64_
   const int64_t chunks = (n + kChunk - 1) / kChunk;
   const int64_t nblk = (n + kRows - 1) / kRows;
   if (nrhs <= kSkinnyMax)
-    return rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, s);
+    return rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, host, s);
   double *abspart = scratch;
   double *blockstat = abspart + chunks * n;
   double *colstat = blockstat + nblk * (3 * kSkinnyMax + 1);
   if (few_gemm_tiles(n, nrhs)) {
-    hipError_t e = rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, s);
+    hipError_t e = rows_residual<false>(n, nrhs, A, lda, X, ldx, B, ldb, R, ldr, with_anorm, scratch, anorm, berr, host, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_colmax, dim3(unsigned(nrhs)), dim3(kRows), 0, s, n, R, ldr, X, ldx, B, ldb, colstat);
-    hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr);
+    hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr, host);
     return hipGetLastError();
   }
   // wide: norms by their own pass, residual by the matrix-core GEMM
@@ -580,7 +583,7 @@ hipError_t launch_residual_berr(int64_t n, int64_t nrhs, const double *A, int64_
                               Acc::Subtract, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_colmax, dim3(unsigned(nrhs)), dim3(kRows), 0, s, n, R, ldr, X, ldx, B, ldb, colstat);
-  hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr);
+  hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr, host);
   return hipGetLastError();
 }
 
@@ -671,7 +674,7 @@ hipError_t launch_colscale(int64_t n, int N, const double *W, int64_t ldw, const
 hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int64_t lda,
                                   const double *L, int64_t ldl, const double *G, int64_t ldg,
                                   double *R, int64_t ldr, bool with_anorm, double *scratch,
-                                  double *anorm, double *berr, hipStream_t s) {
+                                  double *anorm, double *berr, hipStream_t s, BerrHost host) {
   if (n <= 0 || nrhs <= 0) {
     hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, berr, 0.0);
     return hipGetLastError();
@@ -679,9 +682,9 @@ hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int6
   double *colabs = scratch;
   double *colstat = scratch + n;
   if (nrhs <= kSkinnyMax)
-    return rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, s);
+    return rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, host, s);
   if (few_gemm_tiles(n, nrhs)) {
-    hipError_t e = rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, s);
+    hipError_t e = rows_residual<true>(n, nrhs, A, lda, L, ldl, G, ldg, R, ldr, with_anorm, scratch, anorm, berr, host, s);
     if (e != hipSuccess) return e;
   } else {
     if (with_anorm) {
@@ -695,7 +698,7 @@ hipError_t launch_residual_berr_T(int64_t n, int64_t nrhs, const double *A, int6
   }
   hipLaunchKernelGGL(k_colmax, dim3(unsigned(nrhs)), dim3(kRows), 0, s, n, R, ldr, L, ldl, G, ldg,
                      colstat);
-  hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr);
+  hipLaunchKernelGGL(k_berr_final, dim3(1), dim3(64), 0, s, nrhs, colstat, anorm, berr, host);
   return hipGetLastError();
 }
 

@@ -11,7 +11,7 @@
 // each wait, so the loads overlap it.
 //
 // Publication: every solution entry carries its own readiness. Before the
-// sweep the launcher fills a publication buffer P (n x nrhs, in the sync
+// sweep (for up to 8 right-hand sides, before the two of a solve) the launcher fills a publication buffer P (n x nrhs, in the sync
 // area) with a signalling-NaN pattern that no arithmetic produces; a
 // workgroup publishes x_b by storing its entries into P with agent-scope
 // atomic stores (and into B, the output), and a workgroup that needs x_j
@@ -320,7 +320,8 @@ template <int NT, TriMode MODE, typename TF, bool REFINE, typename C>
 __global__ void __launch_bounds__(TPB)
     k_sweep(int64_t n, int64_t nrhs, const TF *__restrict__ A, int64_t ld,
             const C *__restrict__ Winv, double *B, int64_t ldb, int32_t *sync, double *P,
-            int64_t nb, int groups, int width, int64_t spin_limit, const int32_t *gate) {
+            int64_t nb, int groups, int width, int ticket_word, int64_t spin_limit,
+            const int32_t *gate) {
   // (the gate is read before any ticket is taken: every workgroup of a gated
   // launch returns here)
   if (gated(gate)) return;
@@ -339,7 +340,7 @@ __global__ void __launch_bounds__(TPB)
   const int sl = Pr::sl(lane);
   const int i = 16 * wave + Pr::rl(lane);  // the lane's row as an operand
   if (tid == 0) {
-    tk = atomicAdd(&sync[0], 1);
+    tk = atomicAdd(&sync[ticket_word], 1);
     expired_sh = 0;
   }
   for (int e = tid; e < 2 * kNB * XN; e += TPB) xs[0][e] = C(0);  // unused columns stay zero
@@ -512,8 +513,8 @@ __global__ void __launch_bounds__(TPB)
   }
 }
 
-// Before a sweep: ticket and legacy words cleared, P (count entries) set to
-// the unpublished pattern.
+// Before a sweep, or the two of a solve: tickets cleared, P (count entries) set
+// to the unpublished pattern.
 __global__ void k_sweep_reset(int32_t *sync, double *P, int64_t count) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g < 3) sync[g] = 0;
@@ -523,7 +524,7 @@ __global__ void k_sweep_reset(int32_t *sync, double *P, int64_t count) {
 
 template <int NT, TriMode MODE, typename TF, typename C>
 hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *Winv, double *B,
-                   int64_t ldb, int32_t *sync, double *P, hipStream_t s) {
+                   int64_t ldb, int32_t *sync, double *P, SweepOf of, hipStream_t s) {
   // one refinement step per diagonal block for FP64 factors and for FP32
   // arithmetic (a product with an explicit FP32 inverse alone is accurate to
   // kappa(block) u32 only); FP64 arithmetic on FP32 factors needs none
@@ -532,25 +533,31 @@ hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *W
   const int64_t width = nrhs < NT ? nrhs : NT;  // right-hand sides per group
   const int64_t groups = (nrhs + width - 1) / width;
   if (nb * groups > 0x7fffffff) return hipErrorInvalidValue;
-  // ticket and legacy words, and P; the sticky error word sync[3] is left alone
+  // the tickets and P; the sticky error word sync[3] is left alone
   const int64_t count = n * nrhs;
-  const int64_t blocks = (count + 255) / 256 < 1024 ? (count + 255) / 256 : 1024;
-  hipLaunchKernelGGL(k_sweep_reset, dim3(unsigned(blocks < 1 ? 1 : blocks)), dim3(256), 0, s, sync,
-                     P, count);
+  if (of != SweepOf::Second) {
+    const int64_t entries = of == SweepOf::First ? 2 * count : count;
+    const int64_t blocks = (entries + 255) / 256 < 1024 ? (entries + 255) / 256 : 1024;
+    hipLaunchKernelGGL(k_sweep_reset, dim3(unsigned(blocks < 1 ? 1 : blocks)), dim3(256), 0, s,
+                       sync, P, entries);
+  } else {
+    P += count;
+  }
   hipLaunchKernelGGL((k_sweep<NT, MODE, TF, REFINE, C>), dim3(unsigned(nb * groups)), dim3(TPB), 0,
                      s, n, nrhs, LU, ld, Winv, B, ldb, sync, P, nb, int(groups),
-                     int(width), sweep_spin_limit(), refine_gate());
+                     int(width), of == SweepOf::Second ? 1 : 0, sweep_spin_limit(), refine_gate());
   return hipGetLastError();
 }
 
 template <int NT, typename TF, typename C>
 hipError_t sweep_n(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *Winv,
-                   double *B, int64_t ldb, int32_t *sync, double *P, hipStream_t s) {
+                   double *B, int64_t ldb, int32_t *sync, double *P, SweepOf of,
+                   hipStream_t s) {
   switch (mode) {
-    case TriMode::LN: return sweep_t<NT, TriMode::LN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
-    case TriMode::UN: return sweep_t<NT, TriMode::UN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
-    case TriMode::UT: return sweep_t<NT, TriMode::UT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
-    default: return sweep_t<NT, TriMode::LT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    case TriMode::LN: return sweep_t<NT, TriMode::LN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
+    case TriMode::UN: return sweep_t<NT, TriMode::UN>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
+    case TriMode::UT: return sweep_t<NT, TriMode::UT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
+    default: return sweep_t<NT, TriMode::LT>(n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
   }
 }
 
@@ -587,21 +594,22 @@ int group_width(int64_t n, int64_t nrhs) {
 template <typename TF, typename C>
 hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_t ld,
                      const C *Winv, double *B, int64_t ldb, int32_t *sync, double *P,
-                     hipStream_t s) {
+                     SweepOf of, hipStream_t s) {
   if (n <= 0 || nrhs <= 0) return hipSuccess;
   if (sync == nullptr) return hipErrorInvalidValue;
+  if (P != nullptr || nrhs > kSkinnyMax / 2) of = SweepOf::Alone;  // room for one only
   if (P == nullptr) {
     if (nrhs > kSkinnyMax) return hipErrorInvalidValue;
     P = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
   }
-  if (nrhs == 1) return sweep_n<1>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+  if (nrhs == 1) return sweep_n<1>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
   switch (group_width<TF, C>(n, nrhs)) {
-    case 4: return sweep_n<4>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    case 4: return sweep_n<4>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
     case 8:
       if constexpr (std::is_same<C, double>::value)
-        return sweep_n<8>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+        return sweep_n<8>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
       [[fallthrough]];
-    default: return sweep_n<16>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, s);
+    default: return sweep_n<16>(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, P, of, s);
   }
 }
 
@@ -609,18 +617,18 @@ hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_
 
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const double *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s, double *pub) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
+                        hipStream_t s, double *pub, SweepOf of) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, of, s);
 }
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const double *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s, double *pub) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
+                        hipStream_t s, double *pub, SweepOf of) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, of, s);
 }
 hipError_t launch_sweep(TriMode mode, int64_t n, int64_t nrhs, const float *LU, int64_t ld,
                         const float *Winv, double *B, int64_t ldb, int32_t *sync,
-                        hipStream_t s, double *pub) {
-  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, s);
+                        hipStream_t s, double *pub, SweepOf of) {
+  return sweep_any(mode, n, nrhs, LU, ld, Winv, B, ldb, sync, pub, of, s);
 }
 
 }  // namespace rbt
