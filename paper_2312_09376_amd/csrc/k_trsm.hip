@@ -154,21 +154,16 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
   C *strip = sm.strip[wave];  // row-major 128 x 16
   const int64_t col0 = bx * 64 + wave * 16;
 
-  {  // stage the diagonal blocks and the off-diagonal operands, coalesced:
-     // consecutive threads read consecutive addresses of the stored T
+  TB sraw[BATCH ? 1 : 2][IB];  // the strip
+  {  // stage the diagonal blocks and the off-diagonal operands, coalesced
+     // (consecutive threads read consecutive addresses of the stored T), and the
+     // strip: all loads are in flight before the first store waits
     const int f = threadIdx.x & 15, g = threadIdx.x >> 4;
     const int i = TRANS ? g : f, j = TRANS ? f : g;  // element (i, j) of a block of op(T)
     TT raw[NBK];
 #pragma unroll
     for (int b = 0; b < NBK; ++b)
       raw[b] = op_t<MODE>(T, ldt, clampi(IB * b + i, kb - 1), clampi(IB * b + j, kb - 1));
-#pragma unroll
-    for (int b = 0; b < NBK; ++b) {
-      const int gi = IB * b + i, gj = IB * b + j;
-      const C v = (gi < kb && gj < kb) ? C(raw[b]) : (i == j ? C(1) : C(0));
-      if (!unit_diag<MODE>() && i == j) sm.drec[gi] = C(1) / v;
-      dblk[b * BLK + j * IB + i] = (FWD ? i > j : i < j) ? -v : C(0);
-    }
     TT oraw[NOFF];
 #pragma unroll
     for (int p = 0, I = 1; I < NBK; ++I)
@@ -178,6 +173,23 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
         const int bi = FWD ? I : J, bj = FWD ? J : I;
         oraw[p] = op_t<MODE>(T, ldt, clampi(IB * bi + i, kb - 1), clampi(IB * bj + j, kb - 1));
       }
+    if constexpr (!BATCH) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t rr = clampi(lane + 64 * h, kb - 1);
+#pragma unroll
+        for (int cc = 0; cc < IB; ++cc)
+          sraw[h][cc] = B[rr + (col0 + cc < N ? col0 + cc : N - 1) * ldb];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) {
+      const int gi = IB * b + i, gj = IB * b + j;
+      const C v = (gi < kb && gj < kb) ? C(raw[b]) : (i == j ? C(1) : C(0));
+      if (!unit_diag<MODE>() && i == j) sm.drec[gi] = C(1) / v;
+      dblk[b * BLK + j * IB + i] = (FWD ? i > j : i < j) ? -v : C(0);
+    }
     const int slot = (16 * (j & 3) + i) * 4 + (j >> 2);  // lane (lk = j%4, l16 = i), kk = j/4
 #pragma unroll
     for (int p = 0, I = 1; I < NBK; ++I)
@@ -191,23 +203,13 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
 #pragma unroll
   for (int h = 0; h < 2; ++h) {  // strip: lane = row (two halves), 16 columns
     const int row = lane + 64 * h;
-    if constexpr (BATCH) {
 #pragma unroll
-      for (int c = 0; c < IB; ++c) {
-        const int64_t col = col0 + c;
+    for (int c = 0; c < IB; ++c) {
+      const int64_t col = col0 + c;
+      if constexpr (BATCH)
         strip[row * SLD + c] = (row < kb && col < N && row == col) ? C(1) : C(0);
-      }
-    } else {
-      TB raw[IB];
-      const int64_t rr = clampi(row, kb - 1);
-#pragma unroll
-      for (int c = 0; c < IB; ++c) {
-        const int64_t col = col0 + c < N ? col0 + c : N - 1;
-        raw[c] = B[rr + col * ldb];
-      }
-#pragma unroll
-      for (int c = 0; c < IB; ++c)
-        strip[row * SLD + c] = (row < kb && col0 + c < N) ? C(raw[c]) : C(0);
+      else
+        strip[row * SLD + c] = (row < kb && col < N) ? C(sraw[h][c]) : C(0);
     }
   }
   __syncthreads();
@@ -258,12 +260,11 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
   }
 }
 
-template <TriMode MODE, bool BATCH, typename TT, typename TB, typename C>
+template <TriMode MODE, typename TT, typename TB, typename C>
 __global__ void __launch_bounds__(256, 1) k_trsm_left(int kb, int64_t N, const TT *T,
-                                                      int64_t ldt, TB *B, int64_t ldb,
-                                                      int64_t n, int64_t bstride) {
+                                                      int64_t ldt, TB *B, int64_t ldb) {
   __shared__ TrsmSmem<C> sm;
-  trsm_left_body<MODE, BATCH, TT, TB, C>(kb, N, T, ldt, B, ldb, n, bstride,
+  trsm_left_body<MODE, false, TT, TB, C>(kb, N, T, ldt, B, ldb, int64_t(0), int64_t(0),
                                          int64_t(blockIdx.x), sm);
 }
 
@@ -285,12 +286,27 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
   C *strip = sm.strip[wave];  // column-major 16 x 128
   const int64_t row0 = bx * 64 + wave * 16;
 
-  {  // stage the triangle, consecutive threads on consecutive rows of U
+  {  // stage the triangle, consecutive threads on consecutive rows of U, and the
+     // strip (lane = row sr, column group cg: columns cg + 4 u): all loads are in
+     // flight before the first store waits
     const int r = threadIdx.x % IB, c = threadIdx.x / IB;
     TT raw[NBK];
 #pragma unroll
     for (int b = 0; b < NBK; ++b)
       raw[b] = T[clampi(IB * b + r, kb - 1) + int64_t(clampi(IB * b + c, kb - 1)) * ldt];
+    TT uraw[NOFF];
+#pragma unroll
+    for (int p = 0, J = 1; J < NBK; ++J)
+#pragma unroll
+      for (int I = 0; I < J; ++I, ++p)
+        uraw[p] = T[clampi(IB * I + r, kb - 1) + int64_t(clampi(IB * J + c, kb - 1)) * ldt];
+    const int sr = lane % IB, cg = lane / IB;
+    const int64_t row = row0 + sr;
+    const int64_t rr = row < M ? row : M - 1;
+    TT sraw[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) sraw[u] = B[rr + int64_t(clampi(cg + 4 * u, kb - 1)) * ldb];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int b = 0; b < NBK; ++b) {
       const int gi = IB * b + r, gj = IB * b + c;
@@ -298,12 +314,6 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
       if (r == c) sm.drec[gi] = C(1) / v;
       dblk[b * BLK + r * IB + c] = r < c ? -v : C(0);
     }
-    TT uraw[NOFF];
-#pragma unroll
-    for (int p = 0, J = 1; J < NBK; ++J)
-#pragma unroll
-      for (int I = 0; I < J; ++I, ++p)
-        uraw[p] = T[clampi(IB * I + r, kb - 1) + int64_t(clampi(IB * J + c, kb - 1)) * ldt];
     const int slot = (16 * (r & 3) + c) * 4 + (r >> 2);  // lane (lk = r%4, l16 = c), kk = r/4
 #pragma unroll
     for (int p = 0, J = 1; J < NBK; ++J)
@@ -312,23 +322,10 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
         const int gi = IB * I + r, gj = IB * J + c;
         ublk[p * BLK + slot] = (gi < kb && gj < kb) ? C(uraw[p]) : C(0);
       }
-  }
-  {
-    // lane = (row r = lane % 16, column group lane / 16): columns cg + 4u
-    const int r = lane % IB, cg = lane / IB;
-    const int64_t row = row0 + r;
-    const int64_t rr = row < M ? row : M - 1;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      TT raw[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        raw[u] = B[rr + int64_t(clampi(cg + 4 * (16 * h + u), kb - 1)) * ldb];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int c = cg + 4 * (16 * h + u);
-        strip[c * SLD + r] = (row < M && c < kb) ? C(raw[u]) : C(0);
-      }
+    for (int u = 0; u < 32; ++u) {
+      const int cu = cg + 4 * u;
+      strip[cu * SLD + sr] = (row < M && cu < kb) ? C(sraw[u]) : C(0);
     }
   }
   __syncthreads();
@@ -401,18 +398,32 @@ __global__ void __launch_bounds__(256, 1) k_panel_trsm(int kb, int64_t M, int64_
                                                   int64_t(0), bx - gr, sm);
 }
 
+// Inverses of the diagonal blocks of L (blockIdx.z = 0) and of U, 64 of their
+// columns per workgroup: one launch, the two side by side (n = 1000: 17 us, as two
+// launches 29).
+template <typename TT, typename C>
+__global__ void __launch_bounds__(256, 1) k_diag_inverses(int64_t n, const TT *LU, int64_t ld, C *W) {
+  __shared__ TrsmSmem<C> sm;
+  // L^-1 at W + b * 2 kNB^2, U^-1 at W + b * 2 kNB^2 + kNB^2, each ld kNB
+  if (blockIdx.z == 0)
+    trsm_left_body<TriMode::LN, true, TT, C, C>(NB, int64_t(NB), LU, ld, W, int64_t(NB), n,
+                                                int64_t(2 * NB * NB), int64_t(blockIdx.x), sm);
+  else
+    trsm_left_body<TriMode::UN, true, TT, C, C>(NB, int64_t(NB), LU, ld, W + NB * NB, int64_t(NB),
+                                                n, int64_t(2 * NB * NB), int64_t(blockIdx.x), sm);
+}
+
 template <typename TT, typename TB, typename C>
 hipError_t trsm_left_t(TriMode mode, int kb, int64_t N, const TT *T, int64_t ldt, TB *B,
                        int64_t ldb, hipStream_t s) {
   if (kb <= 0 || N <= 0) return hipSuccess;
   if (kb > kNB) return hipErrorInvalidValue;
   const dim3 grid(unsigned((N + 63) / 64));
-  const int64_t z = 0;
   switch (mode) {
-    case TriMode::LN: hipLaunchKernelGGL((k_trsm_left<TriMode::LN, false, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb, z, z); break;
-    case TriMode::UN: hipLaunchKernelGGL((k_trsm_left<TriMode::UN, false, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb, z, z); break;
-    case TriMode::UT: hipLaunchKernelGGL((k_trsm_left<TriMode::UT, false, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb, z, z); break;
-    case TriMode::LT: hipLaunchKernelGGL((k_trsm_left<TriMode::LT, false, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb, z, z); break;
+    case TriMode::LN: hipLaunchKernelGGL((k_trsm_left<TriMode::LN, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb); break;
+    case TriMode::UN: hipLaunchKernelGGL((k_trsm_left<TriMode::UN, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb); break;
+    case TriMode::UT: hipLaunchKernelGGL((k_trsm_left<TriMode::UT, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb); break;
+    case TriMode::LT: hipLaunchKernelGGL((k_trsm_left<TriMode::LT, TT, TB, C>), grid, dim3(256), 0, s, kb, N, T, ldt, B, ldb); break;
   }
   return hipGetLastError();
 }
@@ -423,12 +434,9 @@ hipError_t diag_inverses_t(int64_t n, const TT *LU, int64_t ld, C *W, hipStream_
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + NB - 1) / NB;
   if (nb > 65535) return hipErrorInvalidValue;
-  const dim3 grid(2, unsigned(nb));  // 2 x 64 columns of each 128 x 128 block
-  // L^-1 at W + b * 2 kNB^2, U^-1 at W + b * 2 kNB^2 + kNB^2, each ld kNB
-  hipLaunchKernelGGL((k_trsm_left<TriMode::LN, true, TT, C, C>), grid, dim3(256), 0, s, NB,
-                     int64_t(NB), LU, ld, W, int64_t(NB), n, int64_t(2 * NB * NB));
-  hipLaunchKernelGGL((k_trsm_left<TriMode::UN, true, TT, C, C>), grid, dim3(256), 0, s, NB,
-                     int64_t(NB), LU, ld, W + NB * NB, int64_t(NB), n, int64_t(2 * NB * NB));
+  // 2 x 64 columns of each 128 x 128 block
+  hipLaunchKernelGGL((k_diag_inverses<TT, C>), dim3(2, unsigned(nb), 2), dim3(256), 0, s, n, LU, ld,
+                     W);
   return hipGetLastError();
 }
 
