@@ -152,8 +152,10 @@ int rbt_genp(int64_t n, double *A, int64_t lda, int32_t *info_dev, void *stream)
 /* Device. Solve with the factors of rbt_genp: trans = 0: B <- (L U)^-1 B;
  * trans = 1: B <- (L U)^-T B. B: n x nrhs FP64 (ldb), in place.
  * work: device scratch of rbt_workspace_size(n, nrhs, 0, RBT_FP64) bytes
- * (for nrhs <= 16 it receives the inverses of the 128 x 128 diagonal blocks,
- * which the solve applies with one step of refinement per block). */
+ * (for nrhs <= 384 it receives the inverses of the 128 x 128 diagonal blocks,
+ * which the solve applies with one step of refinement per block; for 17 to
+ * 384 a workspace that ends with the sweeps' area is accepted and takes block
+ * solves). */
 int rbt_getrs(int64_t n, int64_t nrhs, const double *LU, int64_t ldlu, double *B, int64_t ldb,
               int trans, void *work, size_t work_bytes, void *stream);
 
@@ -287,7 +289,10 @@ int rbt_solve_mixed_guarded(int64_t n, int64_t nrhs, const double *A, int64_t ld
  * nullable): 0, or the first column k (1-based) whose pivot candidates were
  * all exactly zero (left unswapped; the elimination goes on with IEEE
  * Inf/NaN). This is the robust solver that the fallback of Sec. 5 re-solves
- * with. work: >= rbt_workspace_size(n, 0, 0, RBT_FP64) bytes. */
+ * with. Up to n = 32768 it factors 32 columns per launch, whose workgroups
+ * exchange the pivots through work with bounded waits (a wait that expires
+ * makes the columns NaN); beyond, column by column. work: >=
+ * rbt_workspace_size(n, 0, 0, RBT_FP64) bytes. */
 int rbt_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv_dev, int32_t *info_dev, void *work,
              size_t work_bytes, void *stream);
 
@@ -329,7 +334,7 @@ int rbt_solve_guarded(int64_t n, int64_t nrhs, const double *A, int64_t lda, dou
  * <= RBT_MAX_DEPTH, prec RBT_FP32 or RBT_BF16; 0 for invalid arguments. About
  * 12 n^2 + 8 (2 n d + 64^2 ceil(n/64) + n nrhs) bytes per system (FP32
  * factors, FP64 factors of the fallback, coefficients, inverse blocks,
- * residual). */
+ * residual) and up to 3.2 KB for systems of order 512 and more. */
 size_t rbt_batched_workspace_size(int64_t batch, const int64_t *n, const int64_t *nrhs, int depth,
                                   int prec);
 
@@ -338,7 +343,9 @@ size_t rbt_batched_workspace_size(int64_t batch, const int64_t *n, const int64_t
  * bytes); synchronizes `stream`. Call once per set of sizes; the plan stays
  * valid for any number of rbt_solve_batched calls with the same batch,
  * depth and prec. nrhs[s] > 16: RBT_ERR_UNSUPPORTED. Each system's
- * transforms run in passes of at most three layers. */
+ * transforms run in passes of at most three layers. Systems of order 512 and
+ * more that cost more than their share of the batch are planned for teams of
+ * 2, 4 or 8 workgroups (their results do not depend on it). */
 int rbt_batched_plan(int64_t batch, const int64_t *n, const int64_t *nrhs, int depth, int prec,
                      void *work, size_t work_bytes, void *stream);
 

@@ -538,11 +538,11 @@ int genp_fp64(int64_t n, double *A, int64_t lda, int32_t *info, hipStream_t s) {
 // Right-hand sides of FP64 factors that are solved by sweeps: up to kSkinnyMax
 // always, up to kSweepWide where the caller has a publication buffer of
 // n * nrhs doubles for them (pub). A sweep costs its chain of blocks, whatever
-// the number of groups of 16, until the groups' reads of the factors outweigh
-// it; the block solves cost two launches per block and grow little with nrhs.
-// Sweeps / block solves, both directions of one solve, in ms: n = 5003 1.07 / 2.13
-// (64) and 1.35 / 2.38 (384); n = 20000 5.07 / 9.56 (64), 9.8 / 12.4 (256), 13.8 / 14.4
-// (384) and 18.4 / 16.3 (512 right-hand sides).
+// the number of groups, until the groups' reads of the factors outweigh it; the
+// block solves cost two launches per block and grow little with nrhs. Sweeps /
+// block solves, both directions of one solve, in ms: n = 5003 0.61 / 2.13 (64) and
+// 1.34 / 2.38 (384); n = 20000 5.08 / 9.56 (64), 9.8 / 12.4 (256), 13.9 / 14.4 (384) and
+// 18.4 / 16.3 (512 right-hand sides).
 constexpr int64_t kSweepWide = 384;
 bool by_sweeps(int64_t nrhs, const double *pub) {
   return nrhs <= kSkinnyMax || (nrhs <= kSweepWide && pub != nullptr);
@@ -670,10 +670,9 @@ int diag_inverses_t(int64_t n, const float *LU, int64_t ld, double *winv, bool f
   return 0;
 }
 // B <- (LU)^-1 B or (LU)^-T B with FP32 factors and FP64 right-hand sides:
-// sweeps, groups of kSkinnyMax columns side by side in one launch where the
-// caller has a publication buffer of n * nrhs doubles (pub), else one after
-// another, in FP32 arithmetic (the
-// right-hand side rounded to FP32 on load, the result widened on store), or
+// sweeps, all columns in one launch where the caller has a publication buffer
+// of n * nrhs doubles (pub), else kSkinnyMax after another, in FP32 arithmetic
+// (the right-hand side rounded to FP32 on load, the result widened on store), or
 // in FP64 arithmetic (f64: the FP64-inner option, and the preconditioner of
 // GMRES-IR, which that method applies in the working precision). The
 // inverses must have been formed by diag_inverses_t with the same f64.

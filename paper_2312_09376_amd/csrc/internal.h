@@ -201,17 +201,18 @@ hipError_t launch_diag_inverses(int64_t n, const float *LU, int64_t ld, float *W
 inline int64_t diag_inv_doubles(int64_t n) { return ((n + kNB - 1) / kNB) * 2 * kNB * kNB; }
 
 // k_solve.hip
-constexpr int64_t kSkinnyMax = 16;  // right-hand sides handled by the sweeps and FMA kernels
-// k_sweep.hip : triangular sweep with op(A) of the factors for
-// nrhs <= kSkinnyMax, using the diagonal-block inverses of
+constexpr int64_t kSkinnyMax = 16;  // right-hand sides of a sweep without a buffer, and of a batched system
+// k_sweep.hip : triangular sweep with op(A) of the factors, using the
+// diagonal-block inverses of
 // launch_diag_inverses, as ONE persistent launch (ticket-ordered block rows,
 // each block's solution published entry by entry). sync:
-// sweep_sync_ints(n) int32 of device scratch: words 0..2 are cleared by each
-// launch (word 0: the ticket), word 3 is the sticky error word (set when a
+// sweep_sync_ints(n) int32 of device scratch: words 0..2 are cleared before a
+// sweep or the two of a solve (words 0 and 1: their tickets), word 3 is the
+// sticky error word (set when a
 // bounded wait expired; the block's solution is then NaN), which the caller
 // clears (kSweepErrWord) and reads back; from word 64 (256 bytes) the
-// publication buffer, n x kSkinnyMax doubles, reset by each launch.
-// FP64 factors take one refinement step per diagonal block, FP32 factors
+// publication buffer, n x kSkinnyMax doubles. FP64 factors and FP32 arithmetic
+// take one refinement step per diagonal block, FP64 arithmetic on FP32 factors
 // the inverse alone.
 inline int64_t sweep_sync_ints(int64_t n) { return 64 + 2 * kSkinnyMax * n; }
 constexpr int kSweepErrWord = 3;
