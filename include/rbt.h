@@ -464,7 +464,7 @@ int rbt_solve_backward_mixed(int64_t n, int64_t nrhs, const float *LU, int64_t l
  *   wait of a persistent triangular sweep may take before it expires
  *   (default 2^20). A negative value makes every wait expire at once: a
  *   host-side way to exercise the RBT_ERR_SYNC path in tests (every kernel
- *   still exits normally). */
+ *   still exits normally). 16 times as many for an exchange of rbt_gepp. */
 #define RBT_OPT_SWEEP_SPIN_LIMIT 6
 /* RBT_OPT_MIXED_FP64_INNER: low-precision elimination and solves
  *   (rbt_solve_mixed, rbt_solve_mixed_guarded, rbt_solve_backward_mixed).

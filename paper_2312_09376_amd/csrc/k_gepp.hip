@@ -151,9 +151,10 @@ __global__ void __launch_bounds__(TPB)
 // resident. A hardware queue dispatches in order, so each of a process's (four
 // by default) holds at most one launch that is only partly resident, and
 // kSlabGroups = 32 workgroups for each are 128, half of what the 256 CUs hold at
-// one per CU. The wait is bounded all the same (spin_limit sleeps): a
-// workgroup whose wait expires sets *err (nullable) and stores NaN into its
-// rows, so the factors are never silently wrong.
+// one per CU. The wait is bounded all the same, by 16 times a sweep's spin limit
+// (some 16 s by default: a workgroup may first have to wait for kernels of other
+// streams to leave its CU): a workgroup whose wait expires sets *err (nullable)
+// and stores NaN into its rows, so the factors are never silently wrong.
 //
 // The column loop is unrolled over 8 columns only (32 copies of its body would
 // not fit the instruction cache): after 8 columns the 32 registers of a row
@@ -612,7 +613,8 @@ hipError_t launch_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv, int32_t
         if (groups > 1 && !fresh)
           hipLaunchKernelGGL(k_slab_reset, dim3(64), dim3(TPB), 0, s, pub, count);
         const dim3 grid{unsigned(groups)}, block{kSlabThreads};
-        const int64_t spin = sweep_spin_limit();
+        const int64_t limit = sweep_spin_limit();
+        const int64_t spin = limit > 0 && limit < INT64_MAX / 16 ? 16 * limit : limit;
         if (rpt == 1)
           hipLaunchKernelGGL((k_gepp_slab<1>), grid, block, 0, s, n, A, lda, k, w, groups, pub,
                              ipiv, info, spin, err);
