@@ -553,13 +553,14 @@ bool by_sweeps(int64_t nrhs, const double *pub) {
 // diagonal blocks (k_trsm.hip) and updates of the remaining rows by the
 // matrix-core GEMM.
 int getrs_fp64(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-               int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s) {
+               int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s,
+               SweepOf first = SweepOf::First) {
   if (n == 0 || nrhs == 0) return 0;
   if (by_sweeps(nrhs, pub)) {
     // one persistent launch per sweep: inverse + one refinement step per block
     double *P = nrhs <= kSkinnyMax ? nullptr : pub;
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::UT : TriMode::LN, n, nrhs, LU, ld, winv, B, ldb,
-                               sync, s, P, SweepOf::First));
+                               sync, s, P, first));
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::LT : TriMode::UN, n, nrhs, LU, ld, winv, B, ldb,
                                sync, s, P, SweepOf::Second));
     return 0;
@@ -620,9 +621,10 @@ hipError_t transform2_t(const Geometry &g, const double *A, int64_t lda, void *o
 }
 // Out = op(C) In; Out += op(C) In (which overwrites In).
 hipError_t transform_vec_t(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
-                           double *Out, int64_t ldo, const double *C, int op, hipStream_t s) {
+                           double *Out, int64_t ldo, const double *C, int op, hipStream_t s,
+                           SweepPrep prep = {}) {
   StageScope t(kStageTransformVec, s, 16.0 * double(g.n) * nrhs);
-  return launch_transform_vec(g, nrhs, In, ldi, Out, ldo, C, op, s);
+  return launch_transform_vec(g, nrhs, In, ldi, Out, ldo, C, op, s, prep);
 }
 hipError_t transform_vec_add_t(const Geometry &g, int64_t nrhs, double *In, int64_t ldi,
                                double *Out, int64_t ldo, const double *C, int op, hipStream_t s) {
@@ -642,9 +644,10 @@ hipError_t transform_v_add_t(const Geometry &g, int64_t nrhs, double *In, int64_
   return launch_axpy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
 }
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s) {
+            int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s,
+            SweepOf first = SweepOf::First) {
   StageScope t(kStageSolve, s, 2.0 * double(n) * n * nrhs);
-  return getrs_fp64(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s);
+  return getrs_fp64(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s, first);
 }
 // Inverses of the diagonal blocks, needed by the solves by sweeps.
 int diag_inverses_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *winv,
@@ -677,7 +680,8 @@ int diag_inverses_t(int64_t n, const float *LU, int64_t ld, double *winv, bool f
 // GMRES-IR, which that method applies in the working precision). The
 // inverses must have been formed by diag_inverses_t with the same f64.
 int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, double *pub, bool f64, hipStream_t s) {
+            int trans, const double *winv, int32_t *sync, double *pub, bool f64, hipStream_t s,
+            SweepOf first = SweepOf::First) {
   StageScope t(kStageSolve, s, 2.0 * double(n) * n * nrhs);
   const float *winv32 = reinterpret_cast<const float *>(winv);
   const int64_t step = pub != nullptr && nrhs > kSkinnyMax ? nrhs : kSkinnyMax;
@@ -688,7 +692,7 @@ int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int
     for (int pass = 0; pass < 2; ++pass) {
       const TriMode m = pass == 0 ? (trans ? TriMode::UT : TriMode::LN)
                                   : (trans ? TriMode::LT : TriMode::UN);
-      const SweepOf of = pass == 0 ? SweepOf::First : SweepOf::Second;
+      const SweepOf of = pass == 0 ? first : SweepOf::Second;
       if (f64)
         RBT_HIP_CHECK(launch_sweep(m, n, nc, LU, ld, winv, Bc, ldb, sync, s, P, of));
       else
@@ -699,9 +703,9 @@ int getrs_t(int64_t n, int64_t nrhs, const float *LU, int64_t ld, double *B, int
 }
 
 int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, int64_t ldb,
-            int trans, const double *winv, int32_t *sync, double *pub, bool /*f64*/,
-            hipStream_t s) {
-  return getrs_t(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s);
+            int trans, const double *winv, int32_t *sync, double *pub, bool /*f64*/, hipStream_t s,
+            SweepOf first = SweepOf::First) {
+  return getrs_t(n, nrhs, LU, ld, B, ldb, trans, winv, sync, pub, s, first);
 }
 // R <- V (L U)^-1 U^T S, the solve of Eq. 1 with the factors of A~ (S may be R;
 // f64: arithmetic of the triangular solves with FP32 factors, see getrs_t), or
@@ -711,8 +715,15 @@ int apply_solve(const Geometry &g, int64_t nrhs, const TF *LU, int64_t ld, const
                 int64_t lds, double *R, int64_t ldr, const double *U, const double *V,
                 const double *winv, int32_t *sync, double *pub, bool f64, hipStream_t s,
                 double *X = nullptr, int64_t ldx = 0) {
-  RBT_HIP_CHECK(transform_vec_t(g, nrhs, S, lds, R, ldr, U, RBT_OP_T, s));
-  const int rc = getrs_t(g.n, nrhs, LU, ld, R, ldr, 0, winv, sync, pub, f64, s);
+  // the transform's kernel also prepares the two sweeps where they take the
+  // sync area's publications (at depth 0 there is none)
+  const bool prep = g.d > 0 && nrhs <= kSweepPairMax;
+  RBT_HIP_CHECK(transform_vec_t(
+      g, nrhs, S, lds, R, ldr, U, RBT_OP_T, s,
+      prep ? SweepPrep{sync, reinterpret_cast<double *>(sync + kSyncPubOffsetInts), 2 * g.n * nrhs}
+           : SweepPrep{}));
+  const int rc = getrs_t(g.n, nrhs, LU, ld, R, ldr, 0, winv, sync, pub, f64, s,
+                         prep ? SweepOf::Prepared : SweepOf::First);
   if (rc) return rc;
   if (X != nullptr)
     RBT_HIP_CHECK(transform_v_add_t(g, nrhs, R, ldr, X, ldx, V, RBT_OP_N, s));

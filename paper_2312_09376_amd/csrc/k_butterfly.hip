@@ -75,9 +75,10 @@ template <int P, int OP, bool ADD>
 __global__ void __launch_bounds__(256) k_transform_vec(const double *In, int64_t ldi, double *Out,
                                                        int64_t ldo, int64_t nrhs,
                                                        const double *__restrict__ C, Pass ps,
-                                                       const int32_t *gate) {
+                                                       SweepPrep prep, const int32_t *gate) {
   if (gated(gate)) return;
   const int64_t gr = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  prep.run(int64_t(blockIdx.y) * gridDim.x * 256 + gr, int64_t(gridDim.x) * gridDim.y * 256);
   if (gr >= ps.ngroups) return;
   const int64_t rb = group_base(ps, gr);
   if (rb >= ps.n) return;
@@ -106,13 +107,13 @@ hipError_t launch_pass2(const Pass &ps, const TI *A, int64_t lda, TO *out, int64
 
 template <int OP, bool ADD>
 hipError_t launch_pass_vec(const Pass &ps, const double *In, int64_t ldi, double *Out, int64_t ldo,
-                           int64_t nrhs, const double *C, hipStream_t s) {
+                           int64_t nrhs, const double *C, SweepPrep prep, hipStream_t s) {
   const int P = ps.hi - ps.lo + 1;
   dim3 grid(unsigned((ps.ngroups + 255) / 256), unsigned(nrhs < 65535 ? nrhs : 65535));
   switch (P) {
-    case 1: hipLaunchKernelGGL((k_transform_vec<1, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
-    case 2: hipLaunchKernelGGL((k_transform_vec<2, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
-    default: hipLaunchKernelGGL((k_transform_vec<3, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, refine_gate()); break;
+    case 1: hipLaunchKernelGGL((k_transform_vec<1, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, prep, refine_gate()); break;
+    case 2: hipLaunchKernelGGL((k_transform_vec<2, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, prep, refine_gate()); break;
+    default: hipLaunchKernelGGL((k_transform_vec<3, OP, ADD>), grid, dim3(256), 0, s, In, ldi, Out, ldo, nrhs, C, ps, prep, refine_gate()); break;
   }
   return hipGetLastError();
 }
@@ -172,7 +173,7 @@ hipError_t launch_transform2(const Geometry &g, const double *A, int64_t lda, vo
 // Out.
 static hipError_t transform_vec_passes(const Geometry &g, int64_t nrhs, const double *In,
                                        int64_t ldi, double *Work, double *Out, int64_t ldo,
-                                       const double *C, int op, hipStream_t s) {
+                                       const double *C, int op, SweepPrep prep, hipStream_t s) {
   const bool add = Work != nullptr;
   const int passes = (g.d + 2) / 3;
   for (int k = 0; k < passes; ++k) {
@@ -184,23 +185,24 @@ static hipError_t transform_vec_passes(const Geometry &g, int64_t nrhs, const do
     double *to = add && !last ? Work : Out;
     const int64_t ldf = add || k == 0 ? ldi : ldo, ldt = add && !last ? ldi : ldo;
     const Pass ps = make_pass(g, lo, hi);
+    const SweepPrep pr = k == 0 ? prep : SweepPrep{};
     hipError_t e;
     if (op == RBT_OP_T)
-      e = add && last ? launch_pass_vec<RBT_OP_T, true>(ps, from, ldf, to, ldt, nrhs, C, s)
-                      : launch_pass_vec<RBT_OP_T, false>(ps, from, ldf, to, ldt, nrhs, C, s);
+      e = add && last ? launch_pass_vec<RBT_OP_T, true>(ps, from, ldf, to, ldt, nrhs, C, pr, s)
+                      : launch_pass_vec<RBT_OP_T, false>(ps, from, ldf, to, ldt, nrhs, C, pr, s);
     else
-      e = add && last ? launch_pass_vec<RBT_OP_N, true>(ps, from, ldf, to, ldt, nrhs, C, s)
-                      : launch_pass_vec<RBT_OP_N, false>(ps, from, ldf, to, ldt, nrhs, C, s);
+      e = add && last ? launch_pass_vec<RBT_OP_N, true>(ps, from, ldf, to, ldt, nrhs, C, pr, s)
+                      : launch_pass_vec<RBT_OP_N, false>(ps, from, ldf, to, ldt, nrhs, C, pr, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
 hipError_t launch_transform_vec(const Geometry &g, int64_t nrhs, const double *In, int64_t ldi,
-                                double *Out, int64_t ldo, const double *C, int op,
-                                hipStream_t s) {
+                                double *Out, int64_t ldo, const double *C, int op, hipStream_t s,
+                                SweepPrep prep) {
   if (g.n == 0 || nrhs == 0) return hipSuccess;
-  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, nullptr, Out, ldo, C, op, s);
+  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, nullptr, Out, ldo, C, op, prep, s);
   if (In == Out && ldi == ldo) return hipSuccess;
   return launch_copy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
 }
@@ -209,7 +211,7 @@ hipError_t launch_transform_vec_add(const Geometry &g, int64_t nrhs, double *In,
                                     double *Out, int64_t ldo, const double *C, int op,
                                     hipStream_t s) {
   if (g.n == 0 || nrhs == 0) return hipSuccess;
-  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, In, Out, ldo, C, op, s);
+  if (g.d > 0) return transform_vec_passes(g, nrhs, In, ldi, In, Out, ldo, C, op, SweepPrep{}, s);
   return launch_axpy_cols(g.n, nrhs, In, ldi, Out, ldo, s);
 }
 

@@ -11,7 +11,8 @@
 // each wait, so the loads overlap it.
 //
 // Publication: every solution entry carries its own readiness. Before the
-// sweep (for up to 8 right-hand sides, before the two of a solve) the launcher fills a publication buffer P (n x nrhs, in the sync
+// sweep (for up to 8 right-hand sides, before the two of a solve) the launcher, or
+// the transform before the solve, fills a publication buffer P (n x nrhs, in the sync
 // area) with a signalling-NaN pattern that no arithmetic produces; a
 // workgroup publishes x_b by storing its entries into P with agent-scope
 // atomic stores (and into B, the output), and a workgroup that needs x_j
@@ -82,14 +83,10 @@ __device__ __forceinline__ void coherent_store(double *p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Entry of P not yet published: a signalling NaN (arithmetic only yields
-// quiet NaNs; a published entry with this pattern is stored as a quiet NaN).
-constexpr uint64_t kUnpublished = 0x7FF4B1A5C0DE0001ull;
+// (a published entry with this pattern is stored as a quiet NaN)
 __device__ __forceinline__ bool unpublished(double v) {
   return __builtin_bit_cast(uint64_t, v) == kUnpublished;
 }
-// P of the single group: 256 bytes after the start of the sync area.
-constexpr int kSyncPubOffsetInts = 64;
 
 // Sums over the four lanes that share a row (the same in all four): a quad,
 // or the lanes l, l + 16, l + 32, l + 48.
@@ -516,10 +513,8 @@ __global__ void __launch_bounds__(TPB)
 // Before a sweep, or the two of a solve: tickets cleared, P (count entries) set
 // to the unpublished pattern.
 __global__ void k_sweep_reset(int32_t *sync, double *P, int64_t count) {
-  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g < 3) sync[g] = 0;
-  const double u = __builtin_bit_cast(double, kUnpublished);
-  for (int64_t k = g; k < count; k += int64_t(gridDim.x) * blockDim.x) P[k] = u;
+  SweepPrep{sync, P, count}.run(int64_t(blockIdx.x) * blockDim.x + threadIdx.x,
+                                int64_t(gridDim.x) * blockDim.x);
 }
 
 template <int NT, TriMode MODE, typename TF, typename C>
@@ -535,12 +530,12 @@ hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *W
   if (nb * groups > 0x7fffffff) return hipErrorInvalidValue;
   // the tickets and P; the sticky error word sync[3] is left alone
   const int64_t count = n * nrhs;
-  if (of != SweepOf::Second) {
+  if (of == SweepOf::Alone || of == SweepOf::First) {
     const int64_t entries = of == SweepOf::First ? 2 * count : count;
     const int64_t blocks = (entries + 255) / 256 < 1024 ? (entries + 255) / 256 : 1024;
     hipLaunchKernelGGL(k_sweep_reset, dim3(unsigned(blocks < 1 ? 1 : blocks)), dim3(256), 0, s,
                        sync, P, entries);
-  } else {
+  } else if (of == SweepOf::Second) {
     P += count;
   }
   hipLaunchKernelGGL((k_sweep<NT, MODE, TF, REFINE, C>), dim3(unsigned(nb * groups)), dim3(TPB), 0,
@@ -597,7 +592,7 @@ hipError_t sweep_any(TriMode mode, int64_t n, int64_t nrhs, const TF *LU, int64_
                      SweepOf of, hipStream_t s) {
   if (n <= 0 || nrhs <= 0) return hipSuccess;
   if (sync == nullptr) return hipErrorInvalidValue;
-  if (P != nullptr || nrhs > kSkinnyMax / 2) of = SweepOf::Alone;  // room for one only
+  if (P != nullptr || nrhs > kSweepPairMax) of = SweepOf::Alone;  // room for one only
   if (P == nullptr) {
     if (nrhs > kSkinnyMax) return hipErrorInvalidValue;
     P = reinterpret_cast<double *>(sync + kSyncPubOffsetInts);
