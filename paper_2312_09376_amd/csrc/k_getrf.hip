@@ -61,7 +61,7 @@ __device__ __forceinline__ void pivot_steps(C (&t)[PW], C (&x)[PW], int l16, C r
   const C lx = PANEL ? x[K] * rp : C(0);
   if constexpr (K + 1 < PW) {
     fmac_rows<K, 1>(t + K + 1, mt);
-    __asm__("s_nop 1" : "+v"(t[K + 1]));  // (the broadcast's distance from it)
+    dpp_distance(t[K + 1]);
     const C q = row_bcast<K + 1>(t[K + 1]);
     C rn = C(1) / q;  // one division per pivot (scaling as in LAPACK's getf2)
     if constexpr (PANEL)
@@ -88,6 +88,10 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
   typedef Mma16<C> M;
   typedef typename M::v4 c4;
   __shared__ C S[NB * LD];
+  // the top tile of the next panel (column-major): wavefronts 0 to 3 read it
+  // from here, since wavefront 0 stores the factored one into S as soon as it
+  // has it; written again only after the next barrier
+  __shared__ C top[PW * (PW + 1)];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -102,8 +106,9 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
   auto entry = [&](T v, int r, int c) {
     return (r < kb && c < kb) ? C(v) : (r == c ? C(1) : C(0));
   };
-  // tile (i, j) -= (tile column q of L, row tile i) (tile row q of U, column tile j)
-  auto update_tile = [&](int q, int i, int j) {
+  // tile (i, j) -= (tile column q of L, row tile i) (tile row q of U, column tile j);
+  // to_top: the result to `top`
+  auto update_tile = [&](int q, int i, int j, bool to_top) {
     const C *pa = S + (PW * q + lk) * LD + PW * i + l16;
     const C *pb = S + (PW * j + l16) * LD + PW * q + lk;
     C *pc = S + (PW * j + l16) * LD + PW * i + M::row(lk, 0);
@@ -119,8 +124,9 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
     for (int v = 0; v < 4; ++v) acc[v] = pc[RS * v];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) acc = M::mma(a[kk], b[kk], acc);
+    C *po = to_top ? top + l16 * (PW + 1) + M::row(lk, 0) : pc;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) pc[RS * v] = acc[v];
+    for (int v = 0; v < 4; ++v) po[RS * v] = acc[v];
   };
   auto store_half = [&](int c, int h) {  // 64 rows of column c
     const int r = 64 * h + lane;
@@ -234,7 +240,7 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
           ++j;
         }
         if (j >= m) break;
-        update_tile(p - 1, p + 1 + i, p + 1 + j);
+        update_tile(p - 1, p + 1 + i, p + 1 + j, false);
       }
       for (int e = wave - XW0; e < 2 * PW; e += XW) store_half(c0 - PW + (e >> 1), e & 1);
     }
@@ -242,19 +248,19 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
     // step p on the column tile and the row tile of step p + 1
     const int m = nt - 1 - p;
     if (wave < 2 * m - 1)
-      update_tile(p, wave < m ? p + 1 + wave : p + 1, wave < m ? p + 1 : p + 2 + wave - m);
+      update_tile(p, wave < m ? p + 1 + wave : p + 1, wave < m ? p + 1 : p + 2 + wave - m,
+                  wave == 0);
     if (m == 0) break;
     __syncthreads();
     if (wave < XW0) {
-      const C *q = S + c1 * LD + c1 + l16;
 #pragma unroll
-      for (int j = 0; j < PW; ++j) t[j] = q[j * LD];
+      for (int j = 0; j < PW; ++j) t[j] = top[j * (PW + 1) + l16];
       if (wave < UW0) {
-        q = S + c1 * LD + last(below(p + 1));
+        const C *q = S + c1 * LD + last(below(p + 1));
 #pragma unroll
         for (int j = 0; j < PW; ++j) x[j] = q[j * LD];
       } else {
-        q = S + (PW * tile0(p + 1) + 4 * lk) * LD + c1 + l16;
+        const C *q = S + (PW * tile0(p + 1) + 4 * lk) * LD + c1 + l16;
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
           const C *qh = tile0(p + 1) + h < nt ? q + PW * h * LD : S;  // (not used beyond nt)
@@ -263,8 +269,8 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
         }
       }
     } else {  // (no values to keep: without this the registers of both arrays stay taken)
-#pragma unroll
-      for (int j = 0; j < PW; ++j) __asm__("" : "=v"(t[j]), "=v"(x[j]));
+      forget(t);
+      forget(x);
     }
   }
   for (int e = wave; e < 2 * PW; e += NW) store_half(PW * (nt - 1) + (e >> 1), e & 1);

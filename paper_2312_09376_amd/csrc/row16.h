@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "mma16.h"
+
 namespace rbt {
 
 // v of lane K of each group of 16 lanes, to the whole group.
@@ -23,6 +25,18 @@ __device__ __forceinline__ double row_bcast(double v) {
 // broadcast is the first operand of v_fmac, a form that the compiler does not
 // make for FP64 by itself (it moves both halves first); the leading s_nop is
 // the distance that a DPP operand needs from the instruction that wrote it.
+// dpp_distance(v): the same distance for a use of v by the compiler's own DPP.
+#ifdef __AMDGCN__
+template <typename C>
+__device__ __forceinline__ void dpp_distance(C &v) {
+  __asm__("s_nop 1" : "+v"(v));
+}
+// Values that are not needed any more (their registers become free).
+template <int N, typename C>
+__device__ __forceinline__ void forget(C (&v)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) __asm__("" : "=v"(v[j]));
+}
 #define RBT_FMAC_OP(T, D, S0, M, K) \
   "v_fmac_" T "_dpp " D ", " S0 ", " M " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
 #define RBT_FMAC_ROWS(C, T)                                                                     \
@@ -71,5 +85,19 @@ RBT_FMAC_ROWS(double, "f64")
 RBT_FMAC_ROWS(float, "f32")
 #undef RBT_FMAC_ROWS
 #undef RBT_FMAC_OP
+#else  // the same in C++, for host builds of the kernels (tests)
+template <typename C>
+__device__ __forceinline__ void dpp_distance(C &) {}
+template <int N, typename C>
+__device__ __forceinline__ void forget(C (&)[N]) {}
+template <int K, int N, typename C>
+__device__ __forceinline__ void fmac_rows(C *x, const C *y, C m) {
+  for (int j = 0; j < N; ++j) x[j] = fma_c(row_bcast<K>(y[j]), m, x[j]);
+}
+template <int K, int N, typename C>
+__device__ __forceinline__ void fmac_rows(C *x, C m) {
+  fmac_rows<K, N>(x, x, m);
+}
+#endif
 
 }  // namespace rbt

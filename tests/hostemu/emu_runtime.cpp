@@ -9,6 +9,10 @@
 // workgroup that passes more than EMU_MAX_BARRIERS barriers (default 10^8;
 // a loop that does not end). Barriers reached from different source lines
 // by the work-items of one workgroup are counted (emu_divergent_barriers).
+// EMU_ORDER: the order in which a workgroup's work-items run between barriers:
+// 0 (default) in turn, 1 each wavefront as far as it can go before the next
+// one starts, 2 the same from the last wavefront down, so that a value passed
+// between wavefronts without a barrier shows as a difference between orders.
 #include <sys/mman.h>
 
 #include <atomic>
@@ -97,6 +101,7 @@ struct Block {
 thread_local Block g_blk;
 std::atomic<uint64_t> g_divergent{0};
 uint64_t g_max_barriers = 100000000ull;
+int g_order = 0;
 
 void fail(const char *what) {
   Block &B = g_blk;
@@ -189,32 +194,43 @@ void run_block(unsigned n, dim3 block) {
     for (int r = 3; r <= 8; ++r) top[-r] = nullptr;
     F.sp = top - 8;
   }
+  auto run = [&](unsigned i) {  // whether work-item i could go on
+    Fiber &F = B.f[i];
+    if (F.state == kDone) return false;
+    const bool ready = F.state == kReady || (F.state == kBarrier && B.gen != F.wait_gen) ||
+                       (F.state == kWave && B.w[i / 64].gen != F.wait_gen);
+    if (!ready) return false;
+    F.state = kReady;
+    threadIdx = Index{i % block.x, (i / block.x) % block.y, i / (block.x * block.y)};
+    B.cur = int(i);
+    void *fake = nullptr;
+#ifdef EMU_ASAN
+    __sanitizer_start_switch_fiber(&fake, F.stack, kStack);
+#endif
+    emu_ctx_switch(&B.sched_sp, F.sp);
+#ifdef EMU_ASAN
+    __sanitizer_finish_switch_fiber(fake, nullptr, nullptr);
+#endif
+    (void)fake;
+    return true;
+  };
+  const unsigned nw = (n + 63) / 64;
   for (;;) {
     bool ran = false;
-    unsigned done = 0;
-    for (unsigned i = 0; i < n; ++i) {
-      Fiber &F = B.f[i];
-      if (F.state == kDone) {
-        ++done;
-        continue;
+    if (g_order == 0) {
+      for (unsigned i = 0; i < n; ++i) ran |= run(i);
+    } else {
+      for (unsigned k = 0; k < nw; ++k) {
+        const unsigned w = g_order == 1 ? k : nw - 1 - k;
+        for (bool more = true; more;) {
+          more = false;
+          for (unsigned i = 64 * w; i < 64 * w + 64 && i < n; ++i) more |= run(i);
+          ran |= more;
+        }
       }
-      const bool ready = F.state == kReady || (F.state == kBarrier && B.gen != F.wait_gen) ||
-                         (F.state == kWave && B.w[i / 64].gen != F.wait_gen);
-      if (!ready) continue;
-      F.state = kReady;
-      threadIdx = Index{i % block.x, (i / block.x) % block.y, i / (block.x * block.y)};
-      B.cur = int(i);
-      void *fake = nullptr;
-#ifdef EMU_ASAN
-      __sanitizer_start_switch_fiber(&fake, F.stack, kStack);
-#endif
-      emu_ctx_switch(&B.sched_sp, F.sp);
-#ifdef EMU_ASAN
-      __sanitizer_finish_switch_fiber(fake, nullptr, nullptr);
-#endif
-      (void)fake;
-      ran = true;
     }
+    unsigned done = 0;
+    for (unsigned i = 0; i < n; ++i) done += B.f[i].state == kDone;
     if (done == n) break;
     if (!ran) fail("deadlock: no work-item can continue");
   }
@@ -244,6 +260,8 @@ void sync_threads(const char *file, int line) {
   to_scheduler(i, false);
 }
 
+void yield_host() { std::this_thread::yield(); }
+
 void wave_op(WaveFn fn, int ctx, const void *in, size_t nin, void *out, size_t nout) {
   Block &B = g_blk;
   const int i = B.cur;
@@ -269,6 +287,7 @@ void wave_op(WaveFn fn, int ctx, const void *in, size_t nin, void *out, size_t n
 
 void launch(dim3 grid, dim3 block, const std::function<void()> &body) {
   if (const char *e = std::getenv("EMU_MAX_BARRIERS")) g_max_barriers = std::strtoull(e, nullptr, 10);
+  if (const char *e = std::getenv("EMU_ORDER")) g_order = std::atoi(e);
   unsigned nthreads = 8;
   if (const char *e = std::getenv("EMU_THREADS")) nthreads = unsigned(std::atoi(e));
   const unsigned n = block.x * block.y * block.z;
@@ -303,13 +322,47 @@ void op_shfl_xor(const unsigned char (*ins)[64], unsigned char (*outs)[64], int 
 }
 
 void check_dpp(int ctrl, int row_mask, int bank_mask) {
-  if (ctrl < 0 || ctrl > 0xFF || row_mask != 0xF || bank_mask != 0xF)
-    fail("DPP control other than quad_perm with all rows and banks");
+  const bool known = (ctrl >= 0 && ctrl <= 0xFF) || (ctrl >= 0x111 && ctrl <= 0x11F) ||
+                     ctrl == 0x142 || ctrl == 0x143 || (ctrl >= 0x150 && ctrl <= 0x15F);
+  if (!known || (row_mask & ~0xF) != 0 || bank_mask != 0xF)
+    fail("a DPP control that the emulation does not have");
 }
 
-void op_quad_perm(const unsigned char (*ins)[64], unsigned char (*outs)[64], int ctrl) {
-  for (int l = 0; l < 64; ++l) std::memcpy(outs[l], ins[(l & ~3) + ((ctrl >> (2 * (l & 3))) & 3)], 64);
+void op_dpp(const unsigned char (*ins)[64], unsigned char (*outs)[64], int ctx) {
+  const int ctrl = ctx & 0xFFFF, rows = ctx >> 16;
+  const InDpp *in[64];
+  for (int l = 0; l < 64; ++l) in[l] = reinterpret_cast<const InDpp *>(ins[l]);
+  for (int l = 0; l < 64; ++l) {
+    int src = -1;
+    if (ctrl <= 0xFF)
+      src = (l & ~3) + ((ctrl >> (2 * (l & 3))) & 3);
+    else if (ctrl <= 0x11F)
+      src = (l & 15) >= ctrl - 0x110 ? l - (ctrl - 0x110) : -1;
+    else if (ctrl == 0x142)  // lane 15 of each row to the next row
+      src = l >= 16 ? (l & ~15) - 1 : -1;
+    else if (ctrl == 0x143)  // lane 31 to rows 2 and 3
+      src = l >= 32 ? 31 : -1;
+    else
+      src = (l & ~15) + (ctrl - 0x150);
+    int r = in[l]->old;
+    if ((rows >> (l / 16)) & 1) {
+      if (src >= 0)
+        r = in[src]->src;
+      else if (in[l]->bound)
+        r = 0;
+    }
+    std::memcpy(outs[l], &r, sizeof(r));
+  }
 }
+
+void op_ballot(const unsigned char (*ins)[64], unsigned char (*outs)[64], int) {
+  unsigned long long m = 0;
+  for (int l = 0; l < 64; ++l)
+    if (*reinterpret_cast<const int *>(ins[l])) m |= 1ull << l;
+  for (int l = 0; l < 64; ++l) std::memcpy(outs[l], &m, sizeof(m));
+}
+
+void op_wave_barrier(const unsigned char (*)[64], unsigned char (*)[64], int) {}
 
 // 16 x 16 x K products: lane l supplies A[l % 16][k] and B[k][l % 16] for the
 // k of its group l / 16 (one k for K = 4, eight consecutive for K = 32;

@@ -3,8 +3,8 @@
 // -x c++). A launch runs each workgroup's work-items as cooperative fibers
 // on the calling thread, one workgroup after another (emu_runtime.cpp):
 //   * __syncthreads() waits for every live work-item of the workgroup;
-//   * wavefront operations (readlane, shuffles, DPP quad permutes, the
-//     16 x 16 matrix-core products) wait for every live lane of the 64-wide
+//   * wavefront operations (readlane, shuffles, ballots, DPP moves, wave
+//     barriers, the 16 x 16 matrix-core products) wait for every live lane of the 64-wide
 //     wavefront, then compute all lanes' results at once from the lanes'
 //     operands, with the lane layouts the device instructions define;
 //   * __shared__ variables are static thread_local (one per host thread,
@@ -50,6 +50,8 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 void sync_threads(const char *file, int line);
+// A spin's pause: lets another workgroup's host thread run.
+void yield_host();
 // Every live lane of the calling wavefront passes `nin` bytes; once all have
 // arrived, fn(ins, outs, ctx) runs once and each lane receives its `nout`
 // bytes of outs. Slots are 64 bytes.
@@ -58,7 +60,9 @@ void wave_op(WaveFn fn, int ctx, const void *in, size_t nin, void *out, size_t n
 
 void op_readlane(const unsigned char (*ins)[64], unsigned char (*outs)[64], int src);
 void op_shfl_xor(const unsigned char (*ins)[64], unsigned char (*outs)[64], int mask);
-void op_quad_perm(const unsigned char (*ins)[64], unsigned char (*outs)[64], int ctrl);
+void op_dpp(const unsigned char (*ins)[64], unsigned char (*outs)[64], int ctx);
+void op_ballot(const unsigned char (*ins)[64], unsigned char (*outs)[64], int);
+void op_wave_barrier(const unsigned char (*ins)[64], unsigned char (*outs)[64], int);
 void op_mfma_f64_16x16x4(const unsigned char (*ins)[64], unsigned char (*outs)[64], int);
 void op_mfma_f32_16x16x4(const unsigned char (*ins)[64], unsigned char (*outs)[64], int);
 void op_mfma_f32_16x16x32_bf16(const unsigned char (*ins)[64], unsigned char (*outs)[64], int);
@@ -108,13 +112,29 @@ inline f4 mfma_f32_16x16x32_bf16(bf8 a, bf8 b, f4 c) {
   return r;
 }
 
-// Only the quad_perm controls (0x00-0xFF) with all rows and banks enabled.
+// DPP moves of 32-bit values: quad_perm, row_shr, row_bcast:15 and 31 and
+// row_newbcast, with a row mask and all banks. A lane that gets no value keeps
+// old (or 0 with bound_ctrl, where its row is enabled).
 void check_dpp(int ctrl, int row_mask, int bank_mask);
+struct InDpp {
+  int old, src, bound;
+};
 inline int update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl) {
-  (void)old;
-  (void)bound_ctrl;
   check_dpp(ctrl, row_mask, bank_mask);
-  return wave_simple(op_quad_perm, ctrl, src);
+  InDpp in{old, src, bound_ctrl};
+  int r;
+  wave_op(op_dpp, ctrl | (row_mask << 16), &in, sizeof(in), &r, sizeof(r));
+  return r;
+}
+inline unsigned long long ballot(bool v) {
+  unsigned long long r;
+  const int in = v;
+  wave_op(op_ballot, 0, &in, sizeof(in), &r, sizeof(r));
+  return r;
+}
+inline void wave_barrier() {
+  int in = 0, out;
+  wave_op(op_wave_barrier, 0, &in, sizeof(in), &out, sizeof(out));
 }
 
 }  // namespace emu
@@ -126,6 +146,14 @@ extern thread_local emu::Index threadIdx, blockIdx, blockDim, gridDim;
 // every lane is active where the kernels read the first lane
 #define __builtin_amdgcn_readfirstlane(v) ::emu::readlane((v), 0)
 #define __builtin_amdgcn_sched_barrier(mask) ((void)0)
+#define __builtin_amdgcn_s_setprio(p) ((void)0)
+#define __builtin_amdgcn_s_sleep(n) ::emu::yield_host()
+#define __builtin_amdgcn_fence(...) ((void)0)
+#define __builtin_amdgcn_wave_barrier() ::emu::wave_barrier()
+#define __threadfence_block() ((void)0)
+#define __ballot(v) ::emu::ballot(v)
+#define __any(v) (::emu::ballot(v) != 0)
+#define __ffsll(v) __builtin_ffsll((long long)(v))
 #define __builtin_amdgcn_update_dpp(old, src, ctrl, rm, bm, bc) \
   ::emu::update_dpp((old), (src), (ctrl), (rm), (bm), (bc))
 #define __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, cbsz, abid, blgp) \
@@ -173,8 +201,31 @@ inline T atomicAdd(T *p, T v) {
   return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST);
 }
 
+inline int atomicCAS(int *p, int expected, int v) {
+  __atomic_compare_exchange_n(p, &expected, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
+  return expected;
+}
+
 #define __HIP_MEMORY_SCOPE_AGENT 0
-#define __hip_atomic_load(p, order, scope) __atomic_load_n((p), (order))
+template <typename T>
+inline T emu_atomic_load(const T *p) {
+  T v;
+  __atomic_load(const_cast<T *>(p), &v, __ATOMIC_SEQ_CST);
+  return v;
+}
+template <typename T>
+inline void emu_atomic_store(T *p, T v) {
+  __atomic_store(p, &v, __ATOMIC_SEQ_CST);
+}
+template <typename T>
+inline bool emu_atomic_cas(T *p, T *expected, T v) {
+  return __atomic_compare_exchange(p, expected, &v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
+}
+#define __hip_atomic_load(p, order, scope) emu_atomic_load(p)
+#define __hip_atomic_store(p, v, order, scope) emu_atomic_store(p, v)
+#define __hip_atomic_fetch_or(p, v, order, scope) __atomic_fetch_or((p), (v), __ATOMIC_SEQ_CST)
+#define __hip_atomic_fetch_add(p, v, order, scope) __atomic_fetch_add((p), (v), __ATOMIC_SEQ_CST)
+#define __hip_atomic_compare_exchange_strong(p, e, v, os, of, scope) emu_atomic_cas((p), (e), (v))
 
 // Kernels run to completion inside the launch.
 #define hipLaunchKernelGGL(kernel, grid, block, shmem, stream, ...) \
