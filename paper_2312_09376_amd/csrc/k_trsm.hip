@@ -21,9 +21,12 @@
 // holds entry l16 of four right-hand sides, which is how the matrix-core
 // product leaves them, and its 16 coefficients in registers. At pivot j lane j
 // scales its entries and the update takes them as a DPP row broadcast inside
-// the multiply-add: no LDS access and no shuffle in the chain of 16 pivots.
-// Every entry sees the same operations in the same order as in
-// one-lane-per-right-hand-side substitution. (With four lanes per right-hand
+// the multiply-add: no LDS access and no shuffle in the chain of 16 pivots. The
+// entries that a pivot does not update take a zero coefficient, which keeps
+// them unless the pivot's entry is Inf or NaN (0 * Inf is NaN and stays so to the
+// end of the tile); a tile that ends with a NaN is therefore solved again, those
+// entries kept by a select. So every entry sees the same operations in the same
+// order as in one-lane-per-right-hand-side substitution. (With four lanes per right-hand
 // side, their coefficients read from LDS a pivot ahead: both solves of a panel
 // step at n = 1000 18.2 us, now 17.7; the inverses of the diagonal blocks,
 // where no pivot scales, 16.6 and 14.5.)
@@ -97,8 +100,9 @@ __device__ __forceinline__ void wave_sync() {
 
 // In-place substitution with one 16 x 16 diagonal block: x[v] = entry l16 of
 // four right-hand sides; m[j] = minus the coefficient of pivot j for entry l16,
-// zero where it has none; rd = the reciprocal of the lane's own pivot.
-template <bool FWD, bool UNIT, int S, typename C>
+// zero where it has none; rd = the reciprocal of the lane's own pivot. KEEP: the
+// entries without a coefficient are kept by a select.
+template <bool FWD, bool UNIT, bool KEEP, int S, typename C>
 __device__ __forceinline__ void substitute(C (&x)[4], const C (&m)[IB], C rd, int l16) {
   if constexpr (S < IB) {
     constexpr int J = FWD ? S : IB - 1 - S;
@@ -107,8 +111,29 @@ __device__ __forceinline__ void substitute(C (&x)[4], const C (&m)[IB], C rd, in
 #pragma unroll
       for (int v = 0; v < 4; ++v) x[v] *= f;
     }
-    fmac_rows<J, 4>(x, m[J]);
-    substitute<FWD, UNIT, S + 1>(x, m, rd, l16);
+    if constexpr (KEEP) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const C nx = fma_c(m[J], row_bcast<J>(x[v]), x[v]);
+        x[v] = (FWD ? l16 > J : l16 < J) ? nx : x[v];
+      }
+    } else {
+      fmac_rows<J, 4>(x, m[J]);
+    }
+    substitute<FWD, UNIT, KEEP, S + 1>(x, m, rd, l16);
+  }
+}
+template <bool FWD, bool UNIT, typename C>
+__device__ __forceinline__ void substitute_tile(C (&x)[4], const C (&m)[IB], C rd, int l16) {
+  C r[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) r[v] = x[v];
+  substitute<FWD, UNIT, false, 0>(x, m, rd, l16);
+  const bool nan = __builtin_isunordered(x[0], x[1]) || __builtin_isunordered(x[2], x[3]);
+  if (__any(nan)) {
+    substitute<FWD, UNIT, true, 0>(r, m, rd, l16);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = r[v];
   }
 }
 
@@ -243,7 +268,7 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) x[v] -= acc0[v] + acc1[v];
-    substitute<FWD, unit_diag<MODE>(), 0>(x, m, rd, l16);
+    substitute_tile<FWD, unit_diag<MODE>()>(x, m, rd, l16);
 #pragma unroll
     for (int v = 0; v < 4; ++v) xs[RS * v] = IB * I + l16 < kb ? x[v] : C(0);
     wave_sync();
@@ -356,7 +381,7 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) x[v] -= acc0[v] + acc1[v];
-    substitute<true, false, 0>(x, m, rd, l16);
+    substitute_tile<true, false>(x, m, rd, l16);
 #pragma unroll
     for (int v = 0; v < 4; ++v) xs[RS * v] = IB * J + l16 < kb ? x[v] : C(0);
     wave_sync();

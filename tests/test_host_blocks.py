@@ -27,3 +27,82 @@ def test_diag_block_in_any_wavefront_order(exe, op, dt, n):
     L = np.tril(F[0], -1).astype(float) + np.eye(n)
     U = np.triu(F[0]).astype(float)
     assert (np.abs(A - L @ U) <= 2 * n * np.finfo(dt).eps * (np.abs(L) @ np.abs(U))).all()
+
+
+def substitution(T, B, lower, unit):
+    """op(T) X = B entry by entry in the arrays' type, a division by a pivot as
+    a product with its reciprocal; IEEE Inf and NaN as they come."""
+    X = B.copy()
+    n = T.shape[0]
+    one = T.dtype.type(1)
+    with np.errstate(all="ignore"):
+        for j in (range(n) if lower else range(n - 1, -1, -1)):
+            if not unit:
+                X[j] = X[j] * (one / T[j, j])
+            rows = slice(j + 1, n) if lower else slice(0, j)
+            X[rows] -= np.outer(T[rows, j], X[j])
+    return X
+
+
+def same_nonfinite(got, want):
+    """NaN where NaN and the same infinities; finite entries within the bound
+    of the elimination's own rounding on well conditioned data."""
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)  # (none where the first pivot solved is the zero)
+    eps = np.finfo(want.dtype).eps
+    top = np.abs(want[fin]).max(initial=1.0)
+    assert np.abs(got[fin] - want[fin]).max(initial=0.0) <= 1000 * eps * top
+
+
+def tame(n, dt, seed=3):
+    """A matrix whose triangles are well conditioned."""
+    return (0.05 * workloads.randn_matrix(n, seed=seed) + np.eye(n)).astype(dt)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("mode", [E.LN, E.UN, E.UT, E.LT])
+@pytest.mark.parametrize("n,at", [(128, 37), (100, 64), (40, 39), (128, 0)])
+def test_left_solve_keeps_entries_beside_a_zero_pivot(exe, f32, mode, n, at):
+    """Non-unit triangles with an exact zero on the diagonal (unit ones: an
+    infinite right-hand side entry): the entries solved before it, in its own
+    16-row tile too, are those of plain substitution, and so are the others."""
+    dt = np.float32 if f32 else np.float64
+    A = tame(n, dt)
+    B = workloads.randn(n, 5, seed=4).astype(dt)
+    unit = mode in (E.LN, E.LT)
+    if unit:
+        B[at, 2] = np.inf
+        T = np.tril(A, -1) + np.eye(n, dtype=dt)
+    else:
+        A[at, at] = 0.0
+        T = np.triu(A)
+    T = T.T if mode in (E.UT, E.LT) else T
+    X = E.call(exe, (20 if f32 else 10) + mode, A, B)[1]
+    same_nonfinite(X, substitution(np.asarray(T, dt), B, mode in (E.LN, E.UT), unit))
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("at", [5, 70])
+def test_panel_solves_keep_entries_beside_a_zero_pivot(exe, f32, at):
+    """L21 U11 = A21: the columns before the zero pivot are correct factors."""
+    dt = np.float32 if f32 else np.float64
+    m, n = 96, 100
+    A = tame(m, dt)
+    A[at, at] = 0.0
+    B = workloads.randn(n, m, seed=5).astype(dt)
+    C = workloads.randn(n, n, seed=6).astype(dt)
+    C[at, 3] = np.nan
+    _, X, Y, _ = E.call(exe, 31 if f32 else 30, A, B, C)
+    U, L = np.triu(A), np.tril(A, -1) + np.eye(m, dtype=dt)
+    same_nonfinite(X, substitution(U.T, B.T.copy(), True, False).T)
+    same_nonfinite(Y[:m], substitution(L, C[:m], True, True))
+
+
+def test_inverse_of_a_block_with_a_zero_pivot(exe):
+    n, at = 128, 50
+    A = tame(n, np.float64)
+    A[at, at] = 0.0
+    W = E.call(exe, 40, A)[2].reshape(2, n, n).transpose(0, 2, 1)
+    same_nonfinite(W[1], substitution(np.triu(A), np.eye(n), False, False))
