@@ -57,7 +57,8 @@ constexpr int XW = NW - XW0;
 // division (the chain) is issued between the other updates.
 template <int K, bool PANEL, typename C>
 __device__ __forceinline__ void pivot_steps(C (&t)[PW], C (&x)[PW], int l16, C rp) {
-  const C mt = -t[K] * (l16 > K ? rp : C(0));  // rows up to the pivot's keep their values
+  // (rows up to the pivot's: a zero multiplier, also where their entry is not finite)
+  const C mt = l16 > K ? -t[K] * rp : C(0);
   const C lx = PANEL ? x[K] * rp : C(0);
   if constexpr (K + 1 < PW) {
     fmac_rows<K, 1>(t + K + 1, mt);
@@ -82,6 +83,17 @@ __device__ __forceinline__ void pivot_steps(C (&t)[PW], C (&x)[PW], int l16, C r
   }
 }
 
+// The updates of one column right of the panel (v: its entry in the lane's row; l:
+// the row of the panel's factored top), rows up to the pivot's kept by a select.
+template <int K, typename C>
+__device__ __forceinline__ void keep_steps(const C (&l)[PW], C &v, int l16) {
+  if constexpr (K < PW) {
+    const C nv = fma_c(-l[K], row_bcast<K>(v), v);
+    v = l16 > K ? nv : v;
+    keep_steps<K + 1>(l, v, l16);
+  }
+}
+
 template <typename T, typename C>
 __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64_t lda,
                                                  int64_t gofs, int32_t *__restrict__ info) {
@@ -92,11 +104,13 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
   // from here, since wavefront 0 stores the factored one into S as soon as it
   // has it; written again only after the next barrier
   __shared__ C top[PW * (PW + 1)];
+  __shared__ __attribute__((aligned(8))) int again[2];  // wavefronts 2 and 3
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lk = lane >> 4;
   const int nt = (kb + PW - 1) / PW;  // 16-column tiles
+  if (tid >= 64 * UW0 && lane == 0 && tid < 64 * XW0) again[wave - UW0] = 0;
 
   // entry (r, c) of the block, identity beyond kb: the load is unconditional at
   // clamped indices, so that a batch of them is in flight together
@@ -171,6 +185,7 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
     for (int j = 0; j < PW; ++j) {
       t[j] = entry(vt[j], l16, j);
       x[j] = entry(vx[j], l16, col(j));
+      S[col(j) * LD + l16] = x[j];  // (for the case of a row that is not finite)
     }
   } else if (wave >= XW0) {
     // the rest of the block, rows and columns 16 .. 127 (indices beyond the
@@ -218,11 +233,18 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
     } else if (row_block(p)) {
       pivot_steps<0, false>(t, x, l16, C(1) / row_bcast<0>(t[0]));
       C *q = S + (PW * tile0(p) + 4 * lk) * LD + c0 + l16;
+      bool nan = false;
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        if (tile0(p) + h < nt) {
+      for (int j = 0; j < PW; j += 2) nan = nan || __builtin_isunordered(x[j], x[j + 1]);
+      if (__any(nan)) {
+        if (lane == 0) again[wave - UW0] = 1;  // (see after the barrier)
+      } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) q[(PW * h + j) * LD] = x[4 * h + j];
+        for (int h = 0; h < 4; ++h) {
+          if (tile0(p) + h < nt) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[(PW * h + j) * LD] = x[4 * h + j];
+          }
         }
       }
     } else if (wave >= XW0 && p > 0) {
@@ -245,6 +267,27 @@ __global__ void __launch_bounds__(NT) k_diag_lu(int kb, T *__restrict__ A, int64
       for (int e = wave - XW0; e < 2 * PW; e += XW) store_half(c0 - PW + (e >> 1), e & 1);
     }
     __syncthreads();
+    // Where a pivot row is not finite, the zero multipliers of the rows up to it
+    // have made NaN of finished entries of the row block (0 * Inf): then once more
+    // from the entries before, with selects. Without a NaN the two are
+    // bit-identical. (Here, where no wavefront holds a part of the block in
+    // registers, the case costs the others none.)
+    if ((again[0] | again[1]) != 0) {
+      if (row_block(p) && again[wave - UW0] != 0) {
+        C l[PW];
+#pragma unroll
+        for (int j = 0; j < PW; ++j) l[j] = S[(c0 + j) * LD + c0 + l16];
+#pragma unroll 1
+        for (int e = 0; e < PW && tile0(p) + (e >> 2) < nt; ++e) {
+          C *q = S + (PW * (tile0(p) + (e >> 2)) + 4 * lk + (e & 3)) * LD + c0 + l16;
+          C v = *q;
+          keep_steps<0>(l, v, l16);
+          *q = v;
+        }
+      }
+      __syncthreads();
+      if (tid < 2) again[tid] = 0;
+    }
     // step p on the column tile and the row tile of step p + 1
     const int m = nt - 1 - p;
     if (wave < 2 * m - 1)

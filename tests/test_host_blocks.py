@@ -106,3 +106,26 @@ def test_inverse_of_a_block_with_a_zero_pivot(exe):
     A[at, at] = 0.0
     W = E.call(exe, 40, A)[2].reshape(2, n, n).transpose(0, 2, 1)
     same_nonfinite(W[1], substitution(np.triu(A), np.eye(n), False, False))
+
+
+@pytest.mark.parametrize("op,dt", [(0, np.float64), (1, np.float32)])
+@pytest.mark.parametrize("n,at", [(128, 3), (128, 20), (100, 47), (60, 33)])
+def test_diag_block_keeps_rows_above_a_zero_pivot(exe, op, dt, n, at):
+    """A leading block that becomes singular at one column: the rows of U up to
+    it right of its 16-column step, and all columns of L before it, are those of
+    plain elimination; info names the column."""
+    A = tame(n, dt)
+    F = A.astype(float)
+    for j in range(at):
+        F[j + 1:, j] /= F[j, j]
+        F[j + 1:, j + 1:] -= np.outer(F[j + 1:, j], F[j, j + 1:])
+    # exact zero: row `at` of L before the column is zero, and so is its diagonal
+    A[at, :at] = 0
+    A[at, at] = 0
+    F[at, :at] = 0
+    F[at, at:] = A[at, at:]
+    got, _, _, info = E.call(exe, op, A)
+    assert info == at + 1
+    right = 16 * (at // 16 + 1)
+    same_nonfinite(got[:at + 1, right:], F[:at + 1, right:].astype(dt))
+    same_nonfinite(got[:, :at], F[:, :at].astype(dt))
