@@ -317,7 +317,7 @@ template <int NT, TriMode MODE, typename TF, bool REFINE, typename C>
 __global__ void __launch_bounds__(TPB)
     k_sweep(int64_t n, int64_t nrhs, const TF *__restrict__ A, int64_t ld,
             const C *__restrict__ Winv, double *B, int64_t ldb, int32_t *sync, double *P,
-            int64_t nb, int groups, int width, int ticket_word, int64_t spin_limit,
+            int64_t nb, int groups, int width, int ticket_word, bool keep, int64_t spin_limit,
             const int32_t *gate) {
   // (the gate is read before any ticket is taken: every workgroup of a gated
   // launch returns here)
@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(TPB)
   constexpr int NV = Pr::NV, XN = Pr::XN;
   __shared__ __attribute__((aligned(16))) C xs[2][kNB * XN];
   __shared__ int32_t tk;
-  __shared__ int expired_sh;
+  __shared__ int expired_sh, nonfinite_sh;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(TPB)
   const int i = 16 * wave + Pr::rl(lane);  // the lane's row as an operand
   if (tid == 0) {
     tk = atomicAdd(&sync[ticket_word], 1);
-    expired_sh = 0;
+    expired_sh = nonfinite_sh = 0;
   }
   for (int e = tid; e < 2 * kNB * XN; e += TPB) xs[0][e] = C(0);  // unused columns stay zero
   __syncthreads();
@@ -479,18 +479,79 @@ __global__ void __launch_bounds__(TPB)
   to_lds(xa, r);
   __syncthreads();
   Pr::template mul<V>(di, xa, lane, x);
+  // KEEP (with `keep`): a block whose solution is not finite everywhere is solved
+  // by substitution (below). Noted before the barriers that are there anyway.
+  constexpr bool KEEP = NT > 1 && std::is_same<TF, double>::value;
+  auto note = [&](const C (&val)[NV]) {
+    if constexpr (KEEP) {
+      if (!keep) return;
+      bool bad = false;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) bad = bad || (in[v] && !(fabs(val[v]) < C(INFINITY)));
+      if (__any(bad) && lane == 0) nonfinite_sh = 1;
+    }
+  };
   if constexpr (REFINE) {
+    note(x);
     to_lds(xb, x);
     __syncthreads();
     C tx[NV], dx[NV];
     Pr::template mul<V>(td, xb, lane, tx);
 #pragma unroll
     for (int v = 0; v < NV; ++v) tx[v] = r[v] - tx[v];
+    note(tx);
     to_lds(xa, tx);
     __syncthreads();
     Pr::template mul<V>(di, xa, lane, dx);
 #pragma unroll
     for (int v = 0; v < NV; ++v) x[v] += dx[v];
+  }
+  if constexpr (KEEP) {
+    // Products with the inverse make NaN of every entry of the block where the
+    // inverse has one Inf or NaN (a zero on the diagonal) or r has (0 * Inf);
+    // substitution, which more than kSkinnyMax right-hand sides take without a
+    // publication buffer, keeps the entries solved before it. A pivot per barrier,
+    // the next one's coefficients in flight.
+    if (keep && nonfinite_sh != 0 && expired_sh == 0) {
+      constexpr int ROWS = kNB * NT / TPB;  // rows per thread, of right-hand side tid % NT
+      const int c = tid % NT, m0 = tid / NT;
+      TF tn[ROWS], dn;
+      auto load = [&](int jj) {
+        const int j = FWD ? jj : kb - 1 - jj;
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+          const int m = m0 + q * (TPB / NT), mc = m < kb ? m : kb - 1;
+          tn[q] = TRANS ? A[(r0 + j) + (r0 + mc) * ld] : A[(r0 + mc) + (r0 + j) * ld];
+        }
+        dn = A[(r0 + j) + (r0 + j) * ld];
+      };
+      load(0);
+      __syncthreads();  // (every wavefront has read xa)
+      to_lds(xa, r);
+      for (int jj = 0; jj < kb; ++jj) {
+        const int j = FWD ? jj : kb - 1 - jj;
+        TF t[ROWS];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) t[q] = tn[q];
+        const C rd = UNIT ? C(1) : C(1) / C(dn);
+        if (jj + 1 < kb) load(jj + 1);
+        __syncthreads();
+        const C xj = xa[Pr::template slot<V>(j) * XN + c] * rd;
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+          const int m = m0 + q * (TPB / NT);
+          C *xm = xa + Pr::template slot<V>(m) * XN + c;
+          if (m == j)
+            xb[Pr::template slot<V>(m) * XN + c] = xj;
+          else if (m < kb && (FWD ? m > j : m < j))
+            *xm = fma_c(-C(t[q]), xj, *xm);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        if (in[v]) x[v] = xb[Pr::template slot<V>(rv[v]) * XN + cv[v]];
+    }
   }
 
   // ---- publish x_b (NaN if a wait of this block expired): the consumers'
@@ -540,7 +601,8 @@ hipError_t sweep_t(int64_t n, int64_t nrhs, const TF *LU, int64_t ld, const C *W
   }
   hipLaunchKernelGGL((k_sweep<NT, MODE, TF, REFINE, C>), dim3(unsigned(nb * groups)), dim3(TPB), 0,
                      s, n, nrhs, LU, ld, Winv, B, ldb, sync, P, nb, int(groups),
-                     int(width), of == SweepOf::Second ? 1 : 0, sweep_spin_limit(), refine_gate());
+                     int(width), of == SweepOf::Second ? 1 : 0, nrhs > kSkinnyMax,
+                     sweep_spin_limit(), refine_gate());
   return hipGetLastError();
 }
 
