@@ -17,8 +17,7 @@
 // arithmetic type (FP32 for the low-precision pass, FP64 for the fallback):
 //   diagonal block in LDS: 16-column panels factored by wavefront 0 with
 //   readlane broadcasts, U rows by substitution, rank-16 updates; its
-//   inverses L^-1 and U^-1 by substitution (one column per lane: wavefront
-//   0 the columns of L^-1, wavefront 1 those of U^-1);
+//   inverses L^-1 and U^-1 by 16 x 16 blocks (see diag_block);
 //   L21 = A21 U11^-1 and U12 = L11^-1 A12 as matrix-core products with the
 //   inverses (FP32: plus one refinement step, X += (A - X D) D^-1), and
 //   A22 -= L21 U12 (FP32: v_mfma_f32_16x16x4f32, or BF16 operands on
@@ -721,30 +720,42 @@ __device__ __noinline__ void diag_block(const Sys &s, int64_t k, int kb, double 
   // Inverses L^-1 (strictly lower part of T) and U^-1 (upper part with the
   // diagonal) by 16 x 16 blocks: the diagonal blocks by substitution, a lane
   // per column (wavefront 0 those of L, wavefront 1 those of U), then block
-  // diagonal d by block diagonal, X_ij = -X_ii sum_t D_it X_tj with two
-  // matrix-core products. (Column by column over the whole block, on one
-  // wavefront each, the inverses were most of this function: it took 95 us
-  // for a 64 x 64 block with two workgroups on the compute unit, 20 us now.)
+  // diagonal d by block diagonal, X_ij = -D_ii^-1 sum_t D_it X_tj, the sum with
+  // matrix-core products. D_ii^-1 is applied as a product with X_ii in FP32,
+  // whose users take a refinement step with the block itself, and by
+  // substitution in FP64, whose users do not: the product raises the residual of
+  // a solve with the inverse several-fold. (Column by column over the
+  // whole block, on one wavefront each, the inverses were most of this function:
+  // it took 95 us for a 64 x 64 FP32 block with two workgroups on the compute
+  // unit, 20 us now.)
+  constexpr bool kSolveInv = sizeof(TF) == 8;
+  // x <- D^-1 x with the unit lower (upper) triangle of the 16 x 16 block at o
+  auto solve_low = [&](TF (&x)[16], int o) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+#pragma unroll
+      for (int i = t + 1; i < 16; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
+  };
+  auto solve_up = [&](TF (&x)[16], int o) {
+#pragma unroll
+    for (int t = 15; t >= 0; --t) {
+      x[t] *= TF(1) / S[(o + t) * LDS_ + o + t];
+#pragma unroll
+      for (int i = 0; i < t; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
+    }
+  };
   if (wave < 2) {
     const int o = 16 * lk, c = l16;
     TF x[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) x[i] = i == c ? TF(1) : TF(0);
     if (wave == 0) {
-#pragma unroll
-      for (int t = 0; t < 16; ++t)
-#pragma unroll
-        for (int i = t + 1; i < 16; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
+      solve_low(x, o);
 #pragma unroll
       for (int i = 1; i < 16; ++i)
         if (i > c) T[(o + c) * LDS_ + o + i] = x[i];
     } else {
-#pragma unroll
-      for (int t = 15; t >= 0; --t) {
-        x[t] *= TF(1) / S[(o + t) * LDS_ + o + t];
-#pragma unroll
-        for (int i = 0; i < t; ++i) x[i] -= S[(o + t) * LDS_ + o + i] * x[t];
-      }
+      solve_up(x, o);
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         if (i <= c) T[(o + c) * LDS_ + o + i] = x[i];
@@ -777,17 +788,34 @@ __device__ __noinline__ void diag_block(const Sys &s, int64_t k, int kb, double 
       for (int v = 0; v < 4; ++v) T[(16 * j + l16) * LDS_ + 16 * i + M::row(lk, v)] = acc[v];
     }
     __syncthreads();
-    for (int t = wave; t < 2 * nl; t += BT / 64) {
-      const bool low = t < nl;
-      const int i = low ? t + d : t - nl, j = low ? t : t - nl + d;
-      typename M::v4 acc = {TF(0), TF(0), TF(0), TF(0)};
+    if constexpr (kSolveInv) {
+      // (a wavefront for each triangle, 16 lanes to a block, a lane per column)
+      if (wave < 2 && lk < nl) {
+        const int i = 16 * (wave == 0 ? lk + d : lk), j = 16 * (wave == 0 ? lk : lk + d);
+        lds_t *q = T + (j + l16) * LDS_ + i;
+        TF x[16];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int kx = 4 * kk + lk;
-        acc = M::mma(-inv_at(low, i, i, l16, kx), T[(16 * j + l16) * LDS_ + 16 * i + kx], acc);
+        for (int r = 0; r < 16; ++r) x[r] = -q[r];
+        if (wave == 0)
+          solve_low(x, i);
+        else
+          solve_up(x, i);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) q[r] = x[r];
       }
+    } else {
+      for (int t = wave; t < 2 * nl; t += BT / 64) {
+        const bool low = t < nl;
+        const int i = low ? t + d : t - nl, j = low ? t : t - nl + d;
+        typename M::v4 acc = {TF(0), TF(0), TF(0), TF(0)};
 #pragma unroll
-      for (int v = 0; v < 4; ++v) T[(16 * j + l16) * LDS_ + 16 * i + M::row(lk, v)] = acc[v];
+        for (int kk = 0; kk < 4; ++kk) {
+          const int kx = 4 * kk + lk;
+          acc = M::mma(-inv_at(low, i, i, l16, kx), T[(16 * j + l16) * LDS_ + 16 * i + kx], acc);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) T[(16 * j + l16) * LDS_ + 16 * i + M::row(lk, v)] = acc[v];
+      }
     }
     __syncthreads();
   }

@@ -15,15 +15,17 @@ SOURCES = ["k_getrf.hip", "k_trsm.hip"]
 LN, UN, UT, LT = range(4)
 
 
-def build(exe=EXE, csrc=emu.CSRC, sources=SOURCES, driver="emu_blocks.cpp"):
-    """Compile unless the executable is newer than every input."""
+def build(exe=EXE, csrc=emu.CSRC, sources=SOURCES, driver="emu_blocks.cpp", watch=()):
+    """Compile unless the executable is newer than every input (watch: sources
+    that the driver includes)."""
     cc = emu.clang()
     if cc is None:
         raise RuntimeError("clang++ not found")
     os.makedirs(os.path.dirname(exe), exist_ok=True)
     srcs = [os.path.join(csrc, s) for s in sources]
     ours = [os.path.join(emu.HERE, "emu_runtime.cpp"), os.path.join(emu.HERE, driver)]
-    inputs = srcs + ours + [os.path.join(csrc, h) for h in os.listdir(csrc) if h.endswith(".h")]
+    inputs = srcs + ours + [os.path.join(csrc, s) for s in watch]
+    inputs += [os.path.join(csrc, h) for h in os.listdir(csrc) if h.endswith(".h")]
     inputs += [os.path.join(emu.HERE, "include", "hip", "hip_runtime.h"), os.path.abspath(__file__)]
     if os.path.exists(exe) and all(os.path.getmtime(f) < os.path.getmtime(exe) for f in inputs):
         return exe
