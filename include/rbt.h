@@ -290,8 +290,10 @@ int rbt_solve_mixed_guarded(int64_t n, int64_t nrhs, const double *A, int64_t ld
  * all exactly zero (left unswapped; the elimination goes on with IEEE
  * Inf/NaN). This is the robust solver that the fallback of Sec. 5 re-solves
  * with. Up to n = 32768 it factors 32 columns per launch, whose workgroups
- * exchange the pivots through work with bounded waits (a wait that expires
- * makes the columns NaN); beyond, column by column. work: >=
+ * exchange the pivots through work; where other work on the device keeps them from
+ * running at once (RBT_OPT_SWEEP_SPIN_LIMIT), one of them factors the columns, with
+ * the same result. Beyond, column by column. info_dev: -1 and NaN columns only where
+ * an exchange expired all the same. work: >=
  * rbt_workspace_size(n, 0, 0, RBT_FP64) bytes. */
 int rbt_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv_dev, int32_t *info_dev, void *work,
              size_t work_bytes, void *stream);
@@ -464,7 +466,9 @@ int rbt_solve_backward_mixed(int64_t n, int64_t nrhs, const float *LU, int64_t l
  *   wait of a persistent triangular sweep may take before it expires
  *   (default 2^20). A negative value makes every wait expire at once: a
  *   host-side way to exercise the RBT_ERR_SYNC path in tests (every kernel
- *   still exits normally). 16 times as many for an exchange of rbt_gepp. */
+ *   still exits normally). For rbt_gepp: how long the workgroups of a slab wait for
+ *   each other to start before one of them takes it alone (negative: its exchanges
+ *   expire instead: NaN and info -1). */
 #define RBT_OPT_SWEEP_SPIN_LIMIT 6
 /* RBT_OPT_MIXED_FP64_INNER: low-precision elimination and solves
  *   (rbt_solve_mixed, rbt_solve_mixed_guarded, rbt_solve_backward_mixed).

@@ -1646,7 +1646,6 @@ extern "C" int rbt_solve_guarded(int64_t n, int64_t nrhs, const double *A, int64
 
 // ---- batched solves ----
 namespace rbt {
-namespace {
 
 int device_cus() {
   int dev = 0, cus = 0;
@@ -1657,7 +1656,6 @@ int device_cus() {
   return cus;
 }
 
-}  // namespace
 }  // namespace rbt
 
 extern "C" size_t rbt_batched_workspace_size(int64_t batch, const int64_t *n,

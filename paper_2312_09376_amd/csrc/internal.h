@@ -387,10 +387,13 @@ __host__ __device__ inline int64_t batched_sys_doubles(int64_t n, int64_t nrhs, 
 // Sec. 5 fallback). launch_gepp factors A in place (P A = L U, ipiv 1-based
 // as LAPACK's getrf; *info = first zero pivot column, 1-based) using
 // scratch_bytes >= gepp_scratch_bytes() of scratch, and the faster slab
-// kernel from gepp_slab_bytes(n) on; *err (nullable) is set when an exchange of
-// the slab kernel waited longer than sweep_spin_limit() (its rows are then NaN).
+// kernel from gepp_slab_bytes(n) on. A slab whose workgroups do not all become
+// resident within sweep_spin_limit() is factored by one of them; *err (nullable) is
+// set, *info is -1 and the slab NaN where a later exchange expires all the same (or
+// the limit is negative).
 // launch_ipiv_to_perm turns ipiv into
 // perm[i] = original row of row i; launch_gather_rows: Y[i, :] = B[perm[i], :].
+int device_cus();  // compute units of the current device (api.hip)
 constexpr int64_t kPermLdsMax = 16384;  // ipiv_to_perm works in LDS up to this n
 size_t gepp_scratch_bytes();
 size_t gepp_slab_bytes(int64_t n);

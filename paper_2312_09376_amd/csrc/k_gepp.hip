@@ -147,14 +147,23 @@ __global__ void __launch_bounds__(TPB)
 // arithmetic never yields, so each 8-byte entry says by itself that it has
 // arrived (as in the triangular sweeps): one store and one load per column.
 //
-// Progress: the workgroups wait for each other, so all of them must become
-// resident. A hardware queue dispatches in order, so each of a process's (four
-// by default) holds at most one launch that is only partly resident, and
-// kSlabGroups = 32 workgroups for each are 128, half of what the 256 CUs hold at
-// one per CU. The wait is bounded all the same, by 16 times a sweep's spin limit
-// (some 16 s by default: a workgroup may first have to wait for kernels of other
-// streams to leave its CU): a workgroup whose wait expires sets *err (nullable)
-// and stores NaN into its rows, so the factors are never silently wrong.
+// Progress: the workgroups wait for each other, so all of them must be resident,
+// which other work on the device (other streams, other processes) may prevent for
+// as long as it likes, or for good where it waits for this slab's CUs in turn. So
+// they agree first: the exchange of column 0 decides, by one compare-and-swap on a
+// word of the buffer, between "together" (some workgroup has seen every candidate, so
+// all are resident and every later wait ends) and "alone" (some workgroup waited
+// for longer than the sweeps' spin limit). Alone, the workgroup that decided it
+// factors the slab by itself from memory, where nothing has been stored yet, and the
+// others leave; the later slabs of the factorization are then taken alone at once.
+// Either way the factors are the same. In the common case this is one
+// compare-and-swap of one thread per slab, beside column 0's update (n = 4000: 15.3 ->
+// 15.5 ms). Together, waits
+// are bounded all the same (kSlabSpins, none after the first that expires); one that
+// expires, or a negative limit, which makes every wait expire at once, leaves NaN in
+// the slab, *info = -1 and *err set (both nullable). The workgroups take an eighth of
+// the device's CUs at most (slab_max_groups): the four hardware queues of a process,
+// each of which dispatches in order, then never hold more than half of it waiting.
 //
 // The column loop is unrolled over 8 columns only (32 copies of its body would
 // not fit the instruction cache): after 8 columns the 32 registers of a row
@@ -227,11 +236,21 @@ __device__ __forceinline__ int wave_argmax(uint64_t &key, uint32_t &row) {
   return src;
 }
 
+// Control words behind the publication buffer: the decision of a slab (preset with
+// the buffer), and 1 + the first column of the last slab taken alone, 0 if none was.
+constexpr int kSlabControl = 2;
+constexpr uint64_t kSlabTogether = 1, kSlabAlone = 2;
+constexpr int64_t kSlabSpins = int64_t(1) << 24;
+__device__ __forceinline__ uint64_t look(const uint64_t *word) {
+  return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr int kLeaveSlab = 1, kTakeSlab = 2;  // what a workgroup of a slab taken alone does
+
 template <int RPT>
 __global__ void __launch_bounds__(kSlabThreads)
     k_gepp_slab(int64_t n, double *__restrict__ A, int64_t lda, int64_t k0, int w, int groups,
-                double *pub, int64_t *__restrict__ ipiv, int32_t *__restrict__ info,
-                int64_t spin_limit, int32_t *err) {
+                double *pub, uint64_t *control, int64_t *__restrict__ ipiv,
+                int32_t *__restrict__ info, int64_t spin_limit, int32_t *err) {
   constexpr int NWAVE = kSlabThreads / 64;
   // this workgroup's candidates, one per wavefront, and the diagonal row (two
   // columns' worth, so that a column needs no barrier after its last read)
@@ -239,13 +258,14 @@ __global__ void __launch_bounds__(kSlabThreads)
   __shared__ __attribute__((aligned(16))) double sl[(kSlabGroups + 1) * kSlot];
   __shared__ uint64_t skey[2][NWAVE];
   __shared__ uint32_t srow[2][NWAVE];
-  __shared__ int expired_sh;
+  __shared__ int expired_sh, mode_sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = blockIdx.x;
+  const bool agree = groups > 1 && spin_limit >= 0;
   const uint32_t m = uint32_t(n - k0);
   const uint32_t first = uint32_t(g) * (kSlabThreads * RPT) + uint32_t(tid);
   double *S = A + k0 + k0 * lda;  // row r, column c of the slab at S[r + c lda]
-  if (tid == 0) expired_sh = 0;
+  int64_t limit = spin_limit < 0 ? spin_limit : (spin_limit < kSlabSpins ? kSlabSpins : spin_limit);
 
   double x[RPT][kSlab];
 #pragma unroll
@@ -255,14 +275,22 @@ __global__ void __launch_bounds__(kSlabThreads)
 #pragma unroll
     for (int c = 0; c < kSlab; ++c) x[r][c] = c < w ? S[rc + int64_t(c) * lda] : 0.0;
   }
+  if (tid == 0) {
+    expired_sh = mode_sh = 0;
+    const uint64_t since = agree ? look(control + 1) : 0;
+    if (since != 0)  // (this slab's own decision, or an earlier one's)
+      mode_sh = g == 0 && since != uint64_t(k0) + 1 ? kTakeSlab : kLeaveSlab;
+  }
+  if (agree) __syncthreads();
 
+  const int columns = agree && mode_sh != 0 ? 0 : w;
 #pragma unroll 1
   for (int q = 0; q < kSlab / 8; ++q) {
     // position c of a row holds column (c + 8 q) mod kSlab
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
       const int j = 8 * q + jj;
-      if (j < w) {
+      if (j < columns) {
         // ---- this workgroup's candidate for column j ----
         uint64_t key = 0;
         uint32_t row = 0xFFFFFFFFu;
@@ -295,6 +323,7 @@ __global__ void __launch_bounds__(kSlabThreads)
           }
         }
         __syncthreads();
+        if (jj == 1 && q == 0 && mode_sh != 0) limit = -1;  // (column 0 decided: alone)
         key = lane < NWAVE ? skey[buf][lane] : 0;
         row = lane < NWAVE ? srow[buf][lane] : 0xFFFFFFFFu;
         const int ww = wave_argmax<false>(key, row);
@@ -312,24 +341,45 @@ __global__ void __launch_bounds__(kSlabThreads)
             slab_publish(pj + groups * kSlot + lane, drow[lane]);
           // ---- all candidates and the diagonal row ----
           const int total = (groups + 1) * kSlot - 2;  // the diagonal row has no last two
-          bool expired = false;
-          for (int e = tid; e < total; e += kSlabThreads) {
-            double v = __hip_atomic_load(pj + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t spins = 0;
-            while (slab_unpublished(v)) {
-              if (spins >= spin_limit) {
-                expired = true;
-                v = __builtin_nan("");
-                break;
+          bool opening = jj == 0 && q == 0 && agree;
+          for (;;) {
+            const int64_t most = opening ? spin_limit : limit;
+            bool expired = false;
+            for (int e = tid; e < total; e += kSlabThreads) {
+              double v = __hip_atomic_load(pj + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              int64_t spins = 0;
+              while (slab_unpublished(v)) {
+                if (spins >= most || (opening && spins % 64 == 63 && look(control) == kSlabAlone)) {
+                  expired = true;
+                  v = __builtin_nan("");
+                  break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                ++spins;
+                v = __hip_atomic_load(pj + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               }
-              __builtin_amdgcn_s_sleep(1);
-              ++spins;
-              v = __hip_atomic_load(pj + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              sl[e] = v;
             }
-            sl[e] = v;
+            if (expired) expired_sh = 1;
+            __syncthreads();
+            if (!opening) break;
+            // the decision: this workgroup's has all candidates, or has waited enough
+            const bool all = expired_sh == 0;
+            if (tid == 0) {
+              uint64_t seen = kSlabUnpublished;
+              const bool made = __hip_atomic_compare_exchange_strong(
+                  control, &seen, all ? kSlabTogether : kSlabAlone, __ATOMIC_RELAXED,
+                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              if (made ? !all : seen == kSlabAlone) mode_sh = made ? kTakeSlab : kLeaveSlab;
+            }
+            if (all) break;  // (what was decided is read at column 1)
+            __syncthreads();
+            if (mode_sh != 0) break;
+            if (tid == 0) expired_sh = 0;  // together: the candidates are on their way
+            __syncthreads();
+            opening = false;
           }
-          if (expired) expired_sh = 1;
-          __syncthreads();
+          if (expired_sh != 0) limit = -1;
           // ---- the winner, the same in every workgroup ----
           key = 0;
           row = 0xFFFFFFFFu;
@@ -344,7 +394,7 @@ __global__ void __launch_bounds__(kSlabThreads)
         const bool pivot = key > 1;  // key 1 is magnitude zero: left unswapped
         const uint32_t p = pivot ? row : uint32_t(j);
         if (!pivot) prow = drow;
-        if (g == 0 && tid == 0) {
+        if (g == 0 && tid == 0 && mode_sh == 0) {
           ipiv[k0 + j] = k0 + int64_t(p) + 1;
           if (key == 1 && info != nullptr && *info == 0) *info = int32_t(k0 + j + 1);
         }
@@ -401,16 +451,70 @@ __global__ void __launch_bounds__(kSlabThreads)
     }
   }
 
-  const bool bad = expired_sh != 0;
-  if (bad && tid == 0 && err != nullptr)
-    __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (agree) __syncthreads();
+  if (mode_sh == 0) {
+    const bool bad = expired_sh != 0;
+    if (bad && tid == 0) {
+      if (err != nullptr)
+        __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (info != nullptr)
+        __hip_atomic_store(info, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const uint32_t row = first + uint32_t(r) * kSlabThreads;
-    if (row < m) {
+    for (int r = 0; r < RPT; ++r) {
+      const uint32_t row = first + uint32_t(r) * kSlabThreads;
+      if (row < m) {
 #pragma unroll
-      for (int c = 0; c < kSlab; ++c)
-        if (c < w) S[row + int64_t(c) * lda] = bad ? __builtin_nan("") : x[r][c];
+        for (int c = 0; c < kSlab; ++c)
+          if (c < w) S[row + int64_t(c) * lda] = bad ? __builtin_nan("") : x[r][c];
+      }
+    }
+  }
+  if (mode_sh != kTakeSlab) return;
+  // The slab by one workgroup, in memory: the same operations column by column.
+  if (tid == 0)
+    __hip_atomic_store(control + 1, uint64_t(k0) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int j = 0; j < w; ++j) {
+    __syncthreads();
+    uint64_t key = 0;
+    uint32_t row = 0xFFFFFFFFu;
+    for (uint32_t r = uint32_t(j + tid); r < m; r += kSlabThreads) {
+      const uint64_t kr = mag_key(fabs(S[r + int64_t(j) * lda]));
+      if (kr > key) {
+        key = kr;
+        row = r;
+      }
+    }
+    wave_argmax<true>(key, row);
+    if (lane == 0) {
+      skey[0][wave] = key;
+      srow[0][wave] = row;
+    }
+    __syncthreads();
+    key = lane < NWAVE ? skey[0][lane] : 0;
+    row = lane < NWAVE ? srow[0][lane] : 0xFFFFFFFFu;
+    wave_argmax<false>(key, row);
+    const uint32_t p = key > 1 ? row : uint32_t(j);
+    double *urow = sl;  // the pivot's row
+    if (tid == 0) {
+      ipiv[k0 + j] = k0 + int64_t(p) + 1;
+      if (key == 1 && info != nullptr && *info == 0) *info = int32_t(k0 + j + 1);
+    }
+    if (tid < w) {
+      const double a = S[j + int64_t(tid) * lda], b = S[p + int64_t(tid) * lda];
+      if (p != uint32_t(j)) {
+        S[j + int64_t(tid) * lda] = b;
+        S[p + int64_t(tid) * lda] = a;
+      }
+      urow[tid] = b;
+    }
+    __syncthreads();
+    const double piv = urow[j];
+    for (uint32_t r = uint32_t(j + 1 + tid); r < m; r += kSlabThreads) {
+      const double l = S[r + int64_t(j) * lda] / piv;
+      S[r + int64_t(j) * lda] = l;
+      for (int c = j + 1; c < w; ++c)
+        S[r + int64_t(c) * lda] = __builtin_fma(-l, urow[c], S[r + int64_t(c) * lda]);
     }
   }
 }
@@ -473,6 +577,7 @@ __global__ void __launch_bounds__(TPB)
     const int64_t c = c0 < k0 ? c0 : c0 + w;
     v[i] = (move && c0 < cols) ? A[cur + c * lda] : 0.0;
   }
+  __builtin_amdgcn_wave_barrier();  // every gather before any scatter
 #pragma unroll
   for (int i = 0; i < kSwapCols; ++i) {
     const int64_t c0 = wave * kSwapCols + i;
@@ -481,24 +586,31 @@ __global__ void __launch_bounds__(TPB)
   }
 }
 
-__global__ void __launch_bounds__(TPB) k_slab_reset(double *__restrict__ pub, int64_t count) {
+__global__ void __launch_bounds__(TPB)
+    k_slab_reset(double *__restrict__ pub, int64_t count, uint64_t *__restrict__ control) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) control[1] = 0;
   for (int64_t e = int64_t(blockIdx.x) * TPB + threadIdx.x; e < count;
        e += int64_t(gridDim.x) * TPB)
     pub[e] = __builtin_bit_cast(double, kSlabUnpublished);
 }
 
+// Workgroups that a slab may take: an eighth of the device's CUs (32 of 256).
+int slab_max_groups() {
+  const int g = device_cus() / 8;
+  return g < 1 ? 1 : (g < kSlabGroups ? g : kSlabGroups);
+}
 // Workgroups of a slab with m rows (0: too many rows for one launch) and the
 // rows per thread. Up to 1024 rows one workgroup takes all, with two rows per
 // thread if need be: no exchange. Above, the fewest rows per thread that
-// kSlabGroups workgroups allow (a thread's rows are updated one after another).
-int slab_groups(int64_t m, int *rpt) {
+// `most` workgroups allow (a thread's rows are updated one after another).
+int slab_groups(int64_t m, int most, int *rpt) {
   if (m <= kSlabThreads * kSlabMaxRpt) {
     *rpt = m <= kSlabThreads ? 1 : kSlabMaxRpt;
     return 1;
   }
   for (int r = 1; r <= kSlabMaxRpt; ++r) {
     const int64_t g = (m + kSlabThreads * r - 1) / (kSlabThreads * r);
-    if (g <= kSlabGroups) {
+    if (g <= most) {
       *rpt = r;
       return int(g);
     }
@@ -518,7 +630,7 @@ int64_t slab_pub_doubles(int groups) {
 constexpr int kPermWaves = 16;
 __global__ void __launch_bounds__(64 * kPermWaves)
     k_ipiv_to_perm(int64_t n, const int64_t *__restrict__ ipiv, int64_t *perm) {
-  extern __shared__ int32_t p_lds[];
+  HIP_DYNAMIC_SHARED(int32_t, p_lds)
   __shared__ int64_t mpos[kPermWaves][64], mcur[kPermWaves][64];
   const bool in_lds = n <= kPermLdsMax;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -581,14 +693,13 @@ size_t gepp_scratch_bytes() {
 }
 
 // Workgroups of the largest slab of an n x n matrix that is one launch.
-static int max_slab_groups(int64_t n) {
-  int rpt = 1;
-  const int g = slab_groups(n, &rpt);
-  const int one = int((n + kSlabThreads - 1) / kSlabThreads);  // (fewer rows a thread later on)
-  return g == 0 || one > kSlabGroups ? kSlabGroups : one;
+static int largest_slab_groups(int64_t n, int most) {
+  const int64_t one = (n + kSlabThreads - 1) / kSlabThreads;  // (one row a thread)
+  return one > most ? most : int(one);
 }
 size_t gepp_slab_bytes(int64_t n) {
-  return size_t(slab_pub_doubles(max_slab_groups(n))) * sizeof(double);
+  const int64_t count = slab_pub_doubles(largest_slab_groups(n, slab_max_groups()));
+  return count == 0 ? 0 : size_t(count + kSlabControl) * sizeof(double);
 }
 
 hipError_t launch_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv, int32_t *info,
@@ -599,7 +710,10 @@ hipError_t launch_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv, int32_t
                                               align256(size_t(kPivotGroups) * sizeof(double)));
   double *pub = static_cast<double *>(scratch);
   const bool slabs = scratch_bytes >= gepp_slab_bytes(n);
-  const int64_t count = slab_pub_doubles(max_slab_groups(n));
+  const int most = slab_max_groups();
+  const int64_t count = slab_pub_doubles(largest_slab_groups(n, most));
+  uint64_t *control = reinterpret_cast<uint64_t *>(pub + count);
+  const int64_t preset = count == 0 ? 0 : count + 1;  // the buffer and the slab's decision
   bool fresh = false;  // the publication buffer is preset for the next slab
   for (int64_t k0 = 0; k0 < n; k0 += kNB) {
     const int64_t kend = k0 + kNB < n ? k0 + kNB : n;
@@ -608,24 +722,23 @@ hipError_t launch_gepp(int64_t n, double *A, int64_t lda, int64_t *ipiv, int32_t
       const int w = int(kend - k < kSlab ? kend - k : kSlab);
       const int64_t m = n - k;
       int rpt = 1;
-      const int groups = slabs ? slab_groups(m, &rpt) : 0;
+      const int groups = slabs ? slab_groups(m, most, &rpt) : 0;
       if (groups > 0) {
         if (groups > 1 && !fresh)
-          hipLaunchKernelGGL(k_slab_reset, dim3(64), dim3(TPB), 0, s, pub, count);
+          hipLaunchKernelGGL(k_slab_reset, dim3(64), dim3(TPB), 0, s, pub, preset, control);
         const dim3 grid{unsigned(groups)}, block{kSlabThreads};
-        const int64_t limit = sweep_spin_limit();
-        const int64_t spin = limit > 0 && limit < INT64_MAX / 16 ? 16 * limit : limit;
+        const int64_t spin = sweep_spin_limit();
         if (rpt == 1)
           hipLaunchKernelGGL((k_gepp_slab<1>), grid, block, 0, s, n, A, lda, k, w, groups, pub,
-                             ipiv, info, spin, err);
+                             control, ipiv, info, spin, err);
         else
           hipLaunchKernelGGL((k_gepp_slab<2>), grid, block, 0, s, n, A, lda, k, w, groups, pub,
-                             ipiv, info, spin, err);
+                             control, ipiv, info, spin, err);
         const int64_t waves = (n - w + kSwapCols - 1) / kSwapCols;
         if (waves > 0) {
           const int64_t grid_swap = (waves + TPB / 64 - 1) / (TPB / 64);
           hipLaunchKernelGGL(k_gepp_swap, dim3(unsigned(grid_swap)), dim3(TPB), 0, s, n, A, lda,
-                             k, w, ipiv, pub, count);
+                             k, w, ipiv, pub, preset);
           fresh = true;
         }
       } else {

@@ -29,7 +29,7 @@ def build(exe=EXE, csrc=emu.CSRC, sources=SOURCES, driver="emu_blocks.cpp", watc
     inputs += [os.path.join(emu.HERE, "include", "hip", "hip_runtime.h"), os.path.abspath(__file__)]
     if os.path.exists(exe) and all(os.path.getmtime(f) < os.path.getmtime(exe) for f in inputs):
         return exe
-    cmd = [cc, "-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer",
+    cmd = [cc, "-std=c++17", "-O2", "-g", "-fsanitize=address", "-fno-omit-frame-pointer",
            "-ffp-contract=off", "-Wno-psabi",
            f"-I{os.path.join(emu.HERE, 'include')}",
            f"-I{os.path.join(emu.ROOT, 'include')}", f"-I{csrc}", "-x", "c++", *srcs, *ours, "-o", exe]
@@ -45,7 +45,8 @@ def run(exe, payload, env=None, timeout=120):
         fin, fout = os.path.join(d, "in"), os.path.join(d, "out")
         with open(fin, "wb") as f:
             f.write(payload)
-        e = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1", **(env or {}))
+        e = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:"
+                 "detect_stack_use_after_return=0", **(env or {}))
         r = subprocess.run([exe, fin, fout], capture_output=True, text=True, timeout=timeout, env=e)
         if r.returncode:
             raise RuntimeError(f"host build exited with {r.returncode}:\n{r.stderr[-4000:]}")

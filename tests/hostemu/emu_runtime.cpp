@@ -18,6 +18,7 @@
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
+#include <mutex>
 #include <thread>
 #include <vector>
 
@@ -163,16 +164,34 @@ void fiber_main() {
   fail("finished fiber resumed");
 }
 
+// Fiber stacks of host threads that have ended, for the next launch's.
+std::mutex g_stacks_mu;
+std::vector<char *> g_stacks;
+char *take_stack() {
+  {
+    std::lock_guard<std::mutex> lock(g_stacks_mu);
+    if (!g_stacks.empty()) {
+      char *p = g_stacks.back();
+      g_stacks.pop_back();
+      return p;
+    }
+  }
+  void *p = mmap(nullptr, kStack, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (p == MAP_FAILED) fail("mmap of a fiber stack failed");
+  return static_cast<char *>(p);
+}
+void give_stacks() {
+  std::lock_guard<std::mutex> lock(g_stacks_mu);
+  for (Fiber &F : g_blk.f) g_stacks.push_back(F.stack);
+  g_blk.f.clear();
+}
+
 void run_block(unsigned n, dim3 block) {
   Block &B = g_blk;
   if (B.f.size() < n) {
     const size_t old = B.f.size();
     B.f.resize(n);
-    for (size_t i = old; i < n; ++i) {
-      void *p = mmap(nullptr, kStack, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
-      if (p == MAP_FAILED) fail("mmap of a fiber stack failed");
-      B.f[i].stack = static_cast<char *>(p);
-    }
+    for (size_t i = old; i < n; ++i) B.f[i].stack = take_stack();
   }
   B.n = n;
   B.live = int(n);
@@ -305,6 +324,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &body) {
       blockIdx = Index{b % grid.x, (b / grid.x) % grid.y, b / (grid.x * grid.y)};
       run_block(n, block);
     }
+    give_stacks();
   };
   std::vector<std::thread> pool;
   for (unsigned t = 0; t < nthreads; ++t) pool.emplace_back(worker);

@@ -29,13 +29,15 @@
 #define __noinline__ __attribute__((noinline))
 #define __launch_bounds__(...)
 #define __shared__ static thread_local
+// (dynamic LDS: what the largest workgroup of the device may have)
+#define HIP_DYNAMIC_SHARED(type, var) static thread_local type var[160 * 1024 / sizeof(type)];
 
 struct dim3 {
   unsigned x, y, z;
   constexpr dim3(unsigned x_ = 1, unsigned y_ = 1, unsigned z_ = 1) : x(x_), y(y_), z(z_) {}
 };
 
-enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorLaunchFailure = 719 };
+enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorInvalidConfiguration = 9, hipErrorLaunchFailure = 719 };
 typedef struct emu_stream *hipStream_t;
 typedef struct emu_event *hipEvent_t;
 
