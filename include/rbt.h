@@ -468,7 +468,8 @@ int rbt_solve_backward_mixed(int64_t n, int64_t nrhs, const float *LU, int64_t l
  *   host-side way to exercise the RBT_ERR_SYNC path in tests (every kernel
  *   still exits normally). For rbt_gepp: how long the workgroups of a slab wait for
  *   each other to start before one of them takes it alone (negative: its exchanges
- *   expire instead: NaN and info -1). */
+ *   expire instead: NaN and info -1). For rbt_solve_batched: the same for the
+ *   workgroups of a team (negative: X and berr NaN). */
 #define RBT_OPT_SWEEP_SPIN_LIMIT 6
 /* RBT_OPT_MIXED_FP64_INNER: low-precision elimination and solves
  *   (rbt_solve_mixed, rbt_solve_mixed_guarded, rbt_solve_backward_mixed).

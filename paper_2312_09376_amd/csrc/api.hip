@@ -1705,7 +1705,7 @@ extern "C" int rbt_solve_batched(int64_t batch, const double *const *A, const in
   const int grid = int(most < cap ? most : cap);
   RBT_HIP_CHECK(launch_batched(batch, work, work_bytes, A, lda, B, ldb, X, ldx, depth, seed, prec,
                                tol, max_iter, iters_dev, berr_dev, info_dev, path_dev, grid,
-                               options().batch_ct2_min_n, S(stream)));
+                               options().batch_ct2_min_n, S(stream), sweep_spin_limit()));
   return 0;
 }
 

@@ -364,13 +364,13 @@ hipError_t launch_batched(int64_t batch, void *work, size_t work_bytes, const do
                           double *const *X, const int64_t *ldx, int depth, uint64_t seed,
                           int prec, double tol, int max_iter, int32_t *iters, double *berr,
                           int32_t *info, int32_t *path, int grid, int64_t ct2_min_n,
-                          hipStream_t s);
+                          hipStream_t s, int64_t spin_limit = int64_t(1) << 20);
 // Teams of workgroups on one large system: members at most, and the smallest
 // order (a member then has at least two 64-row strips of its own).
 constexpr int kBatchTeamMax = 8;
 constexpr int64_t kBatchTeamMinN = 512;
-// Words of a team's area, in doubles: barrier count, expired wait, zero pivot
-// and sweep block count (32 bits each), then
+// Words of a team's area, in doubles: barrier count, expired wait, zero pivot,
+// sweep block count and formation (32 bits each), then
 // kBatchTeamMax partial maxima of the residual (||A||_inf and three per
 // right-hand side).
 constexpr int64_t kBatchTeamHead = 8;

@@ -35,9 +35,12 @@
 // 1500: 20.7 -> 3.7 ms; 64 of them: 23.3 -> 7.7; 512 of 37 to 1500, where the
 // largest otherwise end last: 26.9 -> 20.9.)
 // Progress: a member waits for members of the same team only. Tickets are
-// taken in order, so at most one team is incomplete at any time, and every
-// workgroup outside it works on a complete team or on its own, finishes and
-// takes the next ticket.
+// taken in order, so at most one team of a launch is incomplete at any time, and
+// every workgroup outside it works on a complete team or on its own, finishes and
+// takes the next ticket. Where other work on the device keeps the launch's other
+// workgroups away, the members of that team stop waiting after the sweeps' spin
+// limit: the first of them, which always runs, solves the system by itself and the
+// others go on (team_forms). From a complete team on every wait ends.
 //
 // The host plan (rbt_batched_plan) writes the header and the descriptor
 // table; the kernel checks the header against its arguments and does
@@ -117,6 +120,7 @@ struct Args {
   int64_t granule;  // reference-size granule of the butterfly structure
   int kind, sides;  // butterfly kind (1: rotations) and sides (1: one-sided)
   int64_t ct2_min_n;  // systems with n >= this: two 64-column tiles per round
+  int64_t spin_limit; // looks that the members of a team wait for each other to start
 };
 
 // A value that is the same in every lane, moved to scalar registers: the
@@ -523,8 +527,8 @@ struct Sys {
   int64_t ldx;
   int team, rank;    // workgroups on this system, and which of them this one is
   double *tw;        // team area (team > 1)
-  uint32_t *met;     // LDS: arrivals at this team's barriers so far, and blocks
-                     // published by its sweeps so far
+  uint32_t *met;     // LDS: arrivals at this team's barriers so far, blocks
+                     // published by its sweeps so far, and whether a wait expired
 };
 // A system of one workgroup and one of a team: the functions below are built
 // for each, since the member arithmetic and the waits, where there is one
@@ -539,38 +543,77 @@ struct TeamSys : Sys {
   __device__ __forceinline__ int member() const { return int(wave_uniform(rank)); }
 };
 
+// Words of the team area: arrivals at its barriers, an expired wait, first zero
+// pivot, blocks published by a sweep, and its formation.
+enum TeamWord { kTeamArrived, kTeamExpired, kTeamZeroPivot, kTeamBlocks, kTeamFormed };
+__device__ __forceinline__ uint32_t *team_word(double *tw, int i) {
+  return reinterpret_cast<uint32_t *>(tw) + i;
+}
+__device__ __forceinline__ uint32_t team_look(const uint32_t *w) {
+  return __scoped_atomic_load_n(w, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+}
+
+// Whether the team comes together: one word counts the members that have started,
+// until all have, or one that has waited for `limit` looks sets its top bit by a
+// compare-and-swap (which fails if another one arrives meanwhile). So all members
+// that ever look see the same outcome. Called by one thread. (A negative limit, under
+// which every wait expires at once, leaves the team to its expired barriers.)
+constexpr uint32_t kTeamApart = 1u << 31;
+__device__ __forceinline__ bool team_forms(double *tw, int team, int64_t limit) {
+  uint32_t *word = team_word(tw, kTeamFormed);
+  if (limit < 0) {
+    __scoped_atomic_store_n(team_word(tw, kTeamExpired), 1u, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+    return true;
+  }
+  uint32_t seen = __scoped_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) + 1;
+  for (int64_t spins = 0;; ++spins) {
+    if ((seen & kTeamApart) != 0) return false;
+    if (seen == uint32_t(team)) return true;
+    if (spins >= limit && __scoped_atomic_compare_exchange_n(word, &seen, seen | kTeamApart, false,
+                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                             __MEMORY_SCOPE_DEVICE))
+      return false;
+    __builtin_amdgcn_s_sleep(1);
+    seen = team_look(word);
+  }
+}
+
 // Barrier of the workgroups on a system; memory written before it by any of
-// them is visible after it to all. One thread arrives with a release and
-// looks on with an acquire for the whole workgroup (the workgroup's barriers
-// before and after order the others' accesses with it). The release writes
+// them is visible after it to all. Every wavefront waits for its stores, then one
+// thread arrives with a release and looks on with an acquire for the whole
+// workgroup (the workgroup's barriers before and after order the others' accesses
+// with it). The release writes
 // back and the acquire invalidates the XCD's cache for everyone on it, so there
 // is one of each per workgroup and none while looking: an acquire at every
 // look, by every wavefront, took a 512-system batch from 27 to 52 ms. The wait
-// is bounded: a barrier that expires marks the system, which then reports NaN
-// (see solve_system).
+// is bounded: one that expires marks the system, which then reports NaN (see
+// solve_system), and neither this member nor one that sees the mark waits again.
 constexpr int64_t kTeamSpins = int64_t(1) << 24;
-__device__ __forceinline__ uint32_t *team_word(const Sys &s, int i) {
-  return reinterpret_cast<uint32_t *>(s.tw) + i;
+// Looks until *count has reached target. One thread.
+__device__ __forceinline__ void team_wait(const Sys &s, const uint32_t *count, uint32_t target) {
+  if (s.met[2] != 0) return;
+  const uint32_t *expired = team_word(s.tw, kTeamExpired);
+  for (int64_t spins = 0; int32_t(team_look(count) - target) < 0; ++spins) {
+    if (spins >= kTeamSpins)
+      __scoped_atomic_store_n(team_word(s.tw, kTeamExpired), 1u, __ATOMIC_RELEASE,
+                              __MEMORY_SCOPE_DEVICE);
+    if (spins >= kTeamSpins || (spins % 64 == 63 && team_look(expired) != 0)) {
+      s.met[2] = 1;
+      return;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
 }
 __device__ __forceinline__ void team_sync(const SoloSys &) { __syncthreads(); }
 __device__ __noinline__ void team_sync(const TeamSys &s) {
+  __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores are complete
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t *count = team_word(s, 0);
+    uint32_t *count = team_word(s.tw, kTeamArrived);
     const uint32_t target = *s.met + uint32_t(s.team);
     *s.met = target;
     __scoped_atomic_fetch_add(count, 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
-    int64_t spins = 0;
-    while (int32_t(__scoped_atomic_load_n(count, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) - target) <
-           0) {
-      if (++spins > kTeamSpins) {
-        __scoped_atomic_store_n(team_word(s, 1), 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
-        break;
-      }
-#ifdef __AMDGCN__
-      __builtin_amdgcn_s_sleep(1);
-#endif
-    }
+    team_wait(s, count, target);
     (void)__scoped_atomic_load_n(count, __ATOMIC_ACQUIRE, __MEMORY_SCOPE_DEVICE);
   }
   __syncthreads();
@@ -592,29 +635,16 @@ __device__ __forceinline__ double published(const double RBT_AS_GLOBAL *p) {
 }
 __device__ __forceinline__ void team_block(const SoloSys &, bool) { __syncthreads(); }
 __device__ __noinline__ void team_block(const TeamSys &s, bool owner) {
-#ifdef __AMDGCN__
   if (owner) __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores are complete
-#endif
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t *count = team_word(s, 3);
+    uint32_t *count = team_word(s.tw, kTeamBlocks);
     const uint32_t target = s.met[1] + 1;
     s.met[1] = target;
-    if (owner) {
+    if (owner)
       __scoped_atomic_store_n(count, target, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
-    } else {
-      int64_t spins = 0;
-      while (int32_t(__scoped_atomic_load_n(count, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) -
-                     target) < 0) {
-        if (++spins > kTeamSpins) {
-          __scoped_atomic_store_n(team_word(s, 1), 1u, __ATOMIC_RELEASE, __MEMORY_SCOPE_DEVICE);
-          break;
-        }
-#ifdef __AMDGCN__
-        __builtin_amdgcn_s_sleep(1);
-#endif
-      }
-    }
+    else
+      team_wait(s, count, target);
   }
   __syncthreads();
 }
@@ -1075,7 +1105,7 @@ __device__ __noinline__ void eliminate(const S &s, double *L0, double *L1, int *
   if (team > 1) {
     // first zero pivot over the members' diagonal blocks
     if (threadIdx.x == 0 && *info_sh != 0) {
-      uint32_t *w = team_word(s, 2);
+      uint32_t *w = team_word(s.tw, kTeamZeroPivot);
       uint32_t seen = __scoped_atomic_load_n(w, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
       const uint32_t v = uint32_t(*info_sh);
       while ((seen == 0 || v < seen) &&
@@ -1085,8 +1115,7 @@ __device__ __noinline__ void eliminate(const S &s, double *L0, double *L1, int *
     }
     team_sync(s);
     if (threadIdx.x == 0)
-      *info_sh = int(__scoped_atomic_load_n(team_word(s, 2), __ATOMIC_RELAXED,
-                                            __MEMORY_SCOPE_DEVICE));
+      *info_sh = int(team_look(team_word(s.tw, kTeamZeroPivot)));
     __syncthreads();
   }
 }
@@ -1676,6 +1705,7 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, int team_in, int
   if (tid == 0) {
     *info_sh = 0;
     met_sh[0] = met_sh[1] = 0;
+    met_sh[2] = a.spin_limit < 0;
   }
   __syncthreads();
   // coefficients
@@ -1697,7 +1727,7 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, int team_in, int
       if (tid == 0) {
         *info_sh = 0;
         if (team > 1 && rank == 0)
-          __scoped_atomic_store_n(team_word(s, 2), 0u, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
+          __scoped_atomic_store_n(team_word(s.tw, kTeamZeroPivot), 0u, __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
       }
       team_sync(s);
     }
@@ -1731,8 +1761,9 @@ __device__ void solve_system(const Args &a, const BatchDesc &D, int team_in, int
   }
   if (team > 1) {
     team_sync(s);
-    // a barrier that expired: no member's results can be relied on
-    if (__scoped_atomic_load_n(team_word(s, 1), __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE) != 0) {
+    // a wait that expired: no member's results can be relied on (each member's last
+    // stores to X are these, so none of another's remain)
+    if (team_look(team_word(s.tw, kTeamExpired)) != 0) {
       be = __builtin_nan("");
       for (int64_t e = tid; e < n * s.nrhs; e += BT) s.Xm[(e % n) + (e / n) * s.ldx] = be;
     }
@@ -1754,7 +1785,8 @@ __global__ void __launch_bounds__(BT, 2) k_batched(Args a) {
   __shared__ int64_t tk_sh;
   __shared__ int info_sh;
   __shared__ double anorm_sh;
-  __shared__ uint32_t met_sh[2];
+  __shared__ uint32_t met_sh[3];
+  __shared__ int forms_sh;
   BatchHeader *hdr = reinterpret_cast<BatchHeader *>(a.work);
   // a plan for other sizes, depth or precision, or a workspace too small for
   // it: no system is solved, and every system reports it (info -1, berr NaN,
@@ -1807,6 +1839,19 @@ __global__ void __launch_bounds__(BT, 2) k_batched(Args a) {
       t = ticket - 7 * t8 - 3 * t4 - t2;
     }
     const BatchDesc D = desc[t];
+    if (team > 1) {
+      if (threadIdx.x == 0)
+        forms_sh = team_forms(dbase + D.d_off + batched_sys_doubles(D.n, D.nrhs, a.depth) -
+                                  batched_team_doubles(D.n, D.nrhs),
+                              team, a.spin_limit);
+      __syncthreads();
+      const bool forms = forms_sh != 0;
+      __syncthreads();
+      if (!forms) {
+        if (rank != 0) continue;
+        team = 1;
+      }
+    }
     // systems without work (n = 0, or no right-hand side) are not solved;
     // the plan queues them last
     if (D.n > 0 && D.nrhs > 0) {
@@ -1842,7 +1887,7 @@ __global__ void __launch_bounds__(BT) k_reset_ticket(char *work, size_t work_byt
     double *tw = dbase + D.d_off + batched_sys_doubles(D.n, D.nrhs, depth) -
                  batched_team_doubles(D.n, D.nrhs);
     uint32_t *w = reinterpret_cast<uint32_t *>(tw);
-    w[0] = w[1] = w[2] = w[3] = 0;
+    w[kTeamArrived] = w[kTeamExpired] = w[kTeamZeroPivot] = w[kTeamBlocks] = w[kTeamFormed] = 0;
   }
 }
 
@@ -1853,7 +1898,7 @@ hipError_t launch_batched(int64_t batch, void *work, size_t work_bytes, const do
                           double *const *X, const int64_t *ldx, int depth, uint64_t seed,
                           int prec, double tol, int max_iter, int32_t *iters, double *berr,
                           int32_t *info, int32_t *path, int grid, int64_t ct2_min_n,
-                          hipStream_t s) {
+                          hipStream_t s, int64_t spin_limit) {
   if (ct2_min_n < 0) return hipErrorInvalidValue;
   Args a;
   a.batch = batch;
@@ -1878,6 +1923,7 @@ hipError_t launch_batched(int64_t batch, void *work, size_t work_bytes, const do
   a.kind = butterfly_kind();
   a.sides = butterfly_sides();
   a.ct2_min_n = ct2_min_n;
+  a.spin_limit = spin_limit;
   hipLaunchKernelGGL(k_reset_ticket, dim3(1), dim3(BT), 0, s, static_cast<char *>(work), work_bytes,
                      batch, depth, prec);
   const dim3 g{unsigned(grid)}, b{unsigned(BT)};

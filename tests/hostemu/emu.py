@@ -58,7 +58,7 @@ def build(kernel_src=None, exe=EXE, csrc=CSRC, force=False):
 
 def run_batched(As, Bs, depth=2, prec=0, seed=1, tol=-10.0, max_iter=10, ct2_min_n=2 ** 63 - 1,
                 grid=None, granule=1, kind=0, sides=2, exe=EXE, timeout=300, workdir=None,
-                threads=8):
+                threads=8, spin_limit=None):
     """Solve the batch with the host build. Returns (Xs, iters, berr, info,
     path, checks) with checks = {"divergent_barriers", "ticket", "plan_intact"}
     (ticket: the queue word after the launch); raises RuntimeError with the build's report
@@ -80,8 +80,11 @@ def run_batched(As, Bs, depth=2, prec=0, seed=1, tol=-10.0, max_iter=10, ct2_min
         for a, b in zip(As, Bs):
             f.write(np.asfortranarray(a, dtype=np.float64).tobytes(order="F"))
             f.write(np.asfortranarray(b, dtype=np.float64).tobytes(order="F"))
-    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0:halt_on_error=1",
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0:halt_on_error=1:"
+               "detect_stack_use_after_return=0",
                EMU_THREADS=str(threads))
+    if spin_limit is not None:
+        env["EMU_SPIN_LIMIT"] = str(spin_limit)
     r = subprocess.run([exe, fin, fout], capture_output=True, text=True, timeout=timeout, env=env)
     os.remove(fin)
     if r.returncode:

@@ -119,10 +119,13 @@ int main(int argc, char **argv) {
   }
   std::vector<int32_t> iters(batch, -7), info(batch, -7), path(batch, -7);
   std::vector<double> berr(batch, -7.0);
+  // EMU_SPIN_LIMIT: looks that the members of a team wait for each other
+  int64_t spin_limit = int64_t(1) << 20;
+  if (const char *l = std::getenv("EMU_SPIN_LIMIT")) spin_limit = std::atoll(l);
   const hipError_t e = rbt::launch_batched(
       batch, work, z.total, A.data(), lda.data(), const_cast<const double *const *>(B.data()),
       ldb.data(), X.data(), ldx.data(), depth, seed, prec, tol, max_iter, iters.data(), berr.data(),
-      info.data(), path.data(), grid, ct2_min_n, nullptr);
+      info.data(), path.data(), grid, ct2_min_n, nullptr, spin_limit);
   if (e != hipSuccess) {
     std::fprintf(stderr, "emu_batched: launch rejected (%d)\n", int(e));
     return 2;

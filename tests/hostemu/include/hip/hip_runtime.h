@@ -151,6 +151,7 @@ extern thread_local emu::Index threadIdx, blockIdx, blockDim, gridDim;
 #define __builtin_amdgcn_s_setprio(p) ((void)0)
 #define __builtin_amdgcn_s_sleep(n) ::emu::yield_host()
 #define __builtin_amdgcn_fence(...) ((void)0)
+#define __builtin_amdgcn_s_waitcnt(n) ((void)0)
 #define __builtin_amdgcn_wave_barrier() ::emu::wave_barrier()
 #define __threadfence_block() ((void)0)
 #define __ballot(v) ::emu::ballot(v)
