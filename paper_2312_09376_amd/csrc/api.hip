@@ -119,7 +119,9 @@ struct Layout {
   size_t winv, sync, coef, resid, partial, krylov, small, total;
   size_t o_winv, o_sync, o_coef, o_resid, o_partial, o_krylov, o_small;
   // partial pivoting (the GEPP re-solve): ipiv and perm (n int64 each), a
-  // row-gather buffer (n x nrhs) and the pivot search's partial maxima
+  // row-gather buffer (n x nrhs; also the publications of sweeps for more than
+  // kSkinnyMax right-hand sides); gscr: nothing is stored there, but it belongs to
+  // the size that callers have asked for (rbt_gepp accepts it for n = 0 too)
   size_t piv, o_piv, ygat, o_ygat, gscr, o_gscr;
   size_t hstage, o_hstage, total_staged;  // BF16: operand staging of the trailing update
 };

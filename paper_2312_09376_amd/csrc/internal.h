@@ -198,11 +198,6 @@ hipError_t launch_trsm_left(TriMode mode, int kb, int64_t N, const double *T, in
                             double *B, int64_t ldb, hipStream_t s);
 hipError_t launch_trsm_left(TriMode mode, int kb, int64_t N, const float *T, int64_t ldt, float *B,
                             int64_t ldb, bool fp64_arith, hipStream_t s);
-// X U = B in place, B: M x kb
-hipError_t launch_trsm_right_upper(int kb, int64_t M, const double *T, int64_t ldt, double *B,
-                                   int64_t ldb, hipStream_t s);
-hipError_t launch_trsm_right_upper(int kb, int64_t M, const float *T, int64_t ldt, float *B,
-                                   int64_t ldb, bool fp64_arith, hipStream_t s);
 // Both solves of a panel step in one launch: Br (M x kb) <- Br U^-1 and
 // Bl (kb x N) <- L^-1 Bl with the factored block T (same ldb for both).
 hipError_t launch_panel_trsm(int kb, int64_t M, int64_t N, const double *T, int64_t ldt,

@@ -168,8 +168,8 @@ __device__ __forceinline__ void trsm_left_body(int kb, int64_t N, const TT *T, i
     B += b * bstride;
   }
   // dblk: -op(T)(i, j) of diagonal block b at b*256 + j*16 + i where pivot j
-  // updates entry i, else zero; ablk: off-diagonal block (I, J), J before I, at p*256 + lane*4 + kk = op(T)(16I + l16, 16J + 4kk +
-  // lk), p = I(I-1)/2 + J (forward) or J(J-1)/2 + I (backward)
+  // updates entry i, else zero; ablk: off-diagonal block (I, J), J before I, at
+  // p*256 + lane*4 + kk = op(T)(16I + l16, 16J + 4kk + lk), p = I(I-1)/2 + J (forward) or J(J-1)/2 + I (backward)
   C *dblk = sm.dblk;
   C *ablk = sm.oblk;
   constexpr bool FWD = forward_order<MODE>();
@@ -398,13 +398,6 @@ __device__ __forceinline__ void trsm_right_upper_body(int kb, int64_t M, const T
   }
 }
 
-template <typename TT, typename C>
-__global__ void __launch_bounds__(256, 1) k_trsm_right_upper(int kb, int64_t M, const TT *T,
-                                                             int64_t ldt, TT *B, int64_t ldb) {
-  __shared__ TrsmSmem<C> sm;
-  trsm_right_upper_body<TT, C>(kb, M, T, ldt, B, ldb, int64_t(blockIdx.x), sm);
-}
-
 // Both solves of a panel step with one factored diagonal block, which are
 // independent: L21 = A21 U11^-1 (the first gr workgroups, 64 rows each) and
 // U12 = L11^-1 A12 for the panel's columns to the right (the rest, 64
@@ -477,16 +470,6 @@ hipError_t panel_trsm_t(int kb, int64_t M, int64_t N, const TT *T, int64_t ldt, 
   return hipGetLastError();
 }
 
-template <typename TT, typename C>
-hipError_t trsm_right_upper_t(int kb, int64_t M, const TT *T, int64_t ldt, TT *B, int64_t ldb,
-                              hipStream_t s) {
-  if (kb <= 0 || M <= 0) return hipSuccess;
-  if (kb > kNB) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_trsm_right_upper<TT, C>), dim3(unsigned((M + 63) / 64)), dim3(256), 0, s,
-                     kb, M, T, ldt, B, ldb);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_trsm_left(TriMode mode, int kb, int64_t N, const double *T, int64_t ldt,
@@ -507,15 +490,6 @@ hipError_t launch_diag_inverses(int64_t n, const float *LU, int64_t ld, double *
 }
 hipError_t launch_diag_inverses(int64_t n, const float *LU, int64_t ld, float *W, hipStream_t s) {
   return diag_inverses_t(n, LU, ld, W, s);
-}
-hipError_t launch_trsm_right_upper(int kb, int64_t M, const double *T, int64_t ldt, double *B,
-                                   int64_t ldb, hipStream_t s) {
-  return trsm_right_upper_t<double, double>(kb, M, T, ldt, B, ldb, s);
-}
-hipError_t launch_trsm_right_upper(int kb, int64_t M, const float *T, int64_t ldt, float *B,
-                                   int64_t ldb, bool fp64_arith, hipStream_t s) {
-  return fp64_arith ? trsm_right_upper_t<float, double>(kb, M, T, ldt, B, ldb, s)
-                    : trsm_right_upper_t<float, float>(kb, M, T, ldt, B, ldb, s);
 }
 hipError_t launch_panel_trsm(int kb, int64_t M, int64_t N, const double *T, int64_t ldt,
                              double *Br, double *Bl, int64_t ldb, hipStream_t s) {
