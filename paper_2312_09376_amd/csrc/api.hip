@@ -1677,7 +1677,8 @@ extern "C" int rbt_batched_plan(int64_t batch, const int64_t *n, const int64_t *
   std::vector<BatchDesc> desc;
   const BatchPlanSizes z = batch_plan_sizes(batch, n, nrhs, depth, &desc);
   if (work_bytes < z.total) return RBT_ERR_WORKSPACE;
-  const std::vector<char> host = batch_plan_image(batch, depth, prec, z, desc);
+  const std::vector<char> host =
+      batch_plan_image(batch, depth, prec, z, desc, options().batch_wgs_per_cu * device_cus());
   hipStream_t s = S(stream);
   RBT_HIP_CHECK(hipMemcpyAsync(work, host.data(), host.size(), hipMemcpyHostToDevice, s));
   RBT_HIP_CHECK(hipStreamSynchronize(s));

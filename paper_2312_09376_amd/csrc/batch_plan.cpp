@@ -59,7 +59,7 @@ BatchPlanSizes batch_plan_sizes(int64_t batch, const int64_t *n, const int64_t *
 }
 
 std::vector<char> batch_plan_image(int64_t batch, int depth, int prec, const BatchPlanSizes &z,
-                                   const std::vector<BatchDesc> &desc) {
+                                   const std::vector<BatchDesc> &desc, int64_t slots) {
   std::vector<char> image(kBatchTableOffset + desc.size() * sizeof(BatchDesc), 0);
   BatchHeader h{};
   h.ticket = 0;
@@ -71,14 +71,14 @@ std::vector<char> batch_plan_image(int64_t batch, int depth, int prec, const Bat
   h.total_bytes = int64_t(z.total);
   h.f64_off_bytes = int64_t(z.f64_off);
   // Teams: a system whose own time on one workgroup is more than its fair
-  // share of the batch's (the sum over the 512 workgroups a GPU holds) would be
+  // share of the batch's (the sum over the workgroups that run at once) would be
   // what the batch waits for, so it takes the workgroups that bring it to
   // about that share. Time goes with n^3 / 3 + 200 n^2 (measured at n = 300 and
   // 1499: the n^2 part is the transform, the sweeps and the residuals).
   auto cost = [](double n) { return n * n * (n / 3.0 + 200.0); };
   double share = 0.0;
   for (const BatchDesc &D : desc)
-    if (D.nrhs > 0) share += cost(double(D.n)) / 512.0;
+    if (D.nrhs > 0) share += cost(double(D.n)) / double(slots);
   auto members = [&](const BatchDesc &D) {
     if (D.nrhs <= 0 || D.n < kBatchTeamMinN) return 1;
     const double want = cost(double(D.n)) / share;

@@ -96,6 +96,8 @@ struct StageScope {
   hipEvent_t start_ = nullptr;
 };
 
+int device_cus();  // compute units of the current device (api.hip)
+
 // ---- kernel launchers (each defined next to its kernels) ----
 
 // Preparation of a sweep's (or both sweeps' of a solve) publications: the tickets
@@ -343,9 +345,9 @@ int check_batch_sizes(int64_t batch, const int64_t *n, const int64_t *nrhs);
 BatchPlanSizes batch_plan_sizes(int64_t batch, const int64_t *n, const int64_t *nrhs, int depth,
                                 std::vector<BatchDesc> *desc);
 // The bytes rbt_batched_plan copies to the start of the workspace: header
-// (ticket 0) and descriptor table.
+// (ticket 0) and descriptor table. slots: workgroups that the device holds at once.
 std::vector<char> batch_plan_image(int64_t batch, int depth, int prec, const BatchPlanSizes &z,
-                                   const std::vector<BatchDesc> &desc);
+                                   const std::vector<BatchDesc> &desc, int64_t slots = 512);
 // BF16-operand trailing update with operands staged once (k_hgemm.hip):
 // C (FP32) -= bf16(L21) bf16(U12); K must be a multiple of 64.
 size_t hgemm_stage_bytes(int64_t M, int64_t N, int64_t K);
@@ -388,7 +390,6 @@ __host__ __device__ inline int64_t batched_sys_doubles(int64_t n, int64_t nrhs, 
 // the limit is negative).
 // launch_ipiv_to_perm turns ipiv into
 // perm[i] = original row of row i; launch_gather_rows: Y[i, :] = B[perm[i], :].
-int device_cus();  // compute units of the current device (api.hip)
 constexpr int64_t kPermLdsMax = 16384;  // ipiv_to_perm works in LDS up to this n
 size_t gepp_scratch_bytes();
 size_t gepp_slab_bytes(int64_t n);

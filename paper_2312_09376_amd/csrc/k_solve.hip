@@ -488,14 +488,14 @@ dim3 col_grid(int64_t n, int64_t nrhs) {
 // 181; 4096, 256, 294 / 341; 8191, 128, 803 / 665; 8191, 256, 1002 / 1299).
 bool few_gemm_tiles(int64_t n, int64_t nrhs) {
   const int64_t tiles = ((n + 63) / 64) * ((nrhs + 63) / 64);
-  return tiles < (n % 64 == 0 && nrhs % 64 == 0 ? 256 : 512);
+  return tiles < (n % 64 == 0 && nrhs % 64 == 0 ? 1 : 2) * int64_t(device_cus());
 }
 
 // 16-row tiles per workgroup of k_rows_product for up to 16 right-hand sides:
 // one until that makes a workgroup per compute unit, then two, which read
 // longer runs of a column (one / two tiles, us: n = 4096 32 / 39, 4097 60 / 41,
 // 8191 155 / 124).
-int rows_tiles(int64_t n) { return n <= 4096 ? 1 : 2; }
+int rows_tiles(int64_t n) { return n <= 16 * int64_t(device_cus()) ? 1 : 2; }
 
 // O = G - op(A) X or op(A) X, and the workgroups' statistics; their number.
 template <bool TRANS, bool ABS>
