@@ -544,10 +544,13 @@ int genp_fp64(int64_t n, double *A, int64_t lda, int32_t *info, hipStream_t s) {
 // block solves cost two launches per block and grow little with nrhs. Sweeps /
 // block solves, both directions of one solve, in ms: n = 5003 0.61 / 2.13 (64) and
 // 1.34 / 2.38 (384); n = 20000 5.08 / 9.56 (64), 9.8 / 12.4 (256), 13.9 / 14.4 (384) and
-// 18.4 / 16.3 (512 right-hand sides).
+// 18.4 / 16.3 (512 right-hand sides). An order of one block has no chain to save:
+// rbt_getrs at n = 50 with 17 to 384 right-hand sides takes 33 us by sweeps (the
+// inverse, the reset and two sweeps) and 19 by block solves; from two blocks on sweeps
+// are faster (n = 130: 50 and 58 us, n = 300: 58 and 119).
 constexpr int64_t kSweepWide = 384;
-bool by_sweeps(int64_t nrhs, const double *pub) {
-  return nrhs <= kSkinnyMax || (nrhs <= kSweepWide && pub != nullptr);
+bool by_sweeps(int64_t n, int64_t nrhs, const double *pub) {
+  return nrhs <= kSkinnyMax || (nrhs <= kSweepWide && n > kNB && pub != nullptr);
 }
 
 // B <- (LU)^-1 B (trans = 0) or (LU)^-T B (trans = 1): persistent sweeps with
@@ -558,7 +561,7 @@ int getrs_fp64(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B,
                int trans, const double *winv, int32_t *sync, double *pub, hipStream_t s,
                SweepOf first = SweepOf::First) {
   if (n == 0 || nrhs == 0) return 0;
-  if (by_sweeps(nrhs, pub)) {
+  if (by_sweeps(n, nrhs, pub)) {
     // one persistent launch per sweep: inverse + one refinement step per block
     double *P = nrhs <= kSkinnyMax ? nullptr : pub;
     RBT_HIP_CHECK(launch_sweep(trans ? TriMode::UT : TriMode::LN, n, nrhs, LU, ld, winv, B, ldb,
@@ -654,7 +657,7 @@ int getrs_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *B, in
 // Inverses of the diagonal blocks, needed by the solves by sweeps.
 int diag_inverses_t(int64_t n, int64_t nrhs, const double *LU, int64_t ld, double *winv,
                     const double *pub, hipStream_t s) {
-  if (!by_sweeps(nrhs, pub) || n == 0) return 0;
+  if (!by_sweeps(n, nrhs, pub) || n == 0) return 0;
   StageScope t(kStageSolve, s, 2.0 / 3.0 * double(n) * kNB * kNB);
   RBT_HIP_CHECK(launch_diag_inverses(n, LU, ld, winv, s));
   return 0;
