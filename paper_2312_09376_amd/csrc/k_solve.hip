@@ -483,12 +483,15 @@ dim3 col_grid(int64_t n, int64_t nrhs) {
 
 // Whether k_rows_product takes a residual with more than 16 right-hand sides
 // rather than a GEMM of 64 x 64 tiles: where those leave the device short of
-// work, up to one tile per compute unit if all are whole, two if some are
-// partial (n, right-hand sides, us as a GEMM / so: 5003, 64, 422 / 181; 4096, 128, 268 /
-// 181; 4096, 256, 294 / 341; 8191, 128, 803 / 665; 8191, 256, 1002 / 1299).
+// work, up to one tile per compute unit if all are whole, one and a half if some are
+// partial, whose conditional loads are slower. On 256 compute units (n, right-hand
+// sides, tiles: us as a GEMM / so), whole: 2048, 384, 192: 216 / 197; 4096, 192, 192:
+// 280 / 264; 4096, 256, 256: 295 / 339; partial: 5003, 64, 79: 424 / 187; 5003, 256,
+// 316: 576 / 460; 6000, 256, 376: 687 / 682; 8191, 192, 384: 890 / 975; 5003, 320, 395:
+// 589 / 615; 4096, 400, 448: 502 / 555; 6000, 320, 470: 743 / 890.
 bool few_gemm_tiles(int64_t n, int64_t nrhs) {
   const int64_t tiles = ((n + 63) / 64) * ((nrhs + 63) / 64);
-  return tiles < (n % 64 == 0 && nrhs % 64 == 0 ? 1 : 2) * int64_t(device_cus());
+  return 2 * tiles < (n % 64 == 0 && nrhs % 64 == 0 ? 2 : 3) * int64_t(device_cus());
 }
 
 // 16-row tiles per workgroup of k_rows_product for up to 16 right-hand sides:
