@@ -128,13 +128,14 @@ __global__ void __launch_bounds__(TPB)
 
 // ---- slab of kSlab columns in one launch ----
 //
-// What bounds it: per column, one exchange between the workgroups (a store and
-// a load through the memory side of the XCDs' caches, about 1.3 us) and two
-// workgroup reductions; the arithmetic is negligible. A column takes 2.8 us
-// (several workgroups) or 2.5 us (one, of up to 1024 rows); column by column,
+// What bounds it: one dependent chain per column, a reduction in each wavefront and
+// one over the wavefronts, the candidate's row written by one lane, barriers, a
+// division and the update. A column takes 2.1 us in one workgroup (up to 1024 rows)
+// and 2.9 in several, whose exchange goes through the memory side of the XCDs' caches
+// (a store and a load); column by column,
 // in launches of their own, it took 46 us at n = 4000 (21 of them one
 // workgroup's strided swap of two rows over all columns). The factorization
-// went from 178 to 13.8 ms at n = 4000 and from 3.78 s to 0.22 s at n = 20000.
+// went from 178 to 14 ms (0.2 of it the agreement below) at n = 4000 and from 3.78 s to 0.22 s at n = 20000.
 // Publishing a candidate from LDS as one coalesced store instead of 34 stores
 // of one lane took a column from 3.7 to 2.8 us.
 //

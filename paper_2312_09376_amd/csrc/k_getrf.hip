@@ -22,7 +22,7 @@
 // Step 0 takes the panel and its row block straight from memory while
 // wavefronts 4 to 15 stage the rest. Rows and columns beyond kb hold the
 // identity, so they never disturb the active part. Measured for 128 columns:
-// 36.7 -> 28.3 us (FP64) and 27.6 -> 21.8 us (FP32) against panel, row block and update
+// 36.7 -> 28.9 us (FP64) and 27.6 -> 23 us (FP32) against panel, row block and update
 // one after the other on eight wavefronts with the pivot rows broadcast by
 // readlane; a panel on its own takes 4200 cycles and 5000 to 7000 beside the
 // products, which share the FP64 and FP32 units with it.
