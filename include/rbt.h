@@ -152,10 +152,10 @@ int rbt_genp(int64_t n, double *A, int64_t lda, int32_t *info_dev, void *stream)
 /* Device. Solve with the factors of rbt_genp: trans = 0: B <- (L U)^-1 B;
  * trans = 1: B <- (L U)^-T B. B: n x nrhs FP64 (ldb), in place.
  * work: device scratch of rbt_workspace_size(n, nrhs, 0, RBT_FP64) bytes
- * (for nrhs <= 384 it receives the inverses of the 128 x 128 diagonal blocks,
- * which the solve applies with one step of refinement per block; for 17 to
- * 384 a workspace that ends with the sweeps' area is accepted and takes block
- * solves). */
+ * (for nrhs <= 16, and for nrhs <= 384 where n > 128, it receives the inverses of
+ * the 128 x 128 diagonal blocks, which the solve applies with one step of
+ * refinement per block; a workspace that ends with the sweeps' area is accepted
+ * for more than 16 and takes block solves). */
 int rbt_getrs(int64_t n, int64_t nrhs, const double *LU, int64_t ldlu, double *B, int64_t ldb,
               int trans, void *work, size_t work_bytes, void *stream);
 
